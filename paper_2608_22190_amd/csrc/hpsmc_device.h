@@ -584,9 +584,6 @@ template <typename T, int D> struct PathState {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kMaxStageVec = 4;   // 16-byte slab vectors staged per thread and step
-constexpr int kMmaRS = kMmaRows;  // LDS column stride (floats) of the transposed slab: odd, so
-                                  // the 32 rows a half-wave reads fall in distinct banks
-
 // Direct global -> LDS copy of a matrix-core slab image (gfx950
 // global_load_lds_dwordx4): lane i of a wave writes its 16 bytes at
 // wave_base + 16 i, so vector v of the image lands at LDS vector v.  The copy
@@ -607,58 +604,154 @@ __device__ __forceinline__ void mma_stage_wait() { asm volatile("s_waitcnt vmcnt
 // ---------------------------------------------------------------------------
 // Matrix-core contraction of one step's 2-D slab for the 64 paths of a wave.
 // For 32 paths s at points (x0_s, x1_s) and either coefficient table S (u or v):
-//     T[k0][s] = sum_{k1} S[k0][k1] L_{k1}(x1_s)     -- a (32 x K) (K x 32) product
-//     u_s      = sum_{k0} L_{k0}(x0_s) T[k0][s]
-// The product runs on v_mfma_f32_32x32x2f32 (A: lane l holds A[l%32][l/32], B:
-// B[l/32][l%32], D register r: D[8(r/4) + 4(l/32) + r%4][l%32]) with the mode
-// axis k1 split into halves of KH = ceil(P/2): at step kk lanes 0-31 supply mode
-// kk, lanes 32-63 mode KH + kk.  Paths 0-31 of the wave form one product and
-// paths 32-63 the other; permlane32 swaps move each lane's own Legendre values
-// into the operand layout and bring the rows of T back to the lane that owns
-// the path, so no lane duplicates another's work.
-// Sb: slab in LDS, transposed: Sb[c * kMmaRS + k0], c = k1 (u) or PP + k1 (v);
-// rows k0 in [P, 32) hold zeros, columns k1 in [P, PP) the slab's zero padding.
-// The image holds coefficients in the Chebyshev basis T_{k0} T_{k1} (converted
-// from the Legendre tensors on the host side), whose recurrence T_{k+1} =
-// 2x T_k - T_{k-1} has constant coefficients: one fma per basis value.
+//     T[k0][s] = sum_{k1} S[k0][k1] T_{k1}(x1_s)     -- a (32 x K) (K x 32) product
+//     u_s      = sum_{k0} T_{k0}(x0_s) T[k0][s]
+// in the Chebyshev basis (T_{k+1} = 2x T_k - T_{k-1}: one fma per basis value).
+//
+// From P = 17 on both factors of the product are split into two half-precision parts, a = a0 +
+// a1 and b = b0 + b1 (each part rounded to nearest: 23 bits together), and all
+// four partial products run on v_mfma_f32_32x32x16_f16 with FP32 accumulation.
+// The tables are scaled by a power of two so that their largest entry has
+// magnitude 2^13..2^14 (coef_scale_kernel) and the basis values by 2^10, so no
+// part that matters is subnormal.  An FP32 product (32x32x2, 64 cycles for two
+// modes) was what bounded the kernel, and it does not overlap with the vector
+// work of other waves; the four half-precision products take 32 cycles for
+// eight modes each way and partly do (P = 26: 32 products of 32x32x16 per wave
+// step and 52 more vector instructions, instead of 52 products of 32x32x2:
+// 24 x 24 x 16 nodes with 256 samples 704 -> 392 ms an iteration, P = 22 sweeps
+// 185 -> 107 ms, the Picard form 258 -> 181 ms).
+//
+// Operands of v_mfma_f32_32x32x16_f16: lane l holds A[l%32][8 (l/32) + j] and
+// B[8 (l/32) + j][l%32], j < 8 (four registers of two halves); D register r of
+// lane l: D[8(r/4) + 4(l/32) + r%4][l%32].  The sixteen K slots of a product are
+// the eight modes 8b .. 8b+7 twice: lanes 0-31 feed b0 of those modes, lanes
+// 32-63 b1, against the same A part on both halves.  Paths 0-31 of the wave form
+// one product and paths 32-63 the other: one permlane32 swap of (b0, b1) per mode
+// pair gives both operands, and swaps of the results bring the rows of T back to
+// the lane that owns the path.
+// The slab image in LDS: [table u, v][part a0, a1][block b][row k0 < 32][8 modes]
+// of halves; entries past P are zero.
+//
+// Smaller P stay on v_mfma_f32_32x32x2f32 (A: lane l holds A[l%32][l/32], B:
+// B[l/32][l%32]), where two parts would be less exact than FP32: lanes 0-31 feed
+// mode kk, lanes 32-63 mode KH + kk, from the image's FP32 columns of rows k0.
 // ---------------------------------------------------------------------------
+typedef _Float16 h16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-// B operands: Chebyshev values T_{k1}(x1) of the wave's 64 points
+// two FP32 values as halves (round to nearest), packed
+__device__ __forceinline__ uint32_t pack_h16(float a, float b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, h16x2));
+}
+// the parts that two packed halves leave, a - p.x and b - p.y, packed as halves:
+// one mixed-precision fma each.  m1 is -1 in a register the compiler does not
+// know the value of: as a constant it becomes a conversion and a subtraction.
+// (No inline assembly here: its writes are invisible to the hazard tracking of
+// products in flight, whose unused result rows the compiler reuses.)
+__device__ __forceinline__ uint32_t pack_h16_rest(float a, float b, uint32_t p, float m1)
+{
+    const h16x2 h = __builtin_bit_cast(h16x2, p);
+    return pack_h16(fmaf((float)h.x, m1, a), fmaf((float)h.y, m1, b));
+}
+__device__ __forceinline__ float opaque_minus_one()
+{
+    float m1 = -1.f;
+    asm("" : "+s"(m1));
+    return m1;
+}
+
+// registers of one lane's B operand: four per block of eight modes, or one per mode pair
+template <int KH> struct MmaB {
+    static constexpr bool SPLIT = KH >= kMmaSplitKH;
+    static constexpr int NB = (KH + 3) / 4, NR = SPLIT ? 4 * NB : KH;
+    static constexpr int VECS = SPLIT ? 128 * NB : 2 * ((KH + 1) / 2 * 4) * kMmaRows / 4;   // 16-byte vectors per image
+    uint32_t r[NR];
+    __device__ __forceinline__ h16x8 block(int b) const
+    {
+        const u32x4 q = {r[4 * b], r[4 * b + 1], r[4 * b + 2], r[4 * b + 3]};
+        return __builtin_bit_cast(h16x8, q);
+    }
+};
+
+// B operands: Chebyshev values bscale T_{k1}(x1) of the wave's 64 points in two
+// half-precision parts (b0: paths 0-31, b1: paths 32-63)
 template <int KH>
-__device__ __forceinline__ void mma_operands(float x1, int P, float (&b0)[KH], float (&b1)[KH])
+__device__ __forceinline__ void mma_operands(float x1, int P, float bscale, MmaB<KH> &b0, MmaB<KH> &b1)
 {
     static_assert(KH >= 2 && KH <= 16, "one 32-row tile, at least 4 modes");
     constexpr int K2 = 2 * KH;
-    float L[K2];
     const float x2 = x1 + x1;
-    L[0] = 1.f;
-    L[1] = x1;
+    if constexpr (!MmaB<KH>::SPLIT) {
+        float L[K2];
+        const float xx = x1 + x1;
+        L[0] = 1.f;
+        L[1] = x1;
 #pragma unroll
-    for (int k = 1; k + 1 < K2; ++k) L[k + 1] = fmaf(x2, L[k], -L[k - 1]);
-    if (P < K2) L[K2 - 1] = 0.f;   // odd P: mode P does not exist
+        for (int k = 1; k + 1 < K2; ++k) L[k + 1] = fmaf(xx, L[k], -L[k - 1]);
+        if (P < K2) L[K2 - 1] = 0.f;   // odd P: mode P does not exist
+#pragma unroll
+        for (int kk = 0; kk < KH; ++kk) {
+            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(L[kk]), __float_as_uint(L[KH + kk]), false, false);
+            b0.r[kk] = r[0];   // paths 0-31: lanes 0-31 modes kk, lanes 32-63 modes KH + kk
+            b1.r[kk] = r[1];   // paths 32-63, same split
+        }
+        return;
+    }
+    const float m1 = opaque_minus_one();
+    float lp = bscale, lc = bscale * x1;   // T_{2 kk}, T_{2 kk + 1}
 #pragma unroll
     for (int kk = 0; kk < KH; ++kk) {
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(L[kk]), __float_as_uint(L[KH + kk]), false, false);
-        b0[kk] = __uint_as_float(r[0]);   // paths 0-31: lanes 0-31 modes kk, lanes 32-63 modes KH + kk
-        b1[kk] = __uint_as_float(r[1]);   // paths 32-63, same split
+        const float hi = 2 * kk + 1 < K2 - 1 || P == K2 ? lc : 0.f;   // odd P: mode P does not exist
+        const uint32_t h = pack_h16(lp, hi);
+        const uint32_t l = pack_h16_rest(lp, hi, h, m1);
+        const auto r = __builtin_amdgcn_permlane32_swap(h, l, false, false);
+        b0.r[kk] = r[0];   // lanes 0-31: part 0 of their own point, lanes 32-63: part 1 of lane - 32's
+        b1.r[kk] = r[1];   // lanes 0-31: part 0 of lane + 32's point, lanes 32-63: part 1 of their own
+        lp = fmaf(x2, lc, -lp);
+        lc = fmaf(x2, lp, -lc);
     }
+#pragma unroll
+    for (int kk = KH; kk < MmaB<KH>::NR; ++kk) { b0.r[kk] = 0u; b1.r[kk] = 0u; }
 }
 
-// the four products (u and v tables, both path halves); UO: the u table only
+// the products of the u and v tables with both path halves; UO: the u table only.
+// The a1 part first: its sums are the small ones.
 template <int KH, bool UO = false>
-__device__ __forceinline__ void mma_issue(const float *Sb, int PP, int lane, const float (&b0)[KH],
-                                          const float (&b1)[KH], f32x16 &du0, f32x16 &dv0, f32x16 &du1, f32x16 &dv1)
+__device__ __forceinline__ void mma_issue(const float *Sb, int lane, const MmaB<KH> &b0, const MmaB<KH> &b1,
+                                          f32x16 &du0, f32x16 &dv0, f32x16 &du1, f32x16 &dv1)
 {
-    const float *Au = Sb + (lane >> 5) * KH * kMmaRS + (lane & 31);
-    const float *Av = Au + PP * kMmaRS;
     du0 = f32x16{}; dv0 = f32x16{}; du1 = f32x16{}; dv1 = f32x16{};
+    if constexpr (!MmaB<KH>::SPLIT) {
+        constexpr int PP = (KH + 1) / 2 * 4;
+        const float *Au = Sb + (lane >> 5) * KH * kMmaRows + (lane & 31), *Av = Au + PP * kMmaRows;
 #pragma unroll
-    for (int kk = 0; kk < KH; ++kk) {
-        const float au = Au[kk * kMmaRS];
-        du0 = __builtin_amdgcn_mfma_f32_32x32x2f32(au, b0[kk], du0, 0, 0, 0);
-        if constexpr (!UO) dv0 = __builtin_amdgcn_mfma_f32_32x32x2f32(Av[kk * kMmaRS], b0[kk], dv0, 0, 0, 0);
-        du1 = __builtin_amdgcn_mfma_f32_32x32x2f32(au, b1[kk], du1, 0, 0, 0);
-        if constexpr (!UO) dv1 = __builtin_amdgcn_mfma_f32_32x32x2f32(Av[kk * kMmaRS], b1[kk], dv1, 0, 0, 0);
+        for (int kk = 0; kk < KH; ++kk) {
+            const float au = Au[kk * kMmaRows], q0 = __uint_as_float(b0.r[kk]), q1 = __uint_as_float(b1.r[kk]);
+            du0 = __builtin_amdgcn_mfma_f32_32x32x2f32(au, q0, du0, 0, 0, 0);
+            if constexpr (!UO) dv0 = __builtin_amdgcn_mfma_f32_32x32x2f32(Av[kk * kMmaRows], q0, dv0, 0, 0, 0);
+            du1 = __builtin_amdgcn_mfma_f32_32x32x2f32(au, q1, du1, 0, 0, 0);
+            if constexpr (!UO) dv1 = __builtin_amdgcn_mfma_f32_32x32x2f32(Av[kk * kMmaRows], q1, dv1, 0, 0, 0);
+        }
+        return;
+    }
+    constexpr int NB = MmaB<KH>::NB;
+    const u32x4 *A = (const u32x4 *)Sb + (lane & 31);
+#pragma unroll
+    for (int part = 1; part >= 0; --part) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const h16x8 au = __builtin_bit_cast(h16x8, A[(part * NB + b) * 32]);
+            const h16x8 q0 = b0.block(b), q1 = b1.block(b);
+            du0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(au, q0, du0, 0, 0, 0);
+            du1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(au, q1, du1, 0, 0, 0);
+            if constexpr (!UO) {
+                const h16x8 av = __builtin_bit_cast(h16x8, A[((2 + part) * NB + b) * 32]);
+                dv0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, q0, dv0, 0, 0, 0);
+                dv1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, q1, dv1, 0, 0, 0);
+            }
+        }
     }
 }
 

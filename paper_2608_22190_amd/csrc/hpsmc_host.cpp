@@ -629,9 +629,29 @@ static double walk_radius(const hpsmc_plan *plan, double delta)
     return std::sqrt(2.0 * plan->d * delta);
 }
 
+// Power of two that the basis values of the 2-D matrix-core kernel's split
+// products are scaled by (1 where it runs FP32 products): 2^10 on [-1, 1]^2 (|T_k| <= 1), less when ball points may lie outside the
+// domain, so that T_k stays below the largest half; 0 when no power >= 1 does.
+static double mma_basis_scale(const hpsmc_plan *plan)
+{
+    if (!mma_split(plan->P)) return 1.0;
+    if (plan->pb.quad != HPSMC_QUAD_BALL) return 1024.0;
+    double jmax = 0.0;
+    size_t o = 0;
+    for (int iv = 0; iv < plan->n_iv; ++iv) {
+        const double h = plan->t_breaks[iv + 1] - plan->t_breaks[iv];
+        for (int l = 1; l <= plan->degree[iv]; ++l, ++o)
+            jmax = std::max(jmax, std::sqrt(2.0 * plan->d * 0.5 * (plan->xi[iv][l] + 1.0) * h / plan->nstar[o]));
+    }
+    const double lg = ((plan->P - 1) * std::acosh(1.0 + jmax)) / std::log(2.0);   // log2 of twice T_{P-1}, at most
+    const int e = std::min(10, 15 - (int)std::ceil(lg));
+    return e < 0 ? 0.0 : std::ldexp(1.0, e);
+}
+
 // whether some launch shape runs this plan's rounds on a matrix-core kernel
 static bool mma_capable(const hpsmc_plan *plan)
 {
+    if (plan->d == 2 && mma_basis_scale(plan) == 0.0) return false;
     if (plan->d == 5)
         return advance_mma5_eligible(plan->fp32, 5, plan->P, plan->pb.estimator == HPSMC_EST_PICARD,
                                      plan->pb.quad == HPSMC_QUAD_BALL, 1, 4);
@@ -645,13 +665,13 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     set.host.clear();
     std::vector<int64_t> coef_off, slab_off, slab_off_mma, src_goff;
     std::vector<double> span, delta, h2;
-    std::vector<int32_t> nst, deg;
+    std::vector<int32_t> nst, deg, blk, blk_group;
     const int64_t rows = ipow(plan->P, d - 1);
     const int64_t stride = rows * 2 * plan->PP;
     // plans a matrix-core round kernel can serve also get offsets in its slab layout
     const bool mma_ok = mma_capable(plan);
     const int extra = plan->pb.estimator == HPSMC_EST_PICARD ? 1 : 0;   // the slab of q = N* (t = t_{n-1})
-    const int64_t mstride = d == 5 ? mma5_geom(plan->P).step : mma_slab_elems(plan->PP);
+    const int64_t mstride = d == 5 ? mma5_geom(plan->P).step : mma_slab_elems(plan->P);
     int64_t slab_pos = 0, slab_pos_mma = 0, out = 0;
     // canonical output order: [iv][inst][node id]
     for (int32_t iv : ivs) {
@@ -660,7 +680,9 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
         int noff = 0;
         for (int k = 0; k < iv; ++k) noff += plan->degree[k];
         for (int inst = 0; inst < plan->n_inst; ++inst) {
+            blk_group.push_back((int32_t)coef_off.size());
             for (int l = 1; l <= M; ++l) {
+                blk.push_back((int32_t)blk_group.size() - 1);
                 const int ns = plan->nstar[noff + l - 1];
                 const double sp = 0.5 * (plan->xi[iv][l] + 1.0) * h;
                 const double dl = sp / ns;
@@ -720,6 +742,7 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
             gd.slab_mma = slab_off_mma[g];
             gd.nstar = nst[g];
             gd.c3 = set.host[g * per].c3;
+            gd.blk = blk[g];
             set.ghost.push_back(gd);
         }
     } else if (plan->pb.accel != HPSMC_ACCEL_AITKEN) {
@@ -737,7 +760,8 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     hpsmc_status st;
     if ((st = dalloc(plan, (void **)&set.dev, sizeof(NodeDesc) * set.n))) return st;
     const size_t G = set.n_groups;
-    const size_t gbytes = G * (4 * sizeof(int64_t) + 3 * sizeof(double) + 2 * sizeof(int32_t));
+    const size_t NBLK = blk_group.size();
+    const size_t gbytes = G * (4 * sizeof(int64_t) + 3 * sizeof(double) + 4 * sizeof(int32_t)) + NBLK * 32;
     if ((st = dalloc(plan, &set.group_mem, gbytes))) return st;
     std::vector<char> gh(gbytes);
     char *p = gh.data();
@@ -747,6 +771,10 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     put(nst.data(), G * 4); put(deg.data(), G * 4);
     put(slab_off_mma.data(), G * 8);
     put(src_goff.data(), G * 8);
+    put(blk.data(), G * 4);
+    p += G * 4;            // keeps the scales aligned
+    p += NBLK * 24;        // scale, inv_scale: written on the device
+    put(blk_group.data(), NBLK * 4);
     if (hipMemcpy(set.group_mem, gh.data(), gbytes, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(set.dev, set.host.data(), sizeof(NodeDesc) * set.n, hipMemcpyHostToDevice) != hipSuccess)
         return fail(HPSMC_EDEVICE, "upload of node descriptors failed");
@@ -764,6 +792,12 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     sa.slab_off_mma = mma_ok ? (const int64_t *)(gb + G * 48) : nullptr;
     sa.cs = plan->src_poly;
     sa.cs_off = (const int64_t *)(gb + G * 56);
+    sa.blk = (const int32_t *)(gb + G * 64);
+    sa.scale = (double *)(gb + G * 72);
+    sa.inv_scale = (float *)(gb + G * 72 + NBLK * 16);
+    sa.blk_group = (const int32_t *)(gb + G * 72 + NBLK * 24);
+    sa.n_blk = (int32_t)NBLK;
+    sa.bscale = d == 2 ? mma_basis_scale(plan) : 0.0;
     sa.mma_stride = mstride;
     sa.layout = 0;
     sa.extra = extra;
@@ -1216,7 +1250,7 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
     const bool k1d = set_uses_1d(plan, set);
     const size_t lds = k1d ? advance_1d_lds_bytes(plan->fp32, set.slab.slab_stride)
                      : mma == 2 ? advance_mma5_lds_bytes(plan->P)
-                     : mma ? advance_mma_lds_bytes(plan->PP)
+                     : mma ? advance_mma_lds_bytes(plan->P)
                      : plan->frac ? frac_lds_bytes(plan->fp32, plan->PP, plan->frac_kmax, plan->P, plan->frac_K,
                                                    plan->frac_nt)
                                   : (size_t)2 * ((nvec + 1) & ~1LL) * 16;
@@ -1241,6 +1275,8 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
     a.key1 = (uint32_t)(plan->pb.seed >> 32);
     a.slab_table = plan->slab_table;
     a.slab_stride = mma ? set.slab.mma_stride : set.slab.slab_stride;
+    a.inv_scale = set.slab.inv_scale;
+    a.bscale = (float)set.slab.bscale;
     a.work = plan->counters;
     a.stats = plan->counters + 1;
     a.phys = physics_of(plan);
@@ -1322,6 +1358,7 @@ static hpsmc_status slab_args_for(hpsmc_plan *plan, const NodeSet &set, int layo
     sa.cu = plan->cu_ch;
     sa.cv = plan->cv_ch;
     if (sa.cs) sa.cs = plan->cs_ch;
+    if (layout == 1 && mma_split(P)) HIP_TRY(launch_coef_scale(sa, s));
     return HPSMC_OK;
 }
 
@@ -2642,6 +2679,8 @@ static hpsmc_status adjoint_sampling(hpsmc_plan *plan, NodeSet &set, int tag, hi
     a.key1 = (uint32_t)(plan->pb.seed >> 32);
     a.slab_table = plan->slab_table;
     a.slab_stride = mfma == 2 ? set.slab.mma_stride : set.slab.slab_stride;
+    a.inv_scale = set.slab.inv_scale;
+    a.bscale = (float)set.slab.bscale;
     a.work = plan->counters;
     a.stats = plan->counters + 1;
     a.phys = physics_of(plan);

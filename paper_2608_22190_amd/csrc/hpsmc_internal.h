@@ -38,6 +38,7 @@ struct GroupDesc {
     int32_t node_begin;    // the group's nodes are [node_begin, node_begin + node_count)
     int32_t node_count;
     uint32_t c3;           // Philox counter word 3 without the tag
+    int32_t blk;           // the set's coefficient block of the group's (interval, instance)
 };
 
 // intervals of the start tables of the fractional walk's inverse incomplete
@@ -103,6 +104,8 @@ struct RoundArgs {
     uint32_t key0, key1;
     const void *slab_table;
     int64_t slab_stride;
+    const float *inv_scale;      // matrix-core images of scaled coefficients: [blk][u, v] the inverse scale
+    float bscale;                // the scale of their basis values
     unsigned long long *work;    // block work counter (zeroed by the prep kernel)
     unsigned long long *stats;   // [0] residual evaluations, [1] slot steps
     Physics phys;
@@ -132,6 +135,12 @@ struct SlabArgs {
     const int64_t *slab_off;     // per group: offset of its q = 0 slab in the table (row layout)
     const int64_t *slab_off_mma; // the same in the matrix-core layout (null when not available)
     int64_t mma_stride;          // elements per slab in the matrix-core layout
+    const int32_t *blk;          // per group: its coefficient block
+    const int32_t *blk_group;    // per coefficient block: its first group
+    int32_t n_blk;
+    double *scale;               // [blk][u, v] power of two that the image's coefficients are multiplied by
+    float *inv_scale;            // [blk][u, v] 1 / (scale bscale)
+    double bscale;
     int32_t layout;              // 0: rows [k0][u: PP][v: PP]; 1: matrix-core layout
     int32_t extra;               // slabs past N* per group (1 for the Picard form: q = N*, t_{n-1})
     const double *span;          // per group: t_{n,l} - t_{n-1}
@@ -150,6 +159,7 @@ hipError_t launch_mode_product(const double *in, double *out, int64_t outer, int
                                int64_t inner, const double *mat, double alpha, int accumulate,
                                hipStream_t s);
 hipError_t launch_slabs(const SlabArgs &a, int fp32, int max_nstar, hipStream_t s);
+hipError_t launch_coef_scale(const SlabArgs &a, hipStream_t s);
 hipError_t launch_sample(const SampleArgs &a, int fp32, int samples_per_lane, int waves_per_block,
                          int blocks, hipStream_t s);
 hipError_t launch_reduce_update(const double *part, int chunks, int mode, const NodeDesc *nodes, int64_t n_nodes,
@@ -182,12 +192,24 @@ size_t advance_1d_lds_bytes(int fp32, int64_t slab_stride);
 // matrix-core form of the round kernel: FP32, d = 2, P <= 32, whole slab per
 // LDS buffer, one path per lane
 bool advance_mma_eligible(int fp32, int dim, int P, int cf, int samples_per_lane, int waves_per_block);
-size_t advance_mma_lds_bytes(int PP);
-// matrix-core slab layout: 2 PP columns (u modes k1, then v modes k1) of
-// kMmaRows rows k0 (zeros past P), stored as the kernel's LDS image; the
-// coefficients are those of the Chebyshev basis T_{k0} T_{k1}
+size_t advance_mma_lds_bytes(int P);
+// matrix-core slab layout (d = 2), the kernel's LDS image of one step, coefficients of
+// T_{k0} T_{k1}.  P >= 17: halves [table u, v][part 0, 1][block of 8 modes
+// k1][row k0 < 32][8 modes], the two parts a0 + a1 of the scaled coefficients;
+// smaller P: FP32 columns (u modes k1, then v modes k1) of 33 rows k0.  Zeros past P.
+// The line: against 64 bits (random and decaying tables) the split products'
+// rms error is 1.1-1.15 times the FP32 products' at P = 5 and 10, the same at 14,
+// and 0.93-0.99, 0.92-0.96, 0.87-0.97, 0.83-0.95 of it at P = 18, 22, 26, 32.
 constexpr int kMmaRows = 33;
-inline int64_t mma_slab_elems(int PP) { return (int64_t)2 * PP * kMmaRows; }
+constexpr int kMmaSplitKH = 9;   // from this ceil(P / 2) on
+constexpr bool mma_split(int P) { return (P + 1) / 2 >= kMmaSplitKH; }
+constexpr int mma_blocks(int P) { return (P + 7) / 8; }
+constexpr int64_t mma_slab_elems(int P)   // in floats
+{
+    return mma_split(P) ? (int64_t)512 * mma_blocks(P) : (int64_t)2 * ((P + 3) / 4 * 4) * kMmaRows;
+}
+// largest exponent e of |scaled coefficient| < 2^e
+constexpr int kMmaScaleExp = 14;
 
 // Five-dimensional matrix-core slab layout.  A step's image is a sequence of
 // NCH chunks, each a 32-row tile of the u coefficients followed by the same

@@ -320,9 +320,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MFMA ?
 // ===========================================================================
 // Two-dimensional FP32 form with u* on the matrix cores as well: the lanes
 // read the u-table operands of the forward kernel's contraction (32 rows k0
-// per column k1, Chebyshev basis) straight from the slab image in the matrix-core
-// layout (coalesced 128-byte rows, L2-resident: every block of a group reads
-// the same image), and run its products and epilogue in the same order
+// per block of eight columns k1, Chebyshev basis, two half-precision parts)
+// straight from the slab image in the matrix-core layout (coalesced 512-byte
+// rows, L2-resident: every block of a group reads the same image), and run its products and epilogue in the same order
 // -- so u*(X_q), and with it f'(u*), is bit for bit the forward kernel's.  No
 // slab passes through LDS.  The weighted outer products stack the u and v
 // factors as one set of rows in 16 x 16 tiles (P = 18: six tiles of 256 sums
@@ -365,8 +365,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) a
     const State *sin = (const State *)a.state_in;
     State *sout = (State *)a.state_out;
     float *sbar = (float *)aa.slab_bar;
-    // this lane's u-table operands in a step's image: column (lane / 32) KH + kk, row lane % 32
-    const int aoff = (lane >> 5) * KH * kMmaRS + (lane & 31);
+    // this lane's u-table operands in a step's image: row lane % 32 of every block
+    // (FP32 form: column (lane / 32) KH + kk)
+    constexpr bool SPLIT = MmaB<KH>::SPLIT;
+    constexpr int NB = MmaB<KH>::NB, NA = SPLIT ? 2 * NB : 1, NF = SPLIT ? 1 : KH;
+    const int aoff = (lane >> 5) * KH * kMmaRows + (lane & 31);
 
     for (;;) {
         __syncthreads();
@@ -391,6 +394,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) a
         const int64_t live = a.round == 0 ? (int64_t)G->node_count * a.mcount : (int64_t)a.live_in[g];
         const float *gtab = (const float *)a.slab_table + G->slab_mma;
         float *gbar = sbar + G->slab;
+        float iu = 1.f;
+        if constexpr (SPLIT) iu = a.inv_scale[2 * G->blk];
 
         float x0 = 0.f, x1 = 0.f, lam = 0.f;
         uint32_t node = 0, sample = 0, c0 = 0;
@@ -416,9 +421,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) a
         for (int q = q0; q < q1; ++q) {
             // this step's operands, in flight under the walk step
             const float *gq = gtab + (int64_t)q * a.slab_stride;   // uniform: lanes add a 32-bit offset
-            float au[KH];
+            u32x4 au[NA];
+            float af[NF];
 #pragma unroll
-            for (int kk = 0; kk < KH; ++kk) au[kk] = gq[aoff + kk * kMmaRS];
+            for (int k = 0; k < NA; ++k)
+                if constexpr (SPLIT) au[k] = ((const u32x4 *)gq)[k * 32 + (lane & 31)];
+#pragma unroll
+            for (int kk = 0; kk < NF; ++kk)
+                if constexpr (!SPLIT) af[kk] = gq[aoff + kk * kMmaRows];
             if ((q & 3) == 0 || q == q0) philox(c0, sample, (uint32_t)(q >> 2), c3, a.key0, a.key1, w);
             const int wi = q & 3;
             const uint32_t word = wi == 0 ? w[0] : wi == 1 ? w[1] : wi == 2 ? w[2] : w[3];
@@ -432,16 +442,27 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) a
             // ---- weights of this evaluation: lambda Delta/M f'(u*(X_q)) and lambda Delta/M
             float wu = 0.f, wv = 0.f;
             if (__ballot(alive) != 0ull) {
-                float b0[KH], b1[KH];
-                mma_operands<KH>(x1, P, b0, b1);
+                MmaB<KH> b0, b1;
+                mma_operands<KH>(x1, P, a.bscale, b0, b1);
                 f32x16 du0 = {}, du1 = {}, dv = {};
+                if constexpr (SPLIT) {
 #pragma unroll
-                for (int kk = 0; kk < KH; ++kk) {
-                    du0 = __builtin_amdgcn_mfma_f32_32x32x2f32(au[kk], b0[kk], du0, 0, 0, 0);
-                    du1 = __builtin_amdgcn_mfma_f32_32x32x2f32(au[kk], b1[kk], du1, 0, 0, 0);
+                    for (int k = 0; k < NA; ++k) {   // part 1 of every block, then part 0, as in mma_issue
+                        const int b = k % NB;
+                        const h16x8 a8 = __builtin_bit_cast(h16x8, au[(k < NB ? NB : 0) + b]);
+                        du0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a8, b0.block(b), du0, 0, 0, 0);
+                        du1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a8, b1.block(b), du1, 0, 0, 0);
+                    }
+                } else {
+#pragma unroll
+                    for (int kk = 0; kk < KH; ++kk) {
+                        du0 = __builtin_amdgcn_mfma_f32_32x32x2f32(af[kk], __uint_as_float(b0.r[kk]), du0, 0, 0, 0);
+                        du1 = __builtin_amdgcn_mfma_f32_32x32x2f32(af[kk], __uint_as_float(b1.r[kk]), du1, 0, 0, 0);
+                    }
                 }
                 float u = 0.f, v = 0.f;
                 mma_epilogue<KH, true>(du0, dv, du1, dv, x0, u, v);
+                if constexpr (SPLIT) u *= iu;
                 if (alive) {
                     wv = lam;
                     wu = lam * fprime_of<float>(a.phys, u);

@@ -1,4 +1,4 @@
-// Matrix-core form of the 2-D FP32 round kernel (v_mfma_f32_32x32x2f32).
+// Matrix-core form of the 2-D FP32 round kernel (v_mfma_f32_32x32x16_f16 on split factors).
 #include "hpsmc_device.h"
 
 namespace hpsmc {
@@ -28,8 +28,8 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
     __shared__ long long s_item;
     __shared__ SrcTime<float> s_tf[256];   // source time factors of a window of blockDim.x steps
-    const int mbuf = 2 * a.PP * kMmaRS;   // floats per LDS buffer (slab image)
-    const int mvec = mbuf / 4;            // 16-byte vectors per buffer
+    constexpr int mvec = MmaB<KH>::VECS;                 // 16-byte vectors per LDS buffer (slab image)
+    constexpr int svec = PIC ? mvec / 2 : mvec;         // of which staged: the Picard form reads the u table only
     cptr<GroupDesc> groups = as_const(a.groups);
     cptr<NodeDesc> nodes = as_const(a.nodes);
     const int64_t total = a.batch_prefix[a.n_groups];
@@ -60,6 +60,11 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
         const uint32_t c3 = G->c3 | (uint32_t)a.tag;
         const int64_t live = a.round == 0 ? (int64_t)G->node_count * a.mcount : (int64_t)a.live_in[g];
         const float *gtab = (const float *)a.slab_table + G->slab_mma;
+        float iu = 1.f, iv = 1.f;
+        if constexpr (MmaB<KH>::SPLIT) {
+            iu = a.inv_scale[2 * G->blk];
+            iv = a.inv_scale[2 * G->blk + 1];
+        }
 
         // ---- this lane's path
         const int64_t p = b * a.batch + tid;
@@ -88,7 +93,7 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
             if (qq < q1) s_tf[tid] = source_time<float>(a.phys, (float)(t_prev + (span - (double)qq * ddelta)));
         };
         fill_time(q0);
-        mma_stage((const u32x4 *)(gtab + (int64_t)q0 * a.slab_stride), lds, mvec, tid, nthr);
+        mma_stage((const u32x4 *)(gtab + (int64_t)q0 * a.slab_stride), lds, svec, tid, nthr);
         float ex0 = x0, ex1 = x1;   // where the current step's integrand is evaluated
         if constexpr (BALL) {
             if (alive) {
@@ -98,8 +103,8 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                 ex1 = fmaf(J, off[1], x1);
             }
         }
-        float b0[KH], b1[KH];
-        mma_operands<KH>(ex1, a.P, b0, b1);
+        MmaB<KH> b0, b1;
+        mma_operands<KH>(ex1, a.P, a.bscale, b0, b1);
         mma_stage_wait();
         __syncthreads();
 
@@ -116,13 +121,13 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
             const uint32_t word = wi == 0 ? w[0] : wi == 1 ? w[1] : wi == 2 ? w[2] : w[3];
             const int buf = (q - q0) & 1;
             if (q + 1 < q1)
-                mma_stage((const u32x4 *)(gtab + (int64_t)(q + 1) * a.slab_stride), lds + (buf ^ 1) * mvec, mvec, tid,
+                mma_stage((const u32x4 *)(gtab + (int64_t)(q + 1) * a.slab_stride), lds + (buf ^ 1) * mvec, svec, tid,
                           nthr);
             float u = 0.f, v = 0.f, y0 = x0, y1 = x1, nx0 = x0, nx1 = x1;
             bool inside = false;
             if (__ballot(alive) != 0ull) {
                 f32x16 du0, dv0, du1, dv1;
-                mma_issue<KH, PIC>((const float *)lds + buf * mbuf, a.PP, lane, b0, b1, du0, dv0, du1, dv1);
+                mma_issue<KH, PIC>((const float *)(lds + buf * mvec), lane, b0, b1, du0, dv0, du1, dv1);
                 // under the products: direction, jump, exit test, next operands
                 float d0, d1;
                 angle_dir(u01(word, 0.f), d0, d1);
@@ -139,11 +144,15 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                         nx1 = fmaf(J, off[1], y1);
                     }
                 }
-                float nb0[KH], nb1[KH];
-                mma_operands<KH>(nx1, a.P, nb0, nb1);
+                MmaB<KH> nb0, nb1;
+                mma_operands<KH>(nx1, a.P, a.bscale, nb0, nb1);
                 mma_epilogue<KH, PIC>(du0, dv0, du1, dv1, ex0, u, v);
-#pragma unroll
-                for (int kk = 0; kk < KH; ++kk) { b0[kk] = nb0[kk]; b1[kk] = nb1[kk]; }
+                if constexpr (MmaB<KH>::SPLIT) {
+                    u *= iu;
+                    v *= iv;
+                }
+                b0 = nb0;
+                b1 = nb1;
             }
             ++slots;
             if (alive) {
@@ -175,16 +184,17 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
         if constexpr (PIC) {
             if (q1 == nstar && q == q1) {
                 __syncthreads();
-                mma_stage((const u32x4 *)(gtab + (int64_t)nstar * a.slab_stride), lds, mvec, tid, nthr);
+                mma_stage((const u32x4 *)(gtab + (int64_t)nstar * a.slab_stride), lds, svec, tid, nthr);
                 mma_stage_wait();
                 __syncthreads();
                 if (__ballot(alive) != 0ull) {
-                    float tb0[KH], tb1[KH];
-                    mma_operands<KH>(x1, a.P, tb0, tb1);
+                    MmaB<KH> tb0, tb1;
+                    mma_operands<KH>(x1, a.P, a.bscale, tb0, tb1);
                     f32x16 du0, dv0, du1, dv1;
-                    mma_issue<KH, true>((const float *)lds, a.PP, lane, tb0, tb1, du0, dv0, du1, dv1);
+                    mma_issue<KH, true>((const float *)lds, lane, tb0, tb1, du0, dv0, du1, dv1);
                     float u = 0.f, v = 0.f;
                     mma_epilogue<KH, true>(du0, dv0, du1, dv1, x0, u, v);
+                    if constexpr (MmaB<KH>::SPLIT) u *= iu;
                     if (alive) {
                         const float yc = u - comp;
                         const float tt = acc + yc;
@@ -249,7 +259,7 @@ bool advance_mma_eligible(int fp32, int dim, int P, int cf, int samples_per_lane
            waves_per_block <= 4;
 }
 
-size_t advance_mma_lds_bytes(int PP) { return (size_t)2 * 2 * PP * kMmaRS * sizeof(float); }
+size_t advance_mma_lds_bytes(int P) { return (size_t)2 * mma_slab_elems(P) * sizeof(float); }
 
 hipError_t launch_adv_mma(const RoundArgs &a, dim3 grid, dim3 block, size_t lds, hipStream_t s)
 {

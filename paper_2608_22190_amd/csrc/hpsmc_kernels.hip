@@ -320,6 +320,53 @@ hipError_t launch_mode_product(const double *in, double *out, int64_t outer, int
 // ---------------------------------------------------------------------------
 constexpr int kSlabQ = 32;
 
+// Power-of-two scale of the coefficient tables whose image holds two
+// half-precision parts: one block per coefficient block (interval, instance)
+// bounds every entry at every time by the sum of its time coefficients'
+// magnitudes (|L_q| <= 1) and scales the largest into [2^13, 2^14), so a part
+// loses no bits to the narrow exponent range (the parts' rounding is then
+// 2^-23 of an entry, or 2^-39 of the largest where that is more).  Exponents
+// are kept to what the inverse scale holds in FP32; non-finite coefficients
+// pass through as such.
+__global__ void __launch_bounds__(256) coef_scale_kernel(SlabArgs a)
+{
+    __shared__ double sm[256];
+    const int blk = blockIdx.x, g = a.blk_group[blk], tid = threadIdx.x;
+    const int T1 = a.deg[g] + 1;
+    const int64_t n = (int64_t)a.rows * a.P;
+    for (int uv = 0; uv < 2; ++uv) {
+        const double *c = (uv ? a.cv : a.cu) + a.coef_off[g];
+        const double *cs = uv && a.cs ? a.cs + a.cs_off[g] : nullptr;
+        double mx = 0.0;
+        for (int64_t e = tid; e < n; e += blockDim.x) {
+            double sum = 0.0;
+            for (int k = 0; k < T1; ++k) sum += fabs(cs ? c[e * T1 + k] + cs[e * T1 + k] : c[e * T1 + k]);
+            mx = fmax(mx, sum);
+        }
+        sm[tid] = mx;
+        __syncthreads();
+        for (int o = 128; o > 0; o >>= 1) {
+            if (tid < o) sm[tid] = fmax(sm[tid], sm[tid + o]);
+            __syncthreads();
+        }
+        if (tid == 0) {
+            const double m = sm[0];
+            int e = m > 0.0 && m < 1e300 ? ilogb(m) + 1 : 0;
+            e = max(-100, min(127, e));
+            a.scale[2 * blk + uv] = ldexp(1.0, kMmaScaleExp - e);
+            a.inv_scale[2 * blk + uv] = (float)(ldexp(1.0, e - kMmaScaleExp) / a.bscale);
+        }
+        __syncthreads();
+    }
+}
+
+hipError_t launch_coef_scale(const SlabArgs &a, hipStream_t s)
+{
+    if (a.n_blk <= 0) return hipSuccess;
+    hipLaunchKernelGGL(coef_scale_kernel, dim3((unsigned)a.n_blk), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
 {
@@ -336,6 +383,11 @@ __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
     const double *cu = a.cu + a.coef_off[g], *cv = a.cv + a.coef_off[g];
     const double *cs = a.cs ? a.cs + a.cs_off[g] : nullptr;   // polynomial source, folded into v
     const double span = a.span[g], delta = a.delta[g], h2 = a.h2[g];
+    // matrix-core image of halves (layout 1, P >= 17): an entry is one coefficient, its
+    // two parts go to two places, and a lane pair trades parts for 4-byte stores
+    const bool split = mma && mma_split(a.P);
+    const int nb = mma_blocks(a.P);
+    const double sc[2] = {split ? a.scale[2 * a.blk[g]] : 1.0, split ? a.scale[2 * a.blk[g] + 1] : 1.0};
     for (int q0 = blockIdx.x * kSlabQ; q0 < nq; q0 += gridDim.x * kSlabQ) {
         const int qn = min(kSlabQ, nq - q0);
         __syncthreads();   // the previous chunk's reads of Lt are over
@@ -358,11 +410,16 @@ __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
             if (mma5) {  // 32-row tiles over (k0, k1, k2), columns (k3, k4)
                 live = mma5_source(g5, e, uv, row, kl);
             } else {
-                if (mma) {   // column c = uv * PP + k1 of kMmaRows rows k0
+                if (mma && !split) {   // column c = uv * PP + k1 of kMmaRows rows k0
                     const int c = (int)(e / kMmaRows);
                     row = e - (int64_t)c * kMmaRows;
                     uv = c / a.PP;
                     kl = c - uv * a.PP;
+                } else if (mma) {   // [uv][block][row k0 < 32][mode of the block]
+                    row = (e >> 3) & 31;
+                    const int c = (int)(e >> 8);
+                    uv = c / nb;
+                    kl = 8 * (c - uv * nb) + (int)(e & 7);
                 } else {
                     row = e / (2 * a.PP);
                     const int rem = (int)(e - row * 2 * a.PP);
@@ -388,10 +445,28 @@ __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
                     }
                 }
             }
-            T *dst = table + base + (int64_t)q0 * stride + e;
+            if (split) {
+                // even lanes store part 0 of the pair of modes, odd lanes part 1
+                const int part = (int)(e & 1), c = (int)(e >> 8);
+                uint32_t *dst = (uint32_t *)table + base + (int64_t)q0 * stride +
+                                (((uv * 2 + part) * nb + (c - uv * nb)) * 128 + (int)(e >> 1 & 127));
+                const double f = uv ? sc[1] : sc[0];
 #pragma unroll
-            for (int j = 0; j < kSlabQ; ++j)
-                if (j < qn) dst[(int64_t)j * stride] = (T)acc[j];
+                for (int j = 0; j < kSlabQ; ++j) {
+                    const double v = acc[j] * f;
+                    const _Float16 h = (_Float16)(float)v;
+                    const _Float16 l = (_Float16)(float)(v - (double)(float)h);
+                    const uint32_t w = (uint32_t)__builtin_bit_cast(uint16_t, h) |
+                                       (uint32_t)__builtin_bit_cast(uint16_t, l) << 16;
+                    const uint32_t o = (uint32_t)__shfl_xor((int)w, 1, 64);
+                    if (j < qn) dst[(int64_t)j * stride] = part ? o >> 16 | (w & 0xffff0000u) : (w & 0xffffu) | o << 16;
+                }
+            } else {
+                T *dst = table + base + (int64_t)q0 * stride + e;
+#pragma unroll
+                for (int j = 0; j < kSlabQ; ++j)
+                    if (j < qn) dst[(int64_t)j * stride] = (T)acc[j];
+            }
         }
     }
 }
