@@ -581,6 +581,45 @@ template <typename T, int D> struct PathState {
     uint32_t sample;
 };
 
+// A round of few batches is split into shares: `shares` blocks walk the same
+// batch through the whole round (positions cost little next to a residual
+// evaluation and do not depend on one), share i evaluates steps q0 + i, q0 + i +
+// shares, ..., and the block that finishes last adds the shares' parts of every
+// path sum in share order and alone writes results and survivors.  (Such rounds
+// ran at the latency of one evaluation after another in a few blocks: the last
+// two thirds of the rounds of the long-time plane problem took 0.6 ms for 256
+// steps however few paths were left.)
+// Returns whether this block is the last; sum[] (this thread's parts, of the paths at
+// slot + i stride of the batch) are then the whole.  writer: the thread's parts
+// count (where several waves hold the same paths).  Called by every thread of the block.
+template <int N>
+__device__ __forceinline__ bool share_combine(const RoundArgs &a, int64_t item, int64_t batch, int shares, int bsz,
+                                              int slot, int stride, bool writer, double (&sum)[N], long long &s_flag)
+{
+    double *part = a.share_sum + item * bsz + slot;
+    if (writer) {
+#pragma unroll
+        for (int n = 0; n < N; ++n) __hip_atomic_store(part + n * stride, sum[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) s_flag = (long long)atomicAdd(a.share_done + batch, 1u);
+    __syncthreads();
+    if (s_flag != (long long)shares - 1) return false;
+    __threadfence();
+    if (writer) {
+        part = a.share_sum + batch * shares * bsz + slot;
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            double t = 0.0;
+            for (int i = 0; i < shares; ++i)
+                t += __hip_atomic_load(part + (int64_t)i * bsz + n * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            sum[n] = t;
+        }
+    }
+    return true;
+}
+
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kMaxStageVec = 4;   // 16-byte slab vectors staged per thread and step

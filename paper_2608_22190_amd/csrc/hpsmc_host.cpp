@@ -313,6 +313,9 @@ static double phi_legendre(int p, const double *L) { return 2.0 * (p + 1) / (2.0
 // ---------------------------------------------------------------------------
 // Plan
 // ---------------------------------------------------------------------------
+// paths of the largest batch: 256 threads, four paths each
+constexpr int kShareBatch = 1024;
+
 struct DevBuf {
     void *p = nullptr;
     size_t bytes = 0;
@@ -339,7 +342,7 @@ struct NodeSet {               // the nodes one sampling launch covers
     int64_t ms = 0;            // samples per slice
     void *state[2] = {nullptr, nullptr};
     uint32_t *live = nullptr;  // [2][n_groups]
-    int64_t *prefix = nullptr; // [n_groups + 1]
+    int64_t *prefix = nullptr; // [n_groups + 3]
     double *result = nullptr;  // [n][ms]
     // Aitken-relaxed update: one vector per (interval of the set, instance)
     int32_t n_vec = 0;
@@ -414,6 +417,10 @@ struct hpsmc_plan {
     size_t slab_bytes = 0;
     double *part = nullptr;
     int64_t part_elems = 0;
+    // rounds of few batches, split into shares of steps: [share_max][kShareBatch] part sums, [share_max] counters
+    double *share_sum = nullptr;
+    uint32_t *share_done = nullptr;
+    int64_t share_max = 0;
     unsigned long long *counters = nullptr;  // [0] work, [1] evals, [2] lane steps, [3] unused
     unsigned long long *maxbits = nullptr;   // [4096]
     int64_t m_probe = 0;
@@ -832,7 +839,7 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
         if ((st = dalloc(plan, &set.state[0], sb * set.n * ms))) return st;
         if ((st = dalloc(plan, &set.state[1], sb * set.n * ms))) return st;
         if ((st = dalloc(plan, (void **)&set.live, sizeof(uint32_t) * 2 * G))) return st;
-        if ((st = dalloc(plan, (void **)&set.prefix, sizeof(int64_t) * (G + 2)))) return st;
+        if ((st = dalloc(plan, (void **)&set.prefix, sizeof(int64_t) * (G + 3)))) return st;
         if ((st = dalloc(plan, (void **)&set.result, sizeof(double) * set.n * ms))) return st;
         if (hipMemcpy(set.gdev, set.ghost.data(), sizeof(GroupDesc) * G, hipMemcpyHostToDevice) != hipSuccess)
             return fail(HPSMC_EDEVICE, "upload of group descriptors failed");
@@ -1288,6 +1295,10 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
     // measured no faster.)
     const int split_batch = mma == 2 && plan->sample_split && (waves == 2 || waves == 4) ? 64 : 0;
     const int64_t split_max = blocks;
+    // shares of steps: every round kernel but the windowed 1-D and the fractional one
+    const int64_t share_max = k1d || plan->frac ? 0 : std::min<int64_t>(blocks, plan->share_max);
+    a.share_sum = plan->share_sum;
+    a.share_done = plan->share_done;
     hpsmc_plan::EvPair *ek = next_pair(plan->ev_span, plan->n_span);
     if (ek) HIP_TRY(hipEventRecord(ek->a, s));
     int first = 1;
@@ -1301,8 +1312,8 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
             a.state_out = set.state[(r + 1) & 1];
             a.live_in = set.live + (r & 1) * G;
             a.live_out = set.live + ((r + 1) & 1) * G;
-            HIP_TRY(launch_round_prep(set.gdev, G, r, C, mc, a.batch, split_batch, split_max, a.live_in, a.live_out,
-                                      set.prefix, plan->counters, s));
+            HIP_TRY(launch_round_prep(set.gdev, G, r, C, mc, a.batch, split_batch, split_max, share_max, a.live_in,
+                                      a.live_out, set.prefix, plan->share_done, plan->counters, s));
             hpsmc_plan::EvPair *ea = next_pair(plan->ev_sample, plan->n_sample);
             if (ea) HIP_TRY(hipEventRecord(ea->a, s));
             HIP_TRY(launch_advance(a, plan->fp32, ns, waves, blocks, lds, k1d ? 3 : mma, s));
@@ -1453,7 +1464,7 @@ void hpsmc_destroy(hpsmc_plan *plan)
     void *ptrs[] = {plan->U, plan->cu, plan->cv, plan->tmp0, plan->tmp1, plan->ic, plan->mats,
                     plan->slab_table, plan->part, plan->counters, plan->maxbits, plan->hist_u, plan->hist_v,
                     plan->lam, plan->cbar_u, plan->cbar_v, plan->dtarget, plan->dloss, plan->dgrad, plan->slab_bar,
-                    plan->frac_tab, plan->src_poly, plan->cu_ch, plan->cv_ch, plan->cs_ch};
+                    plan->frac_tab, plan->src_poly, plan->cu_ch, plan->cv_ch, plan->cs_ch, plan->share_sum, plan->share_done};
     for (void *p : ptrs) dfree(plan, p);
     delete plan;
 }
@@ -1548,6 +1559,11 @@ hpsmc_status hpsmc_create(const hpsmc_problem *pb, hpsmc_plan **out)
     if ((st = dalloc(pl, (void **)&pl->tmp0, tmax * 8))) return st;
     if ((st = dalloc(pl, (void **)&pl->tmp1, tmax * 8))) return st;
     if ((st = dalloc(pl, (void **)&pl->ic, I * plan->nsp * 8))) return st;
+    // the general kernel's blocks are at most four to a CU (a wave takes 100 registers or
+    // more): a grid of more blocks than that is not worth filling with shares
+    plan->share_max = 4 * (int64_t)plan->cus;
+    if ((st = dalloc(pl, (void **)&pl->share_sum, (size_t)plan->share_max * kShareBatch * 8))) return st;
+    if ((st = dalloc(pl, (void **)&pl->share_done, (size_t)plan->share_max * 4))) return st;
     if ((st = dalloc(pl, (void **)&pl->counters, 4 * 8))) return st;
     if ((st = dalloc(pl, (void **)&pl->maxbits, 4096 * 8))) return st;
     if (pl->frac && (st = frac_tables(pl))) return st;
@@ -2703,8 +2719,8 @@ static hpsmc_status adjoint_sampling(hpsmc_plan *plan, NodeSet &set, int tag, hi
             a.state_out = set.state[(r + 1) & 1];
             a.live_in = set.live + (r & 1) * G;
             a.live_out = set.live + ((r + 1) & 1) * G;
-            HIP_TRY(launch_round_prep(set.gdev, G, r, C, mc, a.batch, 0, 0, a.live_in, a.live_out, set.prefix,
-                                      plan->counters, s));
+            HIP_TRY(launch_round_prep(set.gdev, G, r, C, mc, a.batch, 0, 0, std::min<int64_t>(blocks, plan->share_max),
+                                      a.live_in, a.live_out, set.prefix, plan->share_done, plan->counters, s));
             hpsmc_plan::EvPair *ea = next_pair(plan->ev_adj, plan->n_adj);
             if (ea) HIP_TRY(hipEventRecord(ea->a, s));
             HIP_TRY(launch_adjoint(aa, plan->fp32, waves, blocks, lds, s));

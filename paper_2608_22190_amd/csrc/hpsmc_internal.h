@@ -95,7 +95,10 @@ struct RoundArgs {
     void *state_out;
     const uint32_t *live_in;     // per group, paths in state_in (round > 0)
     uint32_t *live_out;          // per group, survivors appended to state_out
-    const int64_t *batch_prefix; // [n_groups + 2] work items per group, prefix; [n_groups + 1] paths per item
+    const int64_t *batch_prefix; // [n_groups + 3] batches per group, prefix ([n_groups]: work items, batches
+                                 // times shares); [n_groups + 1] paths per batch; [n_groups + 2] shares
+    double *share_sum;           // [work item][path of the batch] each share's part of the path sums
+    uint32_t *share_done;        // [batch] shares that have written theirs
     double *result;              // [node out][mcount] path value S of each sample
     int32_t n_chunks;            // LDS chunks per slab: P^cf, the first cf dimensions fixed per chunk
     int32_t cf;
@@ -174,12 +177,15 @@ hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long 
 size_t frac_lds_bytes(int fp32, int PP, int kmax, int P, int K, int nt);
 hipError_t launch_eval(const double *cu, const double *cv, int dim, int P, int T1, double t_prev, double h,
                        const double *pts, int64_t npts, double *out, hipStream_t s);
-// batch_prefix: [n_groups + 2]; batch_split > 0 lets a round that fits in at
+// batch_prefix: [n_groups + 3]; batch_split > 0 lets a round that fits in at
 // most split_max items of batch_split paths use that batch (the 5-D
-// matrix-core kernel then splits each item's products over the block's waves)
+// matrix-core kernel then splits each item's products over the block's waves);
+// share_max > 0: a round of few batches is split into shares of steps while
+// batches times shares stay within share_max (share_done: its batch counters)
+constexpr int kMaxShares = 16;
 hipError_t launch_round_prep(const GroupDesc *groups, int32_t n_groups, int32_t round, int32_t steps,
-                             int64_t mcount, int32_t batch, int32_t batch_split, int64_t split_max,
-                             const uint32_t *live_in, uint32_t *live_out, int64_t *batch_prefix,
+                             int64_t mcount, int32_t batch, int32_t batch_split, int64_t split_max, int64_t share_max,
+                             const uint32_t *live_in, uint32_t *live_out, int64_t *batch_prefix, uint32_t *share_done,
                              unsigned long long *work, hipStream_t s);
 // kern: 0 the vector-unit kernel, 1 the 2-D matrix-core kernel, 2 the 5-D one,
 // 3 the windowed 1-D kernel

@@ -60,6 +60,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MFMA ?
     cptr<GroupDesc> groups = as_const(a.groups);
     cptr<NodeDesc> nodes = as_const(a.nodes);
     const int64_t total = a.batch_prefix[a.n_groups];
+    const int shares = (int)a.batch_prefix[a.n_groups + 2];   // a share adds its steps into the table itself: no combination
     using State = PathState<T, D>;
     const State *sin = (const State *)a.state_in;
     State *sout = (State *)a.state_out;
@@ -72,13 +73,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MFMA ?
         __syncthreads();
         const int64_t item = s_item;
         if (item >= total) break;
+        const int64_t batch = item / shares;
+        const int share = (int)(item - batch * shares);
         int lo = 0, hi = a.n_groups - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (a.batch_prefix[mid] <= item) lo = mid; else hi = mid - 1;
+            if (a.batch_prefix[mid] <= batch) lo = mid; else hi = mid - 1;
         }
         const int g = lo;
-        const int64_t b = item - a.batch_prefix[g];
+        const int64_t b = batch - a.batch_prefix[g];
         cptr<GroupDesc> G = groups + g;
         const int nstar = G->nstar;
         const int q0 = a.round * a.steps;
@@ -118,8 +121,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MFMA ?
             }
         }
         u32x4 stage[kMaxStageVec];
-        {
-            const u32x4 *src = (const u32x4 *)(gtab + (int64_t)q0 * a.slab_stride);
+        int qe = q0 + share, buf = 0;   // the next step this share evaluates, its buffer
+        if (qe < q1) {
+            const u32x4 *src = (const u32x4 *)(gtab + (int64_t)qe * a.slab_stride);
 #pragma unroll
             for (int k = 0; k < kMaxStageVec; ++k) {
                 const int64_t v = tid + (int64_t)k * nthr;
@@ -130,9 +134,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MFMA ?
 
         uint32_t w[1][4];
         for (int q = q0; q < q1; ++q) {
-            const int buf = (q - q0) & 1;
-            if (q + 1 < q1) {
-                const u32x4 *src = (const u32x4 *)(gtab + (int64_t)(q + 1) * a.slab_stride);
+            const bool ev = q == qe;   // else another share's step: the walk alone
+            if (ev) qe += shares;
+            if (ev && qe < q1) {
+                const u32x4 *src = (const u32x4 *)(gtab + (int64_t)qe * a.slab_stride);
 #pragma unroll
                 for (int k = 0; k < kMaxStageVec; ++k) {
                     const int64_t v = tid + (int64_t)k * nthr;
@@ -159,6 +164,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MFMA ?
                     inside = inside && (fabs(Y[0][i]) < (T)1);
                 }
                 alive = inside;
+            }
+            if (!ev) {
+                if (alive) {
+#pragma unroll
+                    for (int i = 0; i < D; ++i) X[0][i] = Y[0][i];
+                }
+                continue;
             }
             // ---- weights of this evaluation: lambda Delta/M f'(u*(X_q)) and lambda Delta/M
             T wu = (T)0, wv = (T)0;
@@ -226,7 +238,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MFMA ?
 #pragma unroll
                 for (int i = 0; i < D; ++i) X[0][i] = Y[0][i];
             }
-            if (q + 1 < q1) {
+            if (qe < q1) {
                 u32x4 *dst = lds + (int64_t)(buf ^ 1) * svec;
 #pragma unroll
                 for (int k = 0; k < kMaxStageVec; ++k) {
@@ -234,6 +246,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MFMA ?
                     if (v < nvec) dst[v] = stage[k];
                 }
             }
+            buf ^= 1;
             __syncthreads();
             // ---- block sum of the outer products into the slab adjoint of step q
             T *dstq = gbar + (int64_t)q * aa.bar_stride;
@@ -295,7 +308,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MFMA ?
         }
         // survivors to the next round
         {
-            const bool carry = alive && q1 < nstar;
+            const bool carry = alive && q1 < nstar && share == 0;
             const unsigned long long mask = __ballot(carry);
             if (mask != 0ull) {
                 uint32_t base = 0;
@@ -361,6 +374,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) a
     cptr<GroupDesc> groups = as_const(a.groups);
     cptr<NodeDesc> nodes = as_const(a.nodes);
     const int64_t total = a.batch_prefix[a.n_groups];
+    const int shares = (int)a.batch_prefix[a.n_groups + 2];   // a share adds its steps into the table itself: no combination
     using State = PathState<float, 2>;
     const State *sin = (const State *)a.state_in;
     State *sout = (State *)a.state_out;
@@ -377,13 +391,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) a
         __syncthreads();
         const int64_t item = s_item;
         if (item >= total) break;
+        const int64_t batch = item / shares;
+        const int share = (int)(item - batch * shares);
         int lo = 0, hi = a.n_groups - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (a.batch_prefix[mid] <= item) lo = mid; else hi = mid - 1;
+            if (a.batch_prefix[mid] <= batch) lo = mid; else hi = mid - 1;
         }
         const int g = lo;
-        const int64_t b = item - a.batch_prefix[g];
+        const int64_t b = batch - a.batch_prefix[g];
         cptr<GroupDesc> G = groups + g;
         const int nstar = G->nstar;
         const int q0 = a.round * a.steps;
@@ -418,17 +434,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) a
             lam = (float)(aa.lambda[nodes[node].u_index] * ddelta * aa.inv_M);
         }
         uint32_t w[4];
+        int qe = q0 + share;   // the next step this share evaluates
         for (int q = q0; q < q1; ++q) {
-            // this step's operands, in flight under the walk step
-            const float *gq = gtab + (int64_t)q * a.slab_stride;   // uniform: lanes add a 32-bit offset
-            u32x4 au[NA];
-            float af[NF];
-#pragma unroll
-            for (int k = 0; k < NA; ++k)
-                if constexpr (SPLIT) au[k] = ((const u32x4 *)gq)[k * 32 + (lane & 31)];
-#pragma unroll
-            for (int kk = 0; kk < NF; ++kk)
-                if constexpr (!SPLIT) af[kk] = gq[aoff + kk * kMmaRows];
             if ((q & 3) == 0 || q == q0) philox(c0, sample, (uint32_t)(q >> 2), c3, a.key0, a.key1, w);
             const int wi = q & 3;
             const uint32_t word = wi == 0 ? w[0] : wi == 1 ? w[1] : wi == 2 ? w[2] : w[3];
@@ -438,6 +445,36 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) a
                 y0 = fmaf(J, d0, x0);
                 y1 = fmaf(J, d1, x1);
                 alive = fabsf(y0) < 1.f && fabsf(y1) < 1.f;
+            }
+            if (q != qe) {   // another share's step: the walk alone
+                if (alive) { x0 = y0; x1 = y1; }
+                continue;
+            }
+            qe += shares;
+            // this step's u-table operands, in flight while the factors are written
+            const float *gq = gtab + (int64_t)q * a.slab_stride;   // uniform: lanes add a 32-bit offset
+            u32x4 au[NA];
+            float af[NF];
+#pragma unroll
+            for (int k = 0; k < NA; ++k)
+                if constexpr (SPLIT) au[k] = ((const u32x4 *)gq)[k * 32 + (lane & 31)];
+#pragma unroll
+            for (int kk = 0; kk < NF; ++kk)
+                if constexpr (!SPLIT) af[kk] = gq[aoff + kk * kMmaRows];
+            // ---- outer-product factors of this sample: rows L(X_0), columns L(X_1)
+            {
+                float lp = 0.f, lc = 1.f, mp = 0.f, mc = 1.f;
+#pragma unroll
+                for (int i = 0; i < K2; ++i) {
+                    Am[i * NST + tid] = lc;
+                    Bm[i * NST + tid] = mc;
+                    const float ai = (float)((2.0 * i + 1.0) / (i + 1.0)), bi = (float)(i / (i + 1.0));
+                    const float nx = ai * x0 * lc - bi * lp, ny = ai * x1 * mc - bi * mp;
+                    lp = lc;
+                    lc = nx;
+                    mp = mc;
+                    mc = ny;
+                }
             }
             // ---- weights of this evaluation: lambda Delta/M f'(u*(X_q)) and lambda Delta/M
             float wu = 0.f, wv = 0.f;
@@ -468,23 +505,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) a
                     wu = lam * fprime_of<float>(a.phys, u);
                 }
             }
-            // ---- outer-product factors of this sample: rows L(X_0) weighted, columns L(X_1)
             Wm[tid] = wu;
             Wm[nthr + tid] = wv;
-            {
-                float lp = 0.f, lc = 1.f, mp = 0.f, mc = 1.f;
-#pragma unroll
-                for (int i = 0; i < K2; ++i) {
-                    Am[i * NST + tid] = lc;
-                    Bm[i * NST + tid] = mc;
-                    const float ai = (float)((2.0 * i + 1.0) / (i + 1.0)), bi = (float)(i / (i + 1.0));
-                    const float nx = ai * x0 * lc - bi * lp, ny = ai * x1 * mc - bi * mp;
-                    lp = lc;
-                    lc = nx;
-                    mp = mc;
-                    mc = ny;
-                }
-            }
             if (alive) {
                 x0 = y0;
                 x1 = y1;
@@ -583,7 +605,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) a
             if (any_alive == 0) break;
         }
         // survivors to the next round
-        const bool carry = alive && q1 < nstar;
+        const bool carry = alive && q1 < nstar && share == 0;
         const unsigned long long mask = __ballot(carry);
         if (mask != 0ull) {
             uint32_t base = 0;

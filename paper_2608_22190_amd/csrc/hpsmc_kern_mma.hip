@@ -33,6 +33,7 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
     cptr<GroupDesc> groups = as_const(a.groups);
     cptr<NodeDesc> nodes = as_const(a.nodes);
     const int64_t total = a.batch_prefix[a.n_groups];
+    const int shares = (int)a.batch_prefix[a.n_groups + 2];
     unsigned long long evals = 0, slots = 0;
     using State = PathState<float, 2>;
     const State *sin = (const State *)a.state_in;
@@ -44,13 +45,15 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
         __syncthreads();
         const int64_t item = s_item;
         if (item >= total) break;
-        int lo = 0, hi = a.n_groups - 1;   // last g with batch_prefix[g] <= item
+        const int64_t batch = item / shares;
+        const int share = (int)(item - batch * shares);
+        int lo = 0, hi = a.n_groups - 1;   // last g with batch_prefix[g] <= batch
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (a.batch_prefix[mid] <= item) lo = mid; else hi = mid - 1;
+            if (a.batch_prefix[mid] <= batch) lo = mid; else hi = mid - 1;
         }
         const int g = lo;
-        const int64_t b = item - a.batch_prefix[g];
+        const int64_t b = batch - a.batch_prefix[g];
         cptr<GroupDesc> G = groups + g;
         const int nstar = G->nstar;
         const int q0 = a.round * a.steps;
@@ -68,7 +71,8 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
 
         // ---- this lane's path
         const int64_t p = b * a.batch + tid;
-        bool alive = p < live;
+        const bool began = p < live;
+        bool alive = began;
         uint32_t node = 0, sample = 0, c0 = 0;
         float x0 = 0.f, x1 = 0.f, acc = 0.f, comp = 0.f;
         if (alive) {
@@ -85,6 +89,7 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                 comp = st.comp;
                 node = st.node;
                 sample = st.sample;
+                if (share != 0) { acc = 0.f; comp = 0.f; }
             }
             c0 = nodes[node].c0;
         }
@@ -93,7 +98,8 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
             if (qq < q1) s_tf[tid] = source_time<float>(a.phys, (float)(t_prev + (span - (double)qq * ddelta)));
         };
         fill_time(q0);
-        mma_stage((const u32x4 *)(gtab + (int64_t)q0 * a.slab_stride), lds, svec, tid, nthr);
+        int qe = q0 + share;   // the next step this share evaluates
+        if (qe < q1) mma_stage((const u32x4 *)(gtab + (int64_t)qe * a.slab_stride), lds, svec, tid, nthr);
         float ex0 = x0, ex1 = x1;   // where the current step's integrand is evaluated
         if constexpr (BALL) {
             if (alive) {
@@ -109,7 +115,7 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
         __syncthreads();
 
         uint32_t w[4];
-        int q = q0, tslot = 0;
+        int q = q0, tslot = 0, buf = 0;
         for (; q < q1; ++q, ++tslot) {
             if (tslot == nthr) {   // the previous step's barrier ended every read of the old window
                 tslot = 0;
@@ -119,10 +125,33 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
             if ((q & 3) == 0 || q == q0) philox(c0, sample, (uint32_t)(q >> 2), c3, a.key0, a.key1, w);
             const int wi = q & 3;
             const uint32_t word = wi == 0 ? w[0] : wi == 1 ? w[1] : wi == 2 ? w[2] : w[3];
-            const int buf = (q - q0) & 1;
-            if (q + 1 < q1)
-                mma_stage((const u32x4 *)(gtab + (int64_t)(q + 1) * a.slab_stride), lds + (buf ^ 1) * mvec, svec, tid,
-                          nthr);
+            if (share == 0) ++slots;
+            if (q != qe) {   // another share's step: the walk alone
+                if (alive) {
+                    float d0, d1;
+                    angle_dir(u01(word, 0.f), d0, d1);
+                    const float y0 = fmaf(J, d0, x0), y1 = fmaf(J, d1, x1);
+                    alive = fabsf(y0) < 1.f && fabsf(y1) < 1.f;
+                    if (alive) { x0 = y0; x1 = y1; }
+                }
+                continue;
+            }
+            qe += shares;
+            if (qe < q1)
+                mma_stage((const u32x4 *)(gtab + (int64_t)qe * a.slab_stride), lds + (buf ^ 1) * mvec, svec, tid, nthr);
+            if (shares > 1) {   // the operands of this step's point were not drawn one step ahead
+                ex0 = x0;
+                ex1 = x1;
+                if constexpr (BALL) {
+                    if (alive) {
+                        float off[2];
+                        ball_offset<float, 2>(c0, sample, q, c3, a.key0, a.key1, off);
+                        ex0 = fmaf(J, off[0], x0);
+                        ex1 = fmaf(J, off[1], x1);
+                    }
+                }
+                mma_operands<KH>(ex1, a.P, a.bscale, b0, b1);
+            }
             float u = 0.f, v = 0.f, y0 = x0, y1 = x1, nx0 = x0, nx1 = x1;
             bool inside = false;
             if (__ballot(alive) != 0ull) {
@@ -137,15 +166,15 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                 nx0 = y0;
                 nx1 = y1;
                 if constexpr (BALL) {
-                    if (alive && inside && q + 1 < q1) {
+                    if (alive && inside && qe == q + 1 && qe < q1) {
                         float off[2];
                         ball_offset<float, 2>(c0, sample, q + 1, c3, a.key0, a.key1, off);
                         nx0 = fmaf(J, off[0], y0);
                         nx1 = fmaf(J, off[1], y1);
                     }
                 }
-                MmaB<KH> nb0, nb1;
-                mma_operands<KH>(nx1, a.P, a.bscale, nb0, nb1);
+                MmaB<KH> nb0 = b0, nb1 = b1;
+                if (shares == 1) mma_operands<KH>(nx1, a.P, a.bscale, nb0, nb1);
                 mma_epilogue<KH, PIC>(du0, dv0, du1, dv1, ex0, u, v);
                 if constexpr (MmaB<KH>::SPLIT) {
                     u *= iu;
@@ -154,7 +183,6 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                 b0 = nb0;
                 b1 = nb1;
             }
-            ++slots;
             if (alive) {
                 if (inside) {   // residual at X_q (or its ball point), time tau_q = t_{n,l} - q Delta
                     const float X[2] = {ex0, ex1};
@@ -172,9 +200,9 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                     ++evals;
                 } else {        // path ended: L = q
                     alive = false;
-                    a.result[(int64_t)nodes[node].out * a.mcount + (sample - a.m0)] = (double)acc - (double)comp;
                 }
             }
+            buf ^= 1;
             mma_stage_wait();
             if (__syncthreads_or(alive ? 1 : 0) == 0) { ++q; break; }
         }
@@ -182,7 +210,7 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
         // ---- Picard form (eq. uast): a path still inside after all N* steps adds
         // the interval's initial data u*(X_{N*}, t_{n-1}), the slab of step N*
         if constexpr (PIC) {
-            if (q1 == nstar && q == q1) {
+            if (q1 == nstar && q == q1 && share == 0) {
                 __syncthreads();
                 mma_stage((const u32x4 *)(gtab + (int64_t)nstar * a.slab_stride), lds, svec, tid, nthr);
                 mma_stage_wait();
@@ -205,10 +233,15 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
             }
         }
 
-        // ---- paths alive after the round: finished at N*, or carried to the next round
+        // ---- paths ended in this round or at N*, and those carried to the next round
+        double sum[1] = {(double)acc - (double)comp};
+        if (shares > 1) {
+            if (!share_combine<1>(a, item, batch, shares, a.batch, tid, 0, true, sum, s_item)) continue;
+            acc = (float)sum[0];
+            comp = (float)((double)acc - sum[0]);
+        }
         const bool carry = alive && q1 < nstar;
-        if (alive && !carry)
-            a.result[(int64_t)nodes[node].out * a.mcount + (sample - a.m0)] = (double)acc - (double)comp;
+        if (began && !carry) a.result[(int64_t)nodes[node].out * a.mcount + (sample - a.m0)] = sum[0];
         const unsigned long long mask = __ballot(carry);
         if (mask != 0ull) {
             uint32_t base = 0;

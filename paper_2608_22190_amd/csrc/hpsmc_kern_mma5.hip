@@ -221,6 +221,7 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
     cptr<GroupDesc> groups = as_const(a.groups);
     cptr<NodeDesc> nodes = as_const(a.nodes);
     const int64_t total = a.batch_prefix[a.n_groups];
+    const int shares = (int)a.batch_prefix[a.n_groups + 2];
     // Sparse rounds (few live paths, set by the round's prep kernel): an item is
     // 64 paths that every wave of the block walks alike; wave w runs its share
     // of each tile's k-steps, the shares are summed in wave order, and wave 0
@@ -240,13 +241,15 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
         __syncthreads();
         const int64_t item = s_item;
         if (item >= total) break;
-        int lo = 0, hi = a.n_groups - 1;   // last g with batch_prefix[g] <= item
+        const int64_t batch = item / shares;
+        const int share = (int)(item - batch * shares);
+        int lo = 0, hi = a.n_groups - 1;   // last g with batch_prefix[g] <= batch
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (a.batch_prefix[mid] <= item) lo = mid; else hi = mid - 1;
+            if (a.batch_prefix[mid] <= batch) lo = mid; else hi = mid - 1;
         }
         const int g = lo;
-        const int64_t b = item - a.batch_prefix[g];
+        const int64_t b = batch - a.batch_prefix[g];
         cptr<GroupDesc> G = groups + g;
         const int nstar = G->nstar;
         const int q0 = a.round * a.steps;
@@ -259,7 +262,8 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
 
         // ---- this lane's path
         const int64_t p = b * bsz + (split ? lane : tid);
-        bool alive = p < live;
+        const bool began = p < live;
+        bool alive = began;
         uint32_t node = 0, sample = 0, c0 = 0;
         float X[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, acc = 0.f, comp = 0.f;
         if (alive) {
@@ -276,6 +280,7 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
                 comp = st.comp;
                 node = st.node;
                 sample = st.sample;
+                if (share != 0) { acc = 0.f; comp = 0.f; }
             }
             c0 = nodes[node].c0;
         }
@@ -284,8 +289,9 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
             if (qq < q1) s_tf[tid] = source_time<float>(a.phys, (float)(t_prev + (span - (double)qq * ddelta)));
         };
         fill_time(q0);
-        // chunk 0 of the first step into buffer 0; buf: the buffer of the current chunk
-        mma_stage((const u32x4 *)(gtab + (int64_t)q0 * a.slab_stride), lds, CV, tid, nthr);
+        // chunk 0 of the first evaluated step into buffer 0; buf: the buffer of the current chunk
+        int qe = q0 + share;   // the next step this share evaluates
+        if (qe < q1) mma_stage((const u32x4 *)(gtab + (int64_t)qe * a.slab_stride), lds, CV, tid, nthr);
         mma_stage_wait();
         __syncthreads();
         int buf = 0;
@@ -308,13 +314,17 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
                     Y[i] = m_fma(J, dir[i], X[i]);
                     inside = inside && (fabsf(Y[i]) < 1.f);
                 }
-                if (!inside) {   // path ended: L = q
-                    alive = false;
-                    if (writer)
-                        a.result[(int64_t)nodes[node].out * a.mcount + (sample - a.m0)] = (double)acc - (double)comp;
-                }
+                alive = inside;   // else the path ended: L = q
             }
-            if (writer) ++slots;
+            if (writer && share == 0) ++slots;
+            if (q != qe) {   // another share's step: the walk alone
+                if (alive) {
+#pragma unroll
+                    for (int i = 0; i < 5; ++i) X[i] = Y[i];
+                }
+                continue;
+            }
+            qe += shares;
             // ---- u and v at X_q: the step's chunks, the next one always in flight
             const bool wave_live = __ballot(alive) != 0ull;
             float a3[P], b3[P], a4[HK], b4[HK], L1[P], L2[P];
@@ -322,9 +332,10 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
             legendre_row<P>(X[1], L1);
             legendre_row<P>(X[2], L2);
             const float *step_src = gtab + (int64_t)q * a.slab_stride;
-            const bool more = q + 1 < q1;
-            auto stage_next = [&](int c) {   // chunk c + 1 of this step, or chunk 0 of the next
-                const float *src = c + 1 < NCH ? step_src + (int64_t)(c + 1) * CF : (more ? step_src + a.slab_stride : nullptr);
+            const bool more = qe < q1;
+            auto stage_next = [&](int c) {   // chunk c + 1 of this step, or chunk 0 of the next evaluated one
+                const float *src = c + 1 < NCH ? step_src + (int64_t)(c + 1) * CF
+                                               : (more ? gtab + (int64_t)qe * a.slab_stride : nullptr);
                 if (src) mma_stage((const u32x4 *)src, lds + (buf ^ 1) * CV, CV, tid, nthr);
             };
             float u = 0.f, v = 0.f;
@@ -402,10 +413,15 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
             if (__syncthreads_or(alive ? 1 : 0) == 0) { ++q; break; }
         }
 
-        // ---- paths alive after the round: finished at N*, or carried to the next round
+        // ---- paths ended in this round or at N*, and those carried to the next round
+        double sum[1] = {(double)acc - (double)comp};
+        if (shares > 1) {
+            if (!share_combine<1>(a, item, batch, shares, bsz, split ? lane : tid, 0, writer, sum, s_item)) continue;
+            acc = (float)sum[0];
+            comp = (float)((double)acc - sum[0]);
+        }
         const bool carry = writer && alive && q1 < nstar;
-        if (writer && alive && !carry)
-            a.result[(int64_t)nodes[node].out * a.mcount + (sample - a.m0)] = (double)acc - (double)comp;
+        if (writer && began && !carry) a.result[(int64_t)nodes[node].out * a.mcount + (sample - a.m0)] = sum[0];
         const unsigned long long mask = __ballot(carry);
         if (mask != 0ull) {
             uint32_t base = 0;

@@ -713,9 +713,9 @@ size_t path_state_bytes(int fp32, int dim)
 
 __global__ void round_prep_kernel(const GroupDesc *__restrict__ groups, int32_t n_groups, int32_t round,
                                   int32_t steps, int64_t mcount, int32_t batch, int32_t batch_split,
-                                  int64_t split_max, const uint32_t *__restrict__ live_in,
+                                  int64_t split_max, int64_t share_max, const uint32_t *__restrict__ live_in,
                                   uint32_t *__restrict__ live_out, int64_t *__restrict__ batch_prefix,
-                                  unsigned long long *work)
+                                  uint32_t *__restrict__ share_done, unsigned long long *work)
 {
     // one block of 256 threads: clear the output counters, then an exclusive
     // prefix over groups of their work items (each thread a contiguous chunk,
@@ -723,11 +723,16 @@ __global__ void round_prep_kernel(const GroupDesc *__restrict__ groups, int32_t 
     // then the chunks again).  With batch_split > 0 a round whose paths fit in
     // at most split_max items of batch_split paths takes that batch instead;
     // batch_prefix[n_groups + 1] holds the paths per item the round kernel is
-    // to use.
+    // to use, batch_prefix[n_groups + 2] the shares each batch is split into:
+    // the largest power of two (at most kMaxShares) that keeps batches times
+    // shares within share_max, so that a round of few batches still fills the
+    // grid (each share's block walks the whole round and evaluates every
+    // shares-th step).
     __shared__ int64_t part[256], part_s[256];
     __shared__ int32_t s_split;
     const int t = threadIdx.x, nt = blockDim.x;
     for (int g = t; g < n_groups; g += nt) live_out[g] = 0u;
+    for (int64_t i = t; i < share_max; i += nt) share_done[i] = 0u;
     const int64_t q0 = (int64_t)round * steps;
     auto items = [&](int g, int32_t bsz) -> int64_t {
         int64_t live = round == 0 ? (int64_t)groups[g].node_count * mcount : (int64_t)live_in[g];
@@ -753,8 +758,12 @@ __global__ void round_prep_kernel(const GroupDesc *__restrict__ groups, int32_t 
     }
     if (t == 0) {
         const bool split = batch_split > 0 && part_s[nt - 1] <= split_max;
-        batch_prefix[n_groups] = split ? part_s[nt - 1] : part[nt - 1];
+        const int64_t n = split ? part_s[nt - 1] : part[nt - 1];
+        int64_t shares = 1;
+        while (n > 0 && 2 * shares * n <= share_max && 2 * shares <= kMaxShares && 2 * shares <= steps) shares *= 2;
+        batch_prefix[n_groups] = n * shares;
         batch_prefix[n_groups + 1] = split ? batch_split : batch;
+        batch_prefix[n_groups + 2] = shares;
         s_split = split ? 1 : 0;
         *work = 0ull;
     }
@@ -769,11 +778,12 @@ __global__ void round_prep_kernel(const GroupDesc *__restrict__ groups, int32_t 
 }
 
 hipError_t launch_round_prep(const GroupDesc *groups, int32_t n_groups, int32_t round, int32_t steps, int64_t mcount,
-                             int32_t batch, int32_t batch_split, int64_t split_max, const uint32_t *live_in,
-                             uint32_t *live_out, int64_t *batch_prefix, unsigned long long *work, hipStream_t s)
+                             int32_t batch, int32_t batch_split, int64_t split_max, int64_t share_max,
+                             const uint32_t *live_in, uint32_t *live_out, int64_t *batch_prefix, uint32_t *share_done,
+                             unsigned long long *work, hipStream_t s)
 {
     hipLaunchKernelGGL(round_prep_kernel, dim3(1), dim3(256), 0, s, groups, n_groups, round, steps, mcount, batch,
-                       batch_split, split_max, live_in, live_out, batch_prefix, work);
+                       batch_split, split_max, share_max, live_in, live_out, batch_prefix, share_done, work);
     return hipGetLastError();
 }
 

@@ -25,6 +25,7 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
     cptr<GroupDesc> groups = as_const(a.groups);
     cptr<NodeDesc> nodes = as_const(a.nodes);
     const int64_t total = a.batch_prefix[a.n_groups];
+    const int shares = (int)a.batch_prefix[a.n_groups + 2];
     unsigned long long evals = 0, slots = 0;
     using State = PathState<T, D>;
     const State *sin = (const State *)a.state_in;
@@ -36,14 +37,16 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
         __syncthreads();
         const int64_t item = s_item;
         if (item >= total) break;
-        // group of this work item: last g with batch_prefix[g] <= item
+        const int64_t batch = item / shares;
+        const int share = (int)(item - batch * shares);
+        // group of this batch: last g with batch_prefix[g] <= batch
         int lo = 0, hi = a.n_groups - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (a.batch_prefix[mid] <= item) lo = mid; else hi = mid - 1;
+            if (a.batch_prefix[mid] <= batch) lo = mid; else hi = mid - 1;
         }
         const int g = lo;
-        const int64_t b = item - a.batch_prefix[g];
+        const int64_t b = batch - a.batch_prefix[g];
         cptr<GroupDesc> G = groups + g;
         const int nstar = G->nstar;
         const int q0 = a.round * a.steps;
@@ -56,12 +59,12 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
 
         // ---- the batch's paths
         T X[NS][D], Y[NS][D], acc[NS], comp[NS];
-        bool alive[NS];
+        bool alive[NS], began[NS];
         uint32_t node[NS], sample[NS], c0[NS];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const int64_t p = b * a.batch + (int64_t)s * nthr + tid;
-            alive[s] = p < live;
+            began[s] = alive[s] = p < live;
             node[s] = 0; sample[s] = 0; c0[s] = 0;
             acc[s] = (T)0; comp[s] = (T)0;
 #pragma unroll
@@ -80,6 +83,7 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
                     comp[s] = st.comp;
                     node[s] = st.node;
                     sample[s] = st.sample;
+                    if (share != 0) { acc[s] = (T)0; comp[s] = (T)0; }
                 }
                 c0[s] = nodes[node[s]].c0;
             }
@@ -92,10 +96,11 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
         };
         fill_time(q0);
 
-        // ---- first chunk of the first step's slab into LDS buffer 0
+        // ---- first chunk of the first evaluated step's slab into LDS buffer 0
         u32x4 stage[NSTG];
-        {
-            const u32x4 *src = (const u32x4 *)(gtab + (int64_t)q0 * a.slab_stride);
+        int qe = q0 + share, buf = 0;   // the next step this share evaluates, its buffer
+        if (qe < q1) {
+            const u32x4 *src = (const u32x4 *)(gtab + (int64_t)qe * a.slab_stride);
 #pragma unroll
             for (int k = 0; k < NSTG; ++k) {
                 const int64_t v = tid + (int64_t)k * nthr;
@@ -151,15 +156,22 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
                         Y[s][i] = m_fma(J, dir[s][i], X[s][i]);
                         inside = inside && (fabs(Y[s][i]) < (T)1);
                     }
-                    if (!inside) {   // path ended: L = q
-                        alive[s] = false;
-                        a.result[(int64_t)nodes[node[s]].out * a.mcount + (sample[s] - a.m0)] =
-                            (double)acc[s] - (double)comp[s];
-                    }
+                    alive[s] = inside;   // else the path ended: L = q
                 }
                 any_live = any_live || alive[s];
             }
-            slots += NS;
+            if (share == 0) slots += NS;
+            if (q != qe) {   // another share's step: the walk alone
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    if (alive[s]) {
+#pragma unroll
+                        for (int i = 0; i < D; ++i) X[s][i] = Y[s][i];
+                    }
+                }
+                continue;
+            }
+            qe += shares;
             // ---- the point where step q's integrand is evaluated: the ball centre
             // X_q (eq. interIQ) or the step's Green's-function ball point, written
             // over X (a live path moves to Y after the evaluation)
@@ -191,10 +203,8 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
                     Ll[s][k + 1] = (T)((2.0 * k + 1.0) / (k + 1.0)) * x * Ll[s][k] - (T)(k / (k + 1.0)) * Ll[s][k - 1];
             }
             for (int c = 0; c < NC; ++c) {
-                const int64_t tseq = (int64_t)(q - q0) * NC + c;
-                const int buf = (int)(tseq & 1);
                 int qn = q, cn = c + 1;
-                if (cn == NC) { cn = 0; qn = q + 1; }
+                if (cn == NC) { cn = 0; qn = qe; }
                 const bool has_next = qn < q1;
                 if (has_next) {
                     const u32x4 *src = (const u32x4 *)(gtab + (int64_t)qn * a.slab_stride + (int64_t)cn * a.chunk_elems);
@@ -241,6 +251,7 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
                         if (vv < nvec) dst[vv] = stage[k];
                     }
                 }
+                buf ^= 1;
                 if (c + 1 < NC) __syncthreads();
             }
             if (wave_live) {
@@ -271,7 +282,7 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
         // ---- Picard form (eq. uast): a path still inside after all N* steps has
         // reached t_{n-1} and adds the interval's initial data u*(X_{N*}, t_{n-1}),
         // the slab of step N* (xi = -1), streamed through LDS like any step
-        if (picard && q1 == nstar && q == q1) {
+        if (picard && q1 == nstar && q == q1 && share == 0) {
             bool any_live = false;
 #pragma unroll
             for (int s = 0; s < NS; ++s) any_live = any_live || alive[s];
@@ -337,12 +348,22 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
             }
         }
 
-        // ---- paths alive after the round: finished at N*, or carried to the next round
+        // ---- paths ended in this round or at N*, and those carried to the next round
+        double sum[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) sum[s] = (double)acc[s] - (double)comp[s];
+        if (shares > 1) {
+            if (!share_combine<NS>(a, item, batch, shares, a.batch, tid, nthr, true, sum, s_item)) continue;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                acc[s] = (T)sum[s];
+                comp[s] = (T)((double)acc[s] - sum[s]);
+            }
+        }
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const bool carry = alive[s] && q1 < nstar;
-            if (alive[s] && !carry)
-                a.result[(int64_t)nodes[node[s]].out * a.mcount + (sample[s] - a.m0)] = (double)acc[s] - (double)comp[s];
+            if (began[s] && !carry) a.result[(int64_t)nodes[node[s]].out * a.mcount + (sample[s] - a.m0)] = sum[s];
             const unsigned long long mask = __ballot(carry);
             if (mask != 0ull) {
                 uint32_t base = 0;
