@@ -41,11 +41,8 @@ __device__ __forceinline__ void advance_1d_body(const RoundArgs &a)
     const State *sin = (const State *)a.state_in;
     State *sout = (State *)a.state_out;
 
-    for (;;) {
-        __syncthreads();
-        if (tid == 0) s_item = (long long)atomicAdd(a.work, 1ull);
-        __syncthreads();
-        const int64_t item = s_item;
+    for (bool first = true;; first = false) {
+        const int64_t item = take_item(a, total, first, s_item);
         if (item >= total) break;
         int lo = 0, hi = a.n_groups - 1;   // last g with batch_prefix[g] <= item
         while (lo < hi) {
@@ -225,12 +222,7 @@ __device__ __forceinline__ void advance_1d_body(const RoundArgs &a)
             }
         }
     }
-    evals = wave_sum_u64(evals);
-    slots = wave_sum_u64(slots);
-    if (lane == 0) {
-        atomicAdd(a.stats + 0, evals);
-        atomicAdd(a.stats + 1, slots);
-    }
+    add_stats(a, evals, slots);
 }
 
 template <typename T, int NS, int PM>

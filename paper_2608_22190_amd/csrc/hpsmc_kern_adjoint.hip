@@ -67,11 +67,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MFMA ?
     T *sbar = (T *)aa.slab_bar;
     const int E = 2 * R * P;
 
-    for (;;) {
-        __syncthreads();
-        if (tid == 0) s_item = (long long)atomicAdd(a.work, 1ull);
-        __syncthreads();
-        const int64_t item = s_item;
+    for (bool first = true;; first = false) {
+        const int64_t item = take_item(a, total, first, s_item);
         if (item >= total) break;
         const int64_t batch = item / shares;
         const int share = (int)(item - batch * shares);
@@ -385,11 +382,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) a
     constexpr int NB = MmaB<KH>::NB, NA = SPLIT ? 2 * NB : 1, NF = SPLIT ? 1 : KH;
     const int aoff = (lane >> 5) * KH * kMmaRows + (lane & 31);
 
-    for (;;) {
-        __syncthreads();
-        if (tid == 0) s_item = (long long)atomicAdd(a.work, 1ull);
-        __syncthreads();
-        const int64_t item = s_item;
+    for (bool first = true;; first = false) {
+        const int64_t item = take_item(a, total, first, s_item);
         if (item >= total) break;
         const int64_t batch = item / shares;
         const int share = (int)(item - batch * shares);

@@ -102,11 +102,8 @@ __global__ void __launch_bounds__(256) frac_advance_kernel(RoundArgs a)
     State *sout = (State *)a.state_out;
     const T fa = (T)ph.frac_a;
 
-    for (;;) {
-        __syncthreads();
-        if (tid == 0) s_item = (long long)atomicAdd(a.work, 1ull);
-        __syncthreads();
-        const int64_t item = s_item;
+    for (bool first = true;; first = false) {
+        const int64_t item = take_item(a, total, first, s_item);
         if (item >= total) break;
         int lo = 0, hi = a.n_groups - 1;   // last g with batch_prefix[g] <= item
         while (lo < hi) {
@@ -293,12 +290,7 @@ __global__ void __launch_bounds__(256) frac_advance_kernel(RoundArgs a)
             }
         }
     }
-    evals = wave_sum_u64(evals);
-    slots = wave_sum_u64(slots);
-    if (lane == 0) {
-        atomicAdd(a.stats + 0, evals);
-        atomicAdd(a.stats + 1, slots);
-    }
+    add_stats(a, evals, slots);
 }
 
 // dynamic LDS of the fractional round kernel: two slab buffers and the tables

@@ -31,11 +31,8 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
     const State *sin = (const State *)a.state_in;
     State *sout = (State *)a.state_out;
 
-    for (;;) {
-        __syncthreads();
-        if (tid == 0) s_item = (long long)atomicAdd(a.work, 1ull);
-        __syncthreads();
-        const int64_t item = s_item;
+    for (bool first = true;; first = false) {
+        const int64_t item = take_item(a, total, first, s_item);
         if (item >= total) break;
         const int64_t batch = item / shares;
         const int share = (int)(item - batch * shares);
@@ -383,12 +380,7 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
             }
         }
     }
-    evals = wave_sum_u64(evals);
-    slots = wave_sum_u64(slots);
-    if (lane == 0) {
-        atomicAdd(a.stats + 0, evals);
-        atomicAdd(a.stats + 1, slots);
-    }
+    add_stats(a, evals, slots);
 }
 
 // One-dimensional FP64 kernels with two paths per lane and up to 20 Legendre
