@@ -18,7 +18,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhpsmc.so")
 SOURCES = ["hpsmc_kern_valu_f32.hip", "hpsmc_kern_valu_f64.hip", "hpsmc_kern_mma.hip", "hpsmc_kern_mma5.hip",
-           "hpsmc_kern_adjoint.hip", "hpsmc_kern_frac.hip", "hpsmc_kern_1d.hip", "hpsmc_kernels.hip",
+           "hpsmc_kern_adjoint.hip", "hpsmc_kern_frac.hip", "hpsmc_kern_1d.hip", "hpsmc_kern_lattice.hip", "hpsmc_kernels.hip",
            "hpsmc_host.cpp"]
 HEADERS = ["hpsmc_internal.h", "hpsmc_device.h", "hpsmc_round.h", "hpsmc_lobatto_eigs.h"]
 # per-unit extra flags: in the vector-unit round kernels machine LICM hoists
@@ -27,7 +27,7 @@ HEADERS = ["hpsmc_internal.h", "hpsmc_device.h", "hpsmc_round.h", "hpsmc_lobatto
 # costs occupancy (FP64, one path per lane: the windowed 1-D kernel 150 -> 77
 # VGPRs without it, the general 2-D kernel 225 -> 153)
 _NO_MLICM = ["-mllvm", "-disable-machine-licm"]
-UNIT_FLAGS = {"hpsmc_kern_1d.hip": _NO_MLICM, "hpsmc_kern_valu_f64.hip": _NO_MLICM,
+UNIT_FLAGS = {"hpsmc_kern_1d.hip": _NO_MLICM, "hpsmc_kern_lattice.hip": _NO_MLICM, "hpsmc_kern_valu_f64.hip": _NO_MLICM,
               "hpsmc_kern_valu_f32.hip": _NO_MLICM}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",

@@ -20,20 +20,18 @@ struct RecTable {
     double ad[kMaxP + 2], bd[kMaxP + 2];
     float af[kMaxP + 2], bf[kMaxP + 2];
 };
-// every translation unit holds its own copy, uploaded by its own setter
-static __constant__ RecTable c_rec;
-
-static hipError_t upload_recurrence_tables()
+constexpr RecTable recurrence_table()
 {
-    RecTable t;
+    RecTable t{};
     for (int k = 0; k < kMaxP + 2; ++k) {
         t.ad[k] = (2.0 * k + 1.0) / (k + 1.0);
         t.bd[k] = double(k) / (k + 1.0);
         t.af[k] = float(t.ad[k]);
         t.bf[k] = float(t.bd[k]);
     }
-    return hipMemcpyToSymbol(HIP_SYMBOL(c_rec), &t, sizeof(t));
+    return t;
 }
+static __constant__ RecTable c_rec = recurrence_table();   // part of the code object: nothing to upload
 
 template <typename T> __device__ __forceinline__ T rec_a(int k);
 template <typename T> __device__ __forceinline__ T rec_b(int k);
@@ -878,13 +876,4 @@ hipError_t launch_adv_mma(const RoundArgs &a, dim3 grid, dim3 block, size_t lds,
 hipError_t launch_adv_mma5(const RoundArgs &a, dim3 grid, dim3 block, size_t lds, hipStream_t s);
 hipError_t launch_adv_frac(const RoundArgs &a, int fp32, dim3 grid, dim3 block, size_t lds, hipStream_t s);
 hipError_t launch_adv_1d(const RoundArgs &a, int fp32, int ns, dim3 grid, dim3 block, size_t lds, hipStream_t s);
-// each unit's copy of the recurrence tables
-hipError_t set_rec_tables_main();
-hipError_t set_rec_tables_valu_f32();
-hipError_t set_rec_tables_valu_f64();
-hipError_t set_rec_tables_mma();
-hipError_t set_rec_tables_mma5();
-hipError_t set_rec_tables_frac();
-hipError_t set_rec_tables_adjoint();
-
 }  // namespace hpsmc

@@ -344,6 +344,15 @@ struct NodeSet {               // the nodes one sampling launch covers
     uint32_t *live = nullptr;  // [2][n_groups]
     int64_t *prefix = nullptr; // [n_groups + 3]
     double *result = nullptr;  // [n][ms]
+    // lattice form of 1-D FP64 rounds: one descriptor, live counter and prefix per node
+    bool lat = false;
+    int32_t lat_steps = 0;     // walk steps per round
+    LatArgs lat_args{};
+    void *lat_mem = nullptr;   // descriptors, counters and prefix in one piece
+    GroupDesc *lat_nodes = nullptr;
+    uint32_t *lat_live = nullptr;
+    int64_t *lat_prefix = nullptr;
+    int64_t lat_elems = 0;     // table elements of a round
     // Aitken-relaxed update: one vector per (interval of the set, instance)
     int32_t n_vec = 0;
     int64_t *vbeg = nullptr;   // [n_vec + 1] node ranges
@@ -417,6 +426,7 @@ struct hpsmc_plan {
     size_t slab_bytes = 0;
     double *part = nullptr;
     int64_t part_elems = 0;
+    double *lat_table = nullptr;             // lattice form: residuals of one round
     // rounds of few batches, split into shares of steps: [share_max][kShareBatch] part sums, [share_max] counters
     double *share_sum = nullptr;
     uint32_t *share_done = nullptr;
@@ -847,11 +857,86 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     return HPSMC_OK;
 }
 
+// Lattice form of a 1-D FP64 set: descriptors of every node, if tabulating the
+// residual at the lattice points is the cheaper way.
+static hpsmc_status build_lattice(hpsmc_plan *plan, NodeSet &set)
+{
+    // (past 20 modes the rounding of a position's accumulated sum, 1e-15, times the
+    // polynomials' slope shows above 1e-13 of a path's value: there the residual
+    // stays with the position)
+    if (plan->fp32 || !set.rounds || plan->P > 20 || set.n > 65535 || set.ghost.size() > 65535 ||
+        !advance_1d_eligible(plan->d, plan->P, plan->pb.estimator == HPSMC_EST_PICARD,
+                             plan->pb.quad == HPSMC_QUAD_BALL, plan->frac ? 1 : 0, 1))
+        return HPSMC_OK;
+    std::vector<LatDesc> desc;
+    std::vector<GroupDesc> nodes;
+    int64_t sum_w = 0;
+    int32_t wmax = 0;
+    int64_t emax = 0;
+    double entries = 0.0, visits = 0.0;
+    for (const GroupDesc &G : set.ghost) {
+        const int64_t before = sum_w;
+        for (int k = 0; k < G.node_count; ++k) {
+            const double x0 = set.host[G.node_begin + k].x0[0];
+            if ((1.0 + std::fabs(x0)) / G.jump > 4096.0) return HPSMC_OK;
+            LatDesc d{};
+            d.toff = sum_w;
+            d.mlo = (int32_t)std::floor((-1.0 - x0) / G.jump);
+            const int32_t mhi = (int32_t)std::ceil((1.0 - x0) / G.jump);
+            d.W = ((mhi - d.mlo) / 2 + 2) & ~1;
+            sum_w += d.W;
+            wmax = std::max(wmax, d.W);
+            desc.push_back(d);
+            GroupDesc n = G;
+            n.node_begin = G.node_begin + k;
+            n.node_count = 1;
+            n.path_off = (int64_t)n.node_begin * set.ms;
+            nodes.push_back(n);
+            // share of the steps a path takes before it leaves: the slowest mode of the interval
+            const double z = 2.467 * G.span;
+            entries += (double)d.W * G.nstar;
+            visits += (double)plan->pb.M * G.nstar * 0.9 * (1.0 - std::exp(-z)) / z;
+        }
+        emax = std::max(emax, sum_w - before);
+    }
+    // Evaluated path by path, a set takes the longer of visits / kVisitRate and the
+    // latency of its longest path; tabulated, entries / kEntryRate, visits / kWalkRate
+    // and a shorter latency (measured, in operations and seconds a step).
+    const double t_direct = std::max(visits / 1.0e11, set.max_nstar * 2.8e-6);
+    const double t_lattice = entries / 4.0e11 + std::max(visits / 1.0e12, set.max_nstar * 2.0e-7);
+    const int64_t budget = (int64_t)1 << 29;   // bytes of a round's table
+    int64_t steps = std::min<int64_t>(1024, budget / (8 * sum_w)) / 32 * 32;
+    steps = std::min<int64_t>(steps, (set.max_nstar + 31) / 32 * 32);
+    if (t_lattice >= t_direct || steps < 32 || 2 * lat_window(wmax) * (int64_t)wmax * 8 + 16 > 65536) return HPSMC_OK;
+    hpsmc_status st;
+    const size_t n = nodes.size(), nb = sizeof(GroupDesc) * n, db = sizeof(LatDesc) * n, pb = sizeof(int64_t) * (n + 3);
+    if ((st = dalloc(plan, &set.lat_mem, nb + db + pb + sizeof(uint32_t) * 2 * n))) return st;
+    std::vector<char> img(nb + db);
+    memcpy(img.data(), nodes.data(), nb);
+    memcpy(img.data() + nb, desc.data(), db);
+    if (hipMemcpy(set.lat_mem, img.data(), nb + db, hipMemcpyHostToDevice) != hipSuccess)
+        return fail(HPSMC_EDEVICE, "upload of lattice descriptors failed");
+    char *m = (char *)set.lat_mem;
+    set.lat_nodes = (GroupDesc *)m;
+    set.lat_args.desc = (const LatDesc *)(m + nb);
+    set.lat_prefix = (int64_t *)(m + nb + db);
+    set.lat_live = (uint32_t *)(m + nb + db + pb);
+    set.lat_args.groups = set.gdev;
+    set.lat_args.n_groups = (int32_t)set.ghost.size();
+    set.lat_args.emax = (int32_t)emax;
+    set.lat_args.wmax = wmax;
+    set.lat_args.win = lat_window(wmax);
+    set.lat_steps = (int32_t)steps;
+    set.lat_elems = sum_w * steps;
+    set.lat = true;
+    return HPSMC_OK;
+}
+
 static void free_set(const hpsmc_plan *plan, NodeSet &s)
 {
     for (void *p : {(void *)s.dev, s.group_mem, (void *)s.eps, (void *)s.sumsq, (void *)s.probe, (void *)s.gdev,
                     s.state[0], s.state[1], (void *)s.live, (void *)s.prefix, (void *)s.result, (void *)s.vbeg,
-                    (void *)s.ait})
+                    (void *)s.ait, s.lat_mem})
         dfree(plan, p);
     s = NodeSet{};
 }
@@ -1261,16 +1346,20 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
                      : plan->frac ? frac_lds_bytes(plan->fp32, plan->PP, plan->frac_kmax, plan->P, plan->frac_K,
                                                    plan->frac_nt)
                                   : (size_t)2 * ((nvec + 1) & ~1LL) * 16;
-    const int C = plan->round_steps;
+    const bool lat = k1d && set.lat;   // over nodes instead of groups
+    const int C = lat ? set.lat_steps : plan->round_steps;
     const int R = (set.max_nstar + C - 1) / C;
-    const int G = (int)set.ghost.size();
+    const int G = lat ? (int)set.n : (int)set.ghost.size();
     RoundArgs a{};
-    a.groups = set.gdev;
+    a.groups = lat ? set.lat_nodes : set.gdev;
     a.nodes = set.dev;
     a.n_groups = G;
     a.steps = C;
     a.batch = nthr * ns;
-    a.batch_prefix = set.prefix;
+    a.batch_prefix = lat ? set.lat_prefix : set.prefix;
+    uint32_t *live = lat ? set.lat_live : set.live;
+    LatArgs la = set.lat_args;
+    la.table = plan->lat_table;
     a.result = set.result;
     a.cf = cf;
     a.n_chunks = n_chunks;
@@ -1310,13 +1399,19 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
             a.round = r;
             a.state_in = set.state[r & 1];
             a.state_out = set.state[(r + 1) & 1];
-            a.live_in = set.live + (r & 1) * G;
-            a.live_out = set.live + ((r + 1) & 1) * G;
-            HIP_TRY(launch_round_prep(set.gdev, G, r, C, mc, a.batch, split_batch, split_max, share_max, a.live_in,
-                                      a.live_out, set.prefix, plan->share_done, plan->counters, s));
+            a.live_in = live + (r & 1) * G;
+            a.live_out = live + ((r + 1) & 1) * G;
+            HIP_TRY(launch_round_prep(a.groups, G, r, C, mc, a.batch, split_batch, split_max, share_max, a.live_in,
+                                      a.live_out, const_cast<int64_t *>(a.batch_prefix), plan->share_done,
+                                      plan->counters, s));
             hpsmc_plan::EvPair *ea = next_pair(plan->ev_sample, plan->n_sample);
             if (ea) HIP_TRY(hipEventRecord(ea->a, s));
-            HIP_TRY(launch_advance(a, plan->fp32, ns, waves, blocks, lds, k1d ? 3 : mma, s));
+            if (lat) {
+                HIP_TRY(launch_lat_table(a, la, s));
+                HIP_TRY(launch_lat_advance(a, la, ns, waves, blocks, s));
+            } else {
+                HIP_TRY(launch_advance(a, plan->fp32, ns, waves, blocks, lds, k1d ? 3 : mma, s));
+            }
             if (ea) HIP_TRY(hipEventRecord(ea->b, s));
         }
         HIP_TRY(launch_slice_reduce(set.result, set.n, mc, plan->part, first, s));
@@ -1464,7 +1559,7 @@ void hpsmc_destroy(hpsmc_plan *plan)
     void *ptrs[] = {plan->U, plan->cu, plan->cv, plan->tmp0, plan->tmp1, plan->ic, plan->mats,
                     plan->slab_table, plan->part, plan->counters, plan->maxbits, plan->hist_u, plan->hist_v,
                     plan->lam, plan->cbar_u, plan->cbar_v, plan->dtarget, plan->dloss, plan->dgrad, plan->slab_bar,
-                    plan->frac_tab, plan->src_poly, plan->cu_ch, plan->cv_ch, plan->cs_ch, plan->share_sum, plan->share_done};
+                    plan->frac_tab, plan->src_poly, plan->cu_ch, plan->cv_ch, plan->cs_ch, plan->share_sum, plan->lat_table};
     for (void *p : ptrs) dfree(plan, p);
     delete plan;
 }
@@ -1539,7 +1634,6 @@ hpsmc_status hpsmc_create(const hpsmc_problem *pb, hpsmc_plan **out)
         return fail(HPSMC_EDEVICE, "no HIP device");
     }
     plan->cus = prop.multiProcessorCount;
-    if (set_recurrence_tables() != hipSuccess) return fail(HPSMC_EDEVICE, "constant table upload failed");
 
     // device buffers
     const int64_t I = plan->n_inst;
@@ -1559,11 +1653,15 @@ hpsmc_status hpsmc_create(const hpsmc_problem *pb, hpsmc_plan **out)
     if ((st = dalloc(pl, (void **)&pl->tmp0, tmax * 8))) return st;
     if ((st = dalloc(pl, (void **)&pl->tmp1, tmax * 8))) return st;
     if ((st = dalloc(pl, (void **)&pl->ic, I * plan->nsp * 8))) return st;
-    // the general kernel's blocks are at most four to a CU (a wave takes 100 registers or
-    // more): a grid of more blocks than that is not worth filling with shares
-    plan->share_max = 4 * (int64_t)plan->cus;
-    if ((st = dalloc(pl, (void **)&pl->share_sum, (size_t)plan->share_max * kShareBatch * 8))) return st;
-    if ((st = dalloc(pl, (void **)&pl->share_done, (size_t)plan->share_max * 4))) return st;
+    // shares of steps, in every round kernel but the 1-D and the fractional ones; the general
+    // kernel's blocks are at most four to a CU (a wave takes 100 registers or more): a grid of
+    // more blocks than that is not worth filling
+    if (!plan->frac && !advance_1d_eligible(plan->d, plan->P, pb->estimator == HPSMC_EST_PICARD,
+                                            pb->quad == HPSMC_QUAD_BALL, 0, 1)) {
+        plan->share_max = 4 * (int64_t)plan->cus;
+        if ((st = dalloc(pl, (void **)&pl->share_sum, (size_t)plan->share_max * (kShareBatch * 8 + 4)))) return st;
+        plan->share_done = (uint32_t *)(plan->share_sum + plan->share_max * kShareBatch);
+    }
     if ((st = dalloc(pl, (void **)&pl->counters, 4 * 8))) return st;
     if ((st = dalloc(pl, (void **)&pl->maxbits, 4096 * 8))) return st;
     if (pl->frac && (st = frac_tables(pl))) return st;
@@ -1700,7 +1798,12 @@ hpsmc_status hpsmc_create(const hpsmc_problem *pb, hpsmc_plan **out)
         for (int iv = 0; iv < plan->n_iv; ++iv) all.push_back(iv);
         if ((st = build_set(pl, plan->sets[0], all))) return st;
     }
-    int64_t slab_max = 0, nmax = 0;
+    int64_t slab_max = 0, nmax = 0, lat_max = 0;
+    for (auto &s : plan->sets) {
+        if ((st = build_lattice(pl, s))) return st;
+        lat_max = std::max(lat_max, s.lat_elems);
+    }
+    if (lat_max > 0 && (st = dalloc(pl, (void **)&pl->lat_table, (size_t)lat_max * 8))) return st;
     for (auto &s : plan->sets) { slab_max = std::max(slab_max, s.slab_elems); nmax = std::max(nmax, s.n); }
     plan->slab_bytes = (size_t)slab_max * (plan->fp32 ? 4 : 8);
     if ((st = dalloc(pl, &pl->slab_table, plan->slab_bytes))) return st;

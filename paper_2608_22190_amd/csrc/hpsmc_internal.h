@@ -114,6 +114,21 @@ struct RoundArgs {
     Physics phys;
 };
 
+// One-dimensional lattice form: the points x_j + (mlo + i) J, i < 2 W, cover
+// (-1, 1); the table of a round holds W entries (those of the step's parity) per
+// node and step, [node][step][W].
+struct LatDesc {
+    int64_t toff;          // sum of W over the nodes before
+    int32_t mlo, W;        // W even
+};
+struct LatArgs {
+    const LatDesc *desc;   // per node
+    double *table;
+    const GroupDesc *groups;   // whose nodes they are
+    int32_t n_groups, emax;    // most entries of a group's step
+    int32_t win, wmax;         // steps per LDS window, widest W
+};
+
 // Arguments of one round of the adjoint kernel: the forward paths of one
 // iteration are regenerated and every residual evaluation scatters its
 // weighted basis values into the slab-adjoint table.
@@ -195,6 +210,10 @@ hipError_t launch_advance(const RoundArgs &a, int fp32, int samples_per_lane, in
 // 4 paths per lane; LDS: two windows of slabs
 bool advance_1d_eligible(int dim, int P, int picard, int ball, int frac, int samples_per_lane);
 size_t advance_1d_lds_bytes(int fp32, int64_t slab_stride);
+// lattice form of the 1-D rounds (RoundArgs over nodes instead of groups)
+int lat_window(int W);
+hipError_t launch_lat_table(const RoundArgs &a, const LatArgs &la, hipStream_t s);
+hipError_t launch_lat_advance(const RoundArgs &a, const LatArgs &la, int ns, int waves, int blocks, hipStream_t s);
 // matrix-core form of the round kernel: FP32, d = 2, P <= 32, whole slab per
 // LDS buffer, one path per lane
 bool advance_mma_eligible(int fp32, int dim, int P, int cf, int samples_per_lane, int waves_per_block);
@@ -286,6 +305,5 @@ hipError_t launch_loss_lambda(const double *U, const double *target, int n_inst,
                               double *loss, hipStream_t s);
 hipError_t launch_column_sum(const double *lambda, int64_t rows, int T1, double *out, hipStream_t s);
 hipError_t launch_axpy(double *y, const double *x, int64_t n, hipStream_t s);
-hipError_t set_recurrence_tables();
 
 }  // namespace hpsmc

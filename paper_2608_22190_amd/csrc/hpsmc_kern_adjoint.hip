@@ -3,8 +3,6 @@
 
 namespace hpsmc {
 
-hipError_t set_rec_tables_adjoint() { return upload_recurrence_tables(); }
-
 // ===========================================================================
 // Adjoint of the residual estimator under common random numbers.
 //

@@ -3,8 +3,6 @@
 
 namespace hpsmc {
 
-hipError_t set_rec_tables_frac() { return upload_recurrence_tables(); }
-
 // ===========================================================================
 // Round kernel, fractional form (Ex. 2-3): d = 1, u_t = -(-Delta)^{alpha/2} u
 // + f(u) + s, one path per lane.  The walk jumps by J = R / sqrt(x) with

@@ -3,8 +3,6 @@
 
 namespace hpsmc {
 
-hipError_t set_rec_tables_mma() { return upload_recurrence_tables(); }
-
 // ===========================================================================
 // Round kernel, matrix-core form: d = 2, FP32, one path per lane, the whole
 // slab of a step in LDS (its image copied straight from the table).  The step

@@ -3,8 +3,6 @@
 
 namespace hpsmc {
 
-hipError_t set_rec_tables_mma5() { return upload_recurrence_tables(); }
-
 // ===========================================================================
 // The residual of a walk step needs u and v at the path's point X, each a
 // contraction of the step's slab S[k0..k4] with the tensor product of the

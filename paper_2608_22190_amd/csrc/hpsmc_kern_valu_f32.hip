@@ -3,8 +3,6 @@
 
 namespace hpsmc {
 
-hipError_t set_rec_tables_valu_f32() { return upload_recurrence_tables(); }
-
 hipError_t launch_adv_valu_f32(const RoundArgs &a, int ns, dim3 grid, dim3 block, size_t lds, hipStream_t s)
 {
     return adv_d<float>(a, ns, grid, block, lds, s);

@@ -28,17 +28,6 @@ constexpr int kGridYZ = 65535;
 static inline unsigned grid_blocks(int64_t n, int block) { return (unsigned)std::min<int64_t>((n + block - 1) / block, kGridCap); }
 
 
-hipError_t set_rec_tables_main() { return upload_recurrence_tables(); }
-
-hipError_t set_recurrence_tables()
-{
-    for (hipError_t (*f)() : {set_rec_tables_main, set_rec_tables_valu_f32, set_rec_tables_valu_f64,
-                              set_rec_tables_mma, set_rec_tables_mma5, set_rec_tables_frac,
-                              set_rec_tables_adjoint})
-        if (hipError_t e = f(); e != hipSuccess) return e;
-    return hipSuccess;
-}
-
 // ---------------------------------------------------------------------------
 // Persistent sampling kernel.  Each wavefront repeatedly takes one work item
 // (node, chunk of 64*NS samples) from a global counter until none is left.
