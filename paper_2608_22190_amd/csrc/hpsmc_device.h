@@ -457,12 +457,196 @@ __device__ __forceinline__ T source_of(const Physics &ph, const T (&X)[D], T t)
 }
 
 // ---------------------------------------------------------------------------
-// Tensor-product Legendre contraction of one step's slab.
-//   u(X) = sum_k Su[k] prod_i L_{k_i}(X_i),  v(X) likewise with Sv.
-// The last dimension's L values sit in registers (Ll); the outer dimensions
-// run as loops whose L values advance by the recurrence on the fly.  Slab rows
-// are wave-uniform: [u: PP][v: PP] per multi-index of the first d-1 dims.
-// UO skips the v half: the Picard-form integrand needs u only.
+// Four modes k .. k + 3 of an FP64 slab row: u += cu_k L[k], v += cv_k L[k], the
+// coefficients of the sixteen modes that a row of sixteen lanes holds taken by the
+// row broadcast of the fma's own operand (K0: the first mode's lane).  Four sums run
+// side by side: two paths' u and v, or the even and the odd modes of one path's.
+// The leading s_nop keeps the two wait states between a write of cu / cv by a vector
+// instruction (a register copy) and their first broadcast.  Every lane is active.
+// ---------------------------------------------------------------------------
+template <int K0, int PMAX>
+__device__ __forceinline__ void row_fma4(double &u0, double &v0, double &u1, double &v1, double cu, double cv,
+                                         const double (&L0)[PMAX], const double (&L1)[PMAX], int k)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %4, %6 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %5, %6 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %4, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %5, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %4, %7 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %5, %7 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %4, %11 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %5, %11 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %4, %8 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %5, %8 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %4, %12 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %5, %12 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %4, %9 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %5, %9 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %4, %13 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %5, %13 row_newbcast:%17 row_mask:0xf bank_mask:0xf"
+        : "+&v"(u0), "+&v"(v0), "+&v"(u1), "+&v"(v1)
+        : "v"(cu), "v"(cv), "v"(L0[k]), "v"(L0[k + 1]), "v"(L0[k + 2]), "v"(L0[k + 3]),
+          "v"(L1[k]), "v"(L1[k + 1]), "v"(L1[k + 2]), "v"(L1[k + 3]), "n"(K0), "n"(K0 + 1), "n"(K0 + 2), "n"(K0 + 3));
+}
+template <int K0, int PMAX>
+__device__ __forceinline__ void row_fma4(double &u0, double &v0, double &u1, double &v1, double cu, double cv,
+                                         const double (&L)[PMAX], int k)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %4, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %5, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %4, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %5, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %4, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %5, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %4, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %5, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf"
+        : "+&v"(u0), "+&v"(v0), "+&v"(u1), "+&v"(v1)
+        : "v"(cu), "v"(cv), "v"(L[k]), "v"(L[k + 1]), "v"(L[k + 2]), "v"(L[k + 3]), "n"(K0), "n"(K0 + 1), "n"(K0 + 2), "n"(K0 + 3));
+}
+template <int K0, int PMAX>
+__device__ __forceinline__ void row_fma4(double &u0, double &u1, double cu, const double (&L)[PMAX], int k)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %2, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %2, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %2, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %2, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf"
+        : "+&v"(u0), "+&v"(u1)
+        : "v"(cu), "v"(L[k]), "v"(L[k + 1]), "v"(L[k + 2]), "v"(L[k + 3]), "n"(K0), "n"(K0 + 1), "n"(K0 + 2), "n"(K0 + 3));
+}
+
+// One FP64 slab row in registers: lane l holds modes l % 16, 16 + l % 16, ... of both tables
+template <int PMAX> struct SlabRow {
+    static constexpr int NR = (PMAX + 15) / 16;
+    double cu[NR], cv[NR];
+    __device__ __forceinline__ void load(const double *srow, int PP, const int (&off)[NR])
+    {
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            cu[j] = srow[off[j]];
+            cv[j] = srow[PP + off[j]];
+        }
+    }
+};
+
+// u[s] += W[s] sum_k cu_k L[s][k] (v likewise) over the row's P modes (zeros to a multiple of 4)
+template <int PMAX, int NS, bool UO>
+__device__ __forceinline__ void row_dot(const SlabRow<PMAX> &r, int P, const double (&Ll)[NS][PMAX],
+                                        const double (&W)[NS], double (&u)[NS], double (&v)[NS])
+{
+    constexpr int NA = NS == 1 ? 2 : NS;   // sums: one per path, or the even and odd modes of one
+    constexpr int kPmin = PMAX <= 12 ? 1 : PMAX - 7;   // fewest modes of the tier (adv_p)
+    double tu[NA], tv[NA];
+#pragma unroll
+    for (int s = 0; s < NA; ++s) { tu[s] = 0.0; tv[s] = 0.0; }
+    auto four = [&](auto kbc) {
+        constexpr int kb = decltype(kbc)::value, K0 = 4 * kb % 16;
+        if constexpr (kb < PMAX / 4) {
+            if (kb * 4 < kPmin || kb * 4 < P) {
+                const double cu = r.cu[kb / 4], cv = r.cv[kb / 4];
+                if constexpr (UO) {
+                    row_fma4<K0>(tu[0], tu[1], cu, Ll[0], 4 * kb);   // one path per lane
+                } else if constexpr (NS == 1) {
+                    row_fma4<K0>(tu[0], tv[0], tu[1], tv[1], cu, cv, Ll[0], 4 * kb);
+                } else {
+#pragma unroll
+                    for (int s = 0; s < NS; s += 2)
+                        row_fma4<K0>(tu[s], tv[s], tu[s + 1], tv[s + 1], cu, cv, Ll[s], Ll[s + 1], 4 * kb);
+                }
+            }
+        }
+    };
+    four(std::integral_constant<int, 0>{});
+    four(std::integral_constant<int, 1>{});
+    four(std::integral_constant<int, 2>{});
+    four(std::integral_constant<int, 3>{});
+    four(std::integral_constant<int, 4>{});
+    four(std::integral_constant<int, 5>{});
+    four(std::integral_constant<int, 6>{});
+    four(std::integral_constant<int, 7>{});
+    four(std::integral_constant<int, 8>{});
+    if constexpr (NS == 1) { tu[0] += tu[1]; tv[0] += tv[1]; }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        u[s] = fma(W[s], tu[s], u[s]);
+        if constexpr (!UO) v[s] = fma(W[s], tv[s], v[s]);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Contraction of one step's FP64 slab in LDS for the vector-unit round kernels:
+//   u(X) = sum_k Su[k] prod_i T_{k_i}(X_i),  v(X) likewise with Sv,
+// in the Chebyshev basis (converted by mode products before the time contraction):
+// its recurrence is one fma and has no constants, whose scalar loads made every row
+// wait for the LDS reads of the next one.  The last dimension's values sit in
+// registers (Ll); the outer dimensions run as loops whose values advance on the fly.  The coefficients are
+// the same for every lane, so reading them as LDS broadcasts costs 64 lanes' worth
+// of LDS return for every two of them, which bounded these kernels.  A row is read
+// sixteen coefficients at a time instead, one per lane of every row of sixteen
+// lanes, and the fma's take them through the DPP row broadcast at nearly the fma
+// rate (63 against 67 TFLOP/s in a probe): an eighth of the LDS traffic.  The next
+// row is read one row ahead, and the slabs go straight from global memory into LDS
+// (no staging registers): 24 x 24 x 16 nodes, 128 samples, a quarter interval 534 ->
+// 373 ms with two paths per lane, 356 with one.  (FP32 keeps the broadcasts below: its fma loses a
+// quarter of its rate to the DPP operand, 70 against 97 TFLOP/s, and the 3-D
+// iteration went from 9.7 to 11.3 ms.)  UO skips the v half: the Picard form's
+// integrand needs u only.
+// ---------------------------------------------------------------------------
+template <int D, int PMAX, int NS, int LV, bool UO>
+__device__ __forceinline__ void contract_lds(const double *S, int P, int PP, const double (&X)[NS][D],
+                                             const double (&W)[NS], const double (&Ll)[NS][PMAX], double (&u)[NS],
+                                             double (&v)[NS], int row, const int (&off)[SlabRow<PMAX>::NR])
+{
+    if constexpr (LV == D - 1) {
+        SlabRow<PMAX> r;
+        r.load(S + row * (2 * PP), PP, off);
+        row_dot<PMAX, NS, UO>(r, P, Ll, W, u, v);
+    } else {
+        double Lp[NS], Lc[NS], x2[NS];   // T_{k-1} (T_{-1} = T_1 = x), T_k
+#pragma unroll
+        for (int s = 0; s < NS; ++s) { Lp[s] = X[s][LV]; Lc[s] = 1.0; x2[s] = X[s][LV] + X[s][LV]; }
+        auto advance = [&]() {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const double nx = fma(x2[s], Lc[s], -Lp[s]);
+                Lp[s] = Lc[s];
+                Lc[s] = nx;
+            }
+        };
+        if constexpr (LV == D - 2) {
+            const double *srow = S + row * P * (2 * PP);
+            SlabRow<PMAX> r[2];
+            r[0].load(srow, PP, off);
+            for (int k = 0; k < P; k += 2) {   // two rows a turn: the row ahead needs no copy
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (h == 1 && k + 1 >= P) break;
+                    if (k + h + 1 < P) r[h ^ 1].load(srow + (k + h + 1) * (2 * PP), PP, off);
+                    double W2[NS];
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) W2[s] = W[s] * Lc[s];
+                    row_dot<PMAX, NS, UO>(r[h], P, Ll, W2, u, v);
+                    advance();
+                }
+            }
+        } else {
+            for (int k = 0; k < P; ++k) {
+                double W2[NS];
+#pragma unroll
+                for (int s = 0; s < NS; ++s) W2[s] = W[s] * Lc[s];
+                contract_lds<D, PMAX, NS, LV + 1, UO>(S, P, PP, X, W2, Ll, u, v, row * P + k, off);
+                advance();
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Tensor-product Legendre contraction of one step's slab (the same sums), from
+// scalar loads or LDS broadcasts: slab rows are wave-uniform, [u: PP][v: PP] per
+// multi-index of the first d-1 dims.
 // ---------------------------------------------------------------------------
 template <typename T, int D, int PMAX, int NS, int LV, typename SP, bool UO = false>
 __device__ __forceinline__ void contract(SP S, int P, int PP, const T (&X)[NS][D], const T (&W)[NS],

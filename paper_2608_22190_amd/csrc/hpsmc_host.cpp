@@ -1431,40 +1431,52 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
     return HPSMC_OK;
 }
 
+// Legendre tensors [outer][P^d][T1] into the Chebyshev basis of every spatial
+// dimension, one mode product each (tmp0 and tmp1 in between)
+static hpsmc_status to_chebyshev(hpsmc_plan *plan, const double *in, double *out, int64_t outer, int T1, hipStream_t s)
+{
+    const int P = plan->P, d = plan->d;
+    double *bufs[2] = {plan->tmp0, plan->tmp1};
+    for (int i = 0; i < d; ++i) {
+        double *o = i == d - 1 ? out : bufs[i & 1];
+        HIP_TRY(launch_mode_product(in, o, outer * ipow(P, i), P, P, ipow(P, d - 1 - i) * T1, plan->mats + plan->cheb_off,
+                                    1.0, 0, s));
+        in = o;
+    }
+    return HPSMC_OK;
+}
+
+// Whether the rows of this set's slabs (row layout) hold Chebyshev coefficients:
+// those of the FP64 round kernels and of the windowed 1-D kernel do
+static bool cheb_rows(const hpsmc_plan *plan, const NodeSet &set)
+{
+    return !plan->frac && set.rounds && (!plan->fp32 || set_uses_1d(plan, set));
+}
+
 // Slab arguments for `layout`: the 2-D matrix-core image (layout 1) holds
-// Chebyshev coefficients in both spatial dimensions, so c^u and c^v of the
-// set's intervals are converted first (two mode products per table and
-// interval) and the slab kernel reads the converted tensors.  The rows of the
-// windowed 1-D kernel (cheb1d, row layout) hold Chebyshev coefficients too
-// (one mode product per table and interval).
-static hpsmc_status slab_args_for(hpsmc_plan *plan, const NodeSet &set, int layout, bool cheb1d, SlabArgs &sa,
+// Chebyshev coefficients in both spatial dimensions, and so do the rows of the FP64
+// round kernels and of the windowed 1-D kernel (cheb, row layout): c^u and c^v of
+// the set's intervals are converted first and the slab kernel reads the converted
+// tensors.
+static hpsmc_status slab_args_for(hpsmc_plan *plan, const NodeSet &set, int layout, bool cheb, SlabArgs &sa,
                                   hipStream_t s)
 {
     sa = set.slab;
     sa.slab_table = plan->slab_table;
     sa.layout = layout;
-    if (layout != 1 && !cheb1d) return HPSMC_OK;
+    if (layout != 1 && !(cheb && layout == 0)) return HPSMC_OK;
     if (!plan->cu_ch) return fail(HPSMC_EINVAL, "no Chebyshev coefficient buffers for this slab layout");
-    const int P = plan->P;
-    const double *A = plan->mats + plan->cheb_off;
-    const int64_t I = plan->n_inst;
     for (int32_t iv : set.ivs) {
         const int T1 = plan->degree[iv] + 1;
-        for (int t = 0; t < 2; ++t) {
-            const double *in = (t ? plan->cv : plan->cu) + plan->c_off[iv];
-            double *out = (t ? plan->cv_ch : plan->cu_ch) + plan->c_off[iv];
-            if (plan->d == 1) {
-                HIP_TRY(launch_mode_product(in, out, I, P, P, T1, A, 1.0, 0, s));
-            } else {
-                HIP_TRY(launch_mode_product(in, plan->tmp0, I, P, P, (int64_t)P * T1, A, 1.0, 0, s));
-                HIP_TRY(launch_mode_product(plan->tmp0, out, I * P, P, P, T1, A, 1.0, 0, s));
-            }
-        }
+        for (int t = 0; t < 2; ++t)
+            if (hpsmc_status st = to_chebyshev(plan, (t ? plan->cv : plan->cu) + plan->c_off[iv],
+                                               (t ? plan->cv_ch : plan->cu_ch) + plan->c_off[iv], plan->n_inst, T1, s))
+                return st;
     }
     sa.cu = plan->cu_ch;
     sa.cv = plan->cv_ch;
     if (sa.cs) sa.cs = plan->cs_ch;
-    if (layout == 1 && mma_split(P)) HIP_TRY(launch_coef_scale(sa, s));
+    if (layout == 1 && mma_split(plan->P)) HIP_TRY(launch_coef_scale(sa, s));
     return HPSMC_OK;
 }
 
@@ -1472,7 +1484,7 @@ static hpsmc_status sample_set(hpsmc_plan *plan, NodeSet &set, int tag, int reco
 {
     const int ns = plan->launch.samples_per_lane;
     SlabArgs sa;
-    if (hpsmc_status st = slab_args_for(plan, set, set_uses_mma(plan, set), set_uses_1d(plan, set), sa, s))
+    if (hpsmc_status st = slab_args_for(plan, set, set_uses_mma(plan, set), cheb_rows(plan, set), sa, s))
         return st;
     hpsmc_plan::EvPair *es = next_pair(plan->ev_slab, plan->n_slab);
     if (es) HIP_TRY(hipEventRecord(es->a, s));
@@ -1750,8 +1762,8 @@ hpsmc_status hpsmc_create(const hpsmc_problem *pb, hpsmc_plan **out)
         plan->ainv_off = (int64_t)mats.size();
         mats.insert(mats.end(), Ainv.begin(), Ainv.end());
     }
-    // the basis of the 2-D matrix-core image and of the windowed 1-D kernel's rows
-    const bool cheb = !plan->frac && ((plan->d == 2 && mma_capable(pl)) || plan->d == 1);
+    // the basis of the 2-D matrix-core image and of the FP64 and windowed 1-D kernels' rows
+    const bool cheb = !plan->frac && (!plan->fp32 || (plan->d == 2 && mma_capable(pl)) || plan->d == 1);
     if (cheb) {
         auto Ach = legendre_to_chebyshev(plan->P);
         plan->cheb_off = (int64_t)mats.size();
@@ -1771,20 +1783,10 @@ hpsmc_status hpsmc_create(const hpsmc_problem *pb, hpsmc_plan **out)
         int64_t off = 0;
         for (int iv = 0; iv < plan->n_iv; ++iv) off += plan->psp * (plan->degree[iv] + 1);
         if ((st = dalloc(pl, (void **)&pl->cs_ch, off * 8))) return st;
-        const double *A = pl->mats + pl->cheb_off;
-        const int P = plan->P;
-        for (int iv = 0; iv < plan->n_iv; ++iv) {
-            const int T1 = plan->degree[iv] + 1;
-            const bool ok =
-                plan->d == 1
-                    ? launch_mode_product(pl->src_poly + pl->src_off[iv], pl->cs_ch + pl->src_off[iv], 1, P, P, T1, A,
-                                          1.0, 0, nullptr) == hipSuccess
-                    : launch_mode_product(pl->src_poly + pl->src_off[iv], pl->tmp0, 1, P, P, (int64_t)P * T1, A, 1.0,
-                                          0, nullptr) == hipSuccess &&
-                          launch_mode_product(pl->tmp0, pl->cs_ch + pl->src_off[iv], P, P, P, T1, A, 1.0, 0, nullptr) ==
-                              hipSuccess;
-            if (!ok) return fail(HPSMC_EDEVICE, "source conversion failed");
-        }
+        for (int iv = 0; iv < plan->n_iv; ++iv)
+            if ((st = to_chebyshev(pl, pl->src_poly + pl->src_off[iv], pl->cs_ch + pl->src_off[iv], 1,
+                                   plan->degree[iv] + 1, nullptr)))
+                return st;
     }
 
     // node sets and the slab table

@@ -7,6 +7,33 @@
 
 namespace hpsmc {
 
+// The basis of the slab rows: Chebyshev polynomials in FP64 (contract_lds), Legendre
+// in FP32.
+template <typename T, int PMAX>
+__device__ __forceinline__ void basis_row(T x, T (&L)[PMAX])
+{
+    L[0] = (T)1;
+    if (PMAX > 1) L[1] = x;
+#pragma unroll
+    for (int k = 1; k + 1 < PMAX; ++k) {
+        if constexpr (sizeof(T) == 8) L[k + 1] = fma(x + x, L[k], -L[k - 1]);
+        else L[k + 1] = (T)((2.0 * k + 1.0) / (k + 1.0)) * x * L[k] - (T)(k / (k + 1.0)) * L[k - 1];
+    }
+}
+template <typename T>
+__device__ __forceinline__ T basis_value(T x, int k)
+{
+    T lp = sizeof(T) == 8 ? x : (T)0, lc = (T)1;   // T_{-1} = x
+    for (int m = 0; m < k; ++m) {
+        T nx;
+        if constexpr (sizeof(T) == 8) nx = fma(x + x, lc, -lp);
+        else nx = rec_a<T>(m) * x * lc - rec_b<T>(m) * lp;
+        lp = lc;
+        lc = nx;
+    }
+    return lc;
+}
+
 // EXT: the Picard form and the ball-point rule are compiled in (selected at
 // run time by Physics); without it the residual form with the centre-point
 // rule carries none of their code.
@@ -30,6 +57,9 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
     using State = PathState<T, D>;
     const State *sin = (const State *)a.state_in;
     State *sout = (State *)a.state_out;
+    int off[SlabRow<PMAX>::NR];   // FP64: this lane's modes of a slab row
+#pragma unroll
+    for (int j = 0; j < SlabRow<PMAX>::NR; ++j) off[j] = min(16 * j + (lane & 15), a.PP - 1);
 
     for (bool first = true;; first = false) {
         const int64_t item = take_item(a, total, first, s_item);
@@ -94,16 +124,9 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
         fill_time(q0);
 
         // ---- first chunk of the first evaluated step's slab into LDS buffer 0
-        u32x4 stage[NSTG];
         int qe = q0 + share, buf = 0;   // the next step this share evaluates, its buffer
-        if (qe < q1) {
-            const u32x4 *src = (const u32x4 *)(gtab + (int64_t)qe * a.slab_stride);
-#pragma unroll
-            for (int k = 0; k < NSTG; ++k) {
-                const int64_t v = tid + (int64_t)k * nthr;
-                if (v < nvec) lds[v] = src[v];
-            }
-        }
+        if (qe < q1) mma_stage((const u32x4 *)(gtab + (int64_t)qe * a.slab_stride), lds, (int)nvec, tid, nthr);
+        mma_stage_wait();
         __syncthreads();
 
         uint32_t w[NS][4];
@@ -193,24 +216,14 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 const T x = X[s][D - 1];
-                Ll[s][0] = (T)1;
-                if (PMAX > 1) Ll[s][1] = x;
-#pragma unroll
-                for (int k = 1; k + 1 < PMAX; ++k)
-                    Ll[s][k + 1] = (T)((2.0 * k + 1.0) / (k + 1.0)) * x * Ll[s][k] - (T)(k / (k + 1.0)) * Ll[s][k - 1];
+                basis_row<T, PMAX>(x, Ll[s]);
             }
             for (int c = 0; c < NC; ++c) {
                 int qn = q, cn = c + 1;
                 if (cn == NC) { cn = 0; qn = qe; }
-                const bool has_next = qn < q1;
-                if (has_next) {
-                    const u32x4 *src = (const u32x4 *)(gtab + (int64_t)qn * a.slab_stride + (int64_t)cn * a.chunk_elems);
-#pragma unroll
-                    for (int k = 0; k < NSTG; ++k) {
-                        const int64_t vv = tid + (int64_t)k * nthr;
-                        if (vv < nvec) stage[k] = src[vv];
-                    }
-                }
+                if (qn < q1)   // straight into the other buffer, whose readers passed the last barrier
+                    mma_stage((const u32x4 *)(gtab + (int64_t)qn * a.slab_stride + (int64_t)cn * a.chunk_elems),
+                              lds + (int64_t)(buf ^ 1) * cvec, (int)nvec, tid, nthr);
                 if (wave_live) {
                     const T *S = (const T *)(lds + (int64_t)buf * cvec);
                     T Wc[NS];
@@ -224,31 +237,25 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
                             const int ki = rem % a.P;
                             rem /= a.P;
 #pragma unroll
-                            for (int s = 0; s < NS; ++s) {
-                                T lp = (T)0, lc = (T)1;
-                                for (int m = 0; m < ki; ++m) {
-                                    const T nx = rec_a<T>(m) * X[s][i] * lc - rec_b<T>(m) * lp;
-                                    lp = lc;
-                                    lc = nx;
-                                }
-                                Wc[s] *= lc;
-                            }
+                            for (int s = 0; s < NS; ++s) Wc[s] *= basis_value<T>(X[s][i], ki);
                         }
                     }
-                    if (picard)
-                        contract<T, D, PMAX, NS, CF, const T *, true>(S, a.P, a.PP, X, Wc, Ll, u, v, 0);
-                    else
-                        contract<T, D, PMAX, NS, CF, const T *, false>(S, a.P, a.PP, X, Wc, Ll, u, v, 0);
-                }
-                if (has_next) {
-                    u32x4 *dst = lds + (int64_t)(buf ^ 1) * cvec;
-#pragma unroll
-                    for (int k = 0; k < NSTG; ++k) {
-                        const int64_t vv = tid + (int64_t)k * nthr;
-                        if (vv < nvec) dst[vv] = stage[k];
+                    auto sum = [&](auto uo) {
+                        constexpr bool UO = decltype(uo)::value;
+                        if constexpr (sizeof(T) == 8)
+                            contract_lds<D, PMAX, NS, CF, UO>(S, a.P, a.PP, X, Wc, Ll, u, v, 0, off);
+                        else
+                            contract<T, D, PMAX, NS, CF, const T *, UO>(S, a.P, a.PP, X, Wc, Ll, u, v, 0);
+                    };
+                    if constexpr (EXT) {
+                        if (picard) sum(std::true_type{});
+                        else sum(std::false_type{});
+                    } else {
+                        sum(std::false_type{});
                     }
                 }
                 buf ^= 1;
+                mma_stage_wait();
                 if (c + 1 < NC) __syncthreads();
             }
             if (wave_live) {
@@ -288,11 +295,7 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 const T x = X[s][D - 1];
-                Ll[s][0] = (T)1;
-                if (PMAX > 1) Ll[s][1] = x;
-#pragma unroll
-                for (int k = 1; k + 1 < PMAX; ++k)
-                    Ll[s][k + 1] = (T)((2.0 * k + 1.0) / (k + 1.0)) * x * Ll[s][k] - (T)(k / (k + 1.0)) * Ll[s][k - 1];
+                basis_row<T, PMAX>(x, Ll[s]);
                 u[s] = (T)0;
                 v[s] = (T)0;
             }
@@ -316,18 +319,13 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
                             const int ki = rem % a.P;
                             rem /= a.P;
 #pragma unroll
-                            for (int s = 0; s < NS; ++s) {
-                                T lp = (T)0, lc = (T)1;
-                                for (int m = 0; m < ki; ++m) {
-                                    const T nx = rec_a<T>(m) * X[s][i] * lc - rec_b<T>(m) * lp;
-                                    lp = lc;
-                                    lc = nx;
-                                }
-                                Wc[s] *= lc;
-                            }
+                            for (int s = 0; s < NS; ++s) Wc[s] *= basis_value<T>(X[s][i], ki);
                         }
                     }
-                    contract<T, D, PMAX, NS, CF, const T *, true>((const T *)lds, a.P, a.PP, X, Wc, Ll, u, v, 0);
+                    if constexpr (EXT && sizeof(T) == 8)
+                        contract_lds<D, PMAX, NS, CF, true>((const T *)lds, a.P, a.PP, X, Wc, Ll, u, v, 0, off);
+                    else if constexpr (EXT)
+                        contract<T, D, PMAX, NS, CF, const T *, true>((const T *)lds, a.P, a.PP, X, Wc, Ll, u, v, 0);
                 }
             }
 #pragma unroll
@@ -383,12 +381,16 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
     add_stats(a, evals, slots);
 }
 
-// One-dimensional FP64 kernels with two paths per lane and up to 20 Legendre
-// modes sit a few registers above the two-waves-per-SIMD budget; holding them
-// to it spills five registers to scratch and still lifts the 1-D
-// whole-solve throughput by a third (12.5 M -> 16.1 M node-samples/s).
+// FP64 kernels that sit a few registers above the budget of one more wave per
+// SIMD are held to it: one path per lane to three waves, two paths to two.
 template <typename T, int D, int NS, int PMAX>
-constexpr int advance_min_waves() { return (sizeof(T) == 8 && D == 1 && NS == 2 && PMAX <= 20) ? 2 : 1; }
+constexpr int advance_min_waves()
+{
+    if (sizeof(T) != 8) return 1;
+    if (D == 1) return NS == 2 && PMAX <= 20 ? 2 : 1;
+    if (D == 2 && PMAX <= 28) return NS == 1 ? 3 : NS == 2 ? 2 : 1;
+    return 1;
+}
 
 template <typename T, int D, int PMAX, int NS, int CF, bool EXT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(advance_min_waves<T, D, NS, PMAX>())))
