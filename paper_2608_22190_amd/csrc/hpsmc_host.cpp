@@ -814,7 +814,7 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     sa.inv_scale = (float *)(gb + G * 72 + NBLK * 16);
     sa.blk_group = (const int32_t *)(gb + G * 72 + NBLK * 24);
     sa.n_blk = (int32_t)NBLK;
-    sa.bscale = d == 2 ? mma_basis_scale(plan) : 0.0;
+    sa.bscale = d == 2 ? mma_basis_scale(plan) : 1024.0;   // 5-D: |L_k| <= 1 in the domain
     sa.mma_stride = mstride;
     sa.layout = 0;
     sa.extra = extra;
@@ -1464,6 +1464,7 @@ static hpsmc_status slab_args_for(hpsmc_plan *plan, const NodeSet &set, int layo
     sa = set.slab;
     sa.slab_table = plan->slab_table;
     sa.layout = layout;
+    if (layout == 2) HIP_TRY(launch_coef_scale(sa, s));
     if (layout != 1 && !(cheb && layout == 0)) return HPSMC_OK;
     if (!plan->cu_ch) return fail(HPSMC_EINVAL, "no Chebyshev coefficient buffers for this slab layout");
     for (int32_t iv : set.ivs) {

@@ -1,4 +1,4 @@
-// Matrix-core form of the 5-D FP32 round kernel (v_mfma_f32_32x32x2f32).
+// Matrix-core form of the 5-D FP32 round kernel (v_mfma_f32_32x32x16_f16 on split factors).
 #include "hpsmc_device.h"
 
 namespace hpsmc {
@@ -16,13 +16,17 @@ namespace hpsmc {
 // + O(P^3) operations of a residual evaluation; it runs on the matrix cores in
 // 32-row tiles (the slab layout of mma5_geom) streamed through LDS.
 //
-// Operands of v_mfma_f32_32x32x2f32 (A: lane l holds A[l%32][l/32]; B:
-// B[l/32][l%32]; D register r: D[8(r/4) + 4(l/32) + r%4][l%32]).  Paths 0-31
-// form product "A", paths 32-63 product "B", the u and v tables each take
-// both: four independent accumulators.  K-step j = (k3, m) feeds k4 = 2m on
-// lanes 0-31 and k4 = 2m + 1 on lanes 32-63, so a lane needs L_{k3} and
-// L_{k4} of its own path and of the path 32 lanes away -- one permlane32 swap
-// per value, once per step -- and forms each B entry with one multiply.
+// Both factors are split into two half-precision parts (as in the 2-D kernel, whose
+// operand layout it shares): a product of 32x32x16 takes eight modes, lanes 0-31
+// feeding part 0 of the B entries and lanes 32-63 part 1 against the same part of
+// the slab.  Paths 0-31 form product "A", paths 32-63 product "B".  The B entries are
+// formed and split once per step and stay in registers for all tiles: at P = 10, 50
+// split pairs and swaps a step and 104 products of 32x32x16 a tile, where FP32
+// products (32x32x2) took 200 a tile, of twice the time each, and formed every entry
+// again for every tile: 8^5 x 8 nodes, two samples, 302 -> 155 ms an iteration.  Error
+// against 64 bits (rms over random and decaying tables, of the largest coefficient):
+// 0.75-0.85 of the FP32 products' at P = 5, 0.55-0.8 at 10, the same to 1.2 times it at
+// P = 3 (one spatial node per dimension), 0.83-0.91 at 4.
 // ===========================================================================
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -36,110 +40,69 @@ __device__ __forceinline__ void legendre_row(float x, float (&L)[P])
         L[k + 1] = (float)((2.0 * k + 1.0) / (k + 1.0)) * x * L[k] - (float)(k / (k + 1.0)) * L[k - 1];
 }
 
-// B-operand factors of the wave's 64 points: a3/a4 for product A (paths 0-31),
-// b3/b4 for product B (paths 32-63), in the lane-half split of the K-steps
+// B operands: entries L_{k3}(x3) L_{k4}(x4) of the wave's 64 points, scaled by
+// bscale, in two parts, modes k3 P + k4 in pairs
+template <int P> struct Mma5B {
+    static constexpr int NB = mma5_geom(P).NB;
+    uint32_t r[4 * NB];
+    __device__ __forceinline__ h16x8 block(int b) const
+    {
+        const u32x4 q = {r[4 * b], r[4 * b + 1], r[4 * b + 2], r[4 * b + 3]};
+        return __builtin_bit_cast(h16x8, q);
+    }
+};
 template <int P>
-__device__ __forceinline__ void mma5_operands(float x3, float x4, float (&a3)[P], float (&b3)[P],
-                                              float (&a4)[(P + 1) / 2], float (&b4)[(P + 1) / 2])
+__device__ __forceinline__ void mma5_operands(float x3, float x4, float bscale, Mma5B<P> &bA, Mma5B<P> &bB)
 {
-    constexpr int HK = (P + 1) / 2;
     float L3[P], L4[P];
     legendre_row<P>(x3, L3);
     legendre_row<P>(x4, L4);
 #pragma unroll
-    for (int k = 0; k < P; ++k) {
-        // lanes 0-31 keep their own value and take the upper lane's, lanes 32-63 the reverse
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(L3[k]), __float_as_uint(L3[k]), false, false);
-        a3[k] = __uint_as_float(r[0]);
-        b3[k] = __uint_as_float(r[1]);
-    }
+    for (int k = 0; k < P; ++k) L3[k] *= bscale;   // a power of two
+    const float m1 = opaque_minus_one();
 #pragma unroll
-    for (int m = 0; m < HK; ++m) {
-        const float lo = L4[2 * m], hi = 2 * m + 1 < P ? L4[2 * m + 1] : 0.f;   // odd P: mode P is zero
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
-        a4[m] = __uint_as_float(r[0]);   // lanes 0-31: own L_{2m}; lanes 32-63: L_{2m+1} of lane - 32
-        b4[m] = __uint_as_float(r[1]);   // lanes 0-31: L_{2m} of lane + 32; lanes 32-63: own L_{2m+1}
+    for (int i = 0; i < 4 * Mma5B<P>::NB; ++i) {
+        bA.r[i] = 0u;
+        bB.r[i] = 0u;
+        if (2 * i < P * P) {
+            const int m0 = 2 * i, n0 = 2 * i + 1 < P * P ? 2 * i + 1 : 2 * i;
+            const float e0 = L3[m0 / P] * L4[m0 % P], e1 = n0 > m0 ? L3[n0 / P] * L4[n0 % P] : 0.f;
+            const uint32_t h = pack_h16(e0, e1), l = pack_h16_rest(e0, e1, h, m1);
+            const auto r = __builtin_amdgcn_permlane32_swap(h, l, false, false);
+            bA.r[i] = r[0];
+            bB.r[i] = r[1];
+        }
     }
 }
 
-// the four products of one tile over k-steps [J0, J1) (S: the chunk's u tile,
-// its v tile 32 RS floats on)
-template <int P, int J0, int J1>
-__device__ __forceinline__ void mma5_tile(const float *S, int lane, const float (&a3)[P], const float (&b3)[P],
-                                          const float (&a4)[(P + 1) / 2], const float (&b4)[(P + 1) / 2],
-                                          f32x16 &uA, f32x16 &vA, f32x16 &uB, f32x16 &vB)
+// the products of one tile and table with both path halves (S: the tile's two parts),
+// over the blocks b of part `part` of `nparts` (b % nparts == part: the waves that
+// share one item in a sparse round); the small part of the slab first.  Slab operands
+// are read two blocks ahead of their products; the fence keeps the scheduler from
+// hoisting all of a tile's reads.
+template <int P, bool PARTS>
+__device__ __forceinline__ void mma5_tile(const u32x4 *S, int lane, const Mma5B<P> &bA, const Mma5B<P> &bB, int part,
+                                          int nparts, f32x16 &dA, f32x16 &dB)
 {
-    constexpr Mma5Geom g = mma5_geom(P);
-    static_assert(0 <= J0 && J0 < J1 && J1 <= g.KJ, "k-step range");
-    constexpr int JB = J0 & ~3;   // first 16-byte group
-    const float *Au = S + (lane & 31) * g.RS + (lane >> 5) * g.KH2;
-    const float *Av = Au + 32 * g.RS;
-    uA = f32x16{}; vA = f32x16{}; uB = f32x16{}; vB = f32x16{};
-    // the B entries are formed next to their products: hoisted out of the tile
-    // and k0 loops, all KJ pairs of them would stay live
-    float f3[P], g3[P], f4[(P + 1) / 2], g4[(P + 1) / 2];
+    constexpr int NB = mma5_geom(P).NB, N = 2 * NB;
+    const u32x4 *A = S + (lane & 31);
+    dA = f32x16{};
+    dB = f32x16{};
+    // operand n: block n % NB of part 1 (n < NB), then of part 0
+    auto addr = [](int n) { return ((n < NB ? NB : 0) + n % NB) * 32; };
+    u32x4 x[2];
+    x[0] = A[addr(0)];
+    if (N > 1) x[1] = A[addr(1)];
 #pragma unroll
-    for (int k = 0; k < P; ++k) {
-        f3[k] = a3[k];
-        g3[k] = b3[k];
-        asm volatile("" : "+v"(f3[k]), "+v"(g3[k]));
-    }
-#pragma unroll
-    for (int m = 0; m < (P + 1) / 2; ++m) {
-        f4[m] = a4[m];
-        g4[m] = b4[m];
-        asm volatile("" : "+v"(f4[m]), "+v"(g4[m]));
-    }
-    // A operands four k-steps at a time, one group ahead of the products; the
-    // scheduling fence keeps later groups from being hoisted (their registers
-    // would push the kernel past two waves per SIMD)
-    f32x4 xu = *(const f32x4 *)(Au + JB), xv = *(const f32x4 *)(Av + JB);
-#pragma unroll
-    for (int jj = JB; jj < J1; jj += 4) {
-        f32x4 nu = xu, nv = xv;
-        if (jj + 4 < J1) {
-            nu = *(const f32x4 *)(Au + jj + 4);
-            nv = *(const f32x4 *)(Av + jj + 4);
+    for (int n = 0; n < N; ++n) {
+        const int b = n % NB;
+        const h16x8 a8 = __builtin_bit_cast(h16x8, x[n & 1]);
+        if (!PARTS || b % nparts == part) {
+            dA = __builtin_amdgcn_mfma_f32_32x32x16_f16(a8, bA.block(b), dA, 0, 0, 0);
+            dB = __builtin_amdgcn_mfma_f32_32x32x16_f16(a8, bB.block(b), dB, 0, 0, 0);
         }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int j = jj + s;
-            if (j >= J0 && j < J1) {
-                const int k3 = j / g.HK, m = j - k3 * g.HK;
-                const float bA = f3[k3] * f4[m], bB = g3[k3] * g4[m];
-                uA = __builtin_amdgcn_mfma_f32_32x32x2f32(xu[s], bA, uA, 0, 0, 0);
-                vA = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[s], bA, vA, 0, 0, 0);
-                uB = __builtin_amdgcn_mfma_f32_32x32x2f32(xu[s], bB, uB, 0, 0, 0);
-                vB = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[s], bB, vB, 0, 0, 0);
-            }
-        }
+        if (n + 2 < N) x[n & 1] = A[addr(n + 2)];
         __builtin_amdgcn_sched_barrier(0);
-        xu = nu;
-        xv = nv;
-    }
-}
-
-// the products of part `part` of `nparts` (1, 2 or 4: the waves that share
-// one item in a sparse round) -- k-steps [KJ part / nparts, KJ (part + 1) / nparts)
-template <int P>
-__device__ __forceinline__ void mma5_tile_part(int part, int nparts, const float *S, int lane, const float (&a3)[P],
-                                               const float (&b3)[P], const float (&a4)[(P + 1) / 2],
-                                               const float (&b4)[(P + 1) / 2], f32x16 &uA, f32x16 &vA, f32x16 &uB,
-                                               f32x16 &vB)
-{
-    constexpr int KJ = mma5_geom(P).KJ;
-    if (nparts == 1) {
-        mma5_tile<P, 0, KJ>(S, lane, a3, b3, a4, b4, uA, vA, uB, vB);
-    } else if (nparts == 2) {
-        if (part == 0) mma5_tile<P, 0, KJ / 2>(S, lane, a3, b3, a4, b4, uA, vA, uB, vB);
-        else mma5_tile<P, KJ / 2, KJ>(S, lane, a3, b3, a4, b4, uA, vA, uB, vB);
-    } else {
-        switch (part) {
-        case 0: mma5_tile<P, 0, KJ / 4>(S, lane, a3, b3, a4, b4, uA, vA, uB, vB); break;
-        case 1: mma5_tile<P, KJ / 4, KJ / 2>(S, lane, a3, b3, a4, b4, uA, vA, uB, vB); break;
-        case 2: mma5_tile<P, KJ / 2, 3 * KJ / 4>(S, lane, a3, b3, a4, b4, uA, vA, uB, vB); break;
-        default: mma5_tile<P, 3 * KJ / 4, KJ>(S, lane, a3, b3, a4, b4, uA, vA, uB, vB); break;
-        }
     }
 }
 
@@ -148,28 +111,24 @@ __device__ __forceinline__ void mma5_tile_part(int part, int nparts, const float
 // half) of the path's column after one swap of the A and B products.
 // Main tile t of a k0: rows f = 32 t + i = (k1, k2); au[k1] += L_{k2} T.
 template <int P>
-__device__ __forceinline__ void mma5_fold_main(int t, const f32x16 &uA, const f32x16 &vA, const f32x16 &uB,
-                                               const f32x16 &vB, const float (&L2)[P], float (&au)[P], float (&av)[P])
+__device__ __forceinline__ void mma5_fold_main(int t, const f32x16 &dA, const f32x16 &dB, const float (&L2)[P],
+                                               float (&acc)[P])
 {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int ia = 8 * (r >> 2) + (r & 3), ib = ia + 4;
         const int fa = 32 * t + ia, fb = 32 * t + ib;
-        const auto pu = __builtin_amdgcn_permlane32_swap(__float_as_uint(uA[r]), __float_as_uint(uB[r]), false, false);
-        const auto pv = __builtin_amdgcn_permlane32_swap(__float_as_uint(vA[r]), __float_as_uint(vB[r]), false, false);
-        au[fa / P] = fmaf(L2[fa % P], __uint_as_float(pu[0]), au[fa / P]);
-        au[fb / P] = fmaf(L2[fb % P], __uint_as_float(pu[1]), au[fb / P]);
-        av[fa / P] = fmaf(L2[fa % P], __uint_as_float(pv[0]), av[fa / P]);
-        av[fb / P] = fmaf(L2[fb % P], __uint_as_float(pv[1]), av[fb / P]);
+        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(dA[r]), __float_as_uint(dB[r]), false, false);
+        acc[fa / P] = fmaf(L2[fa % P], __uint_as_float(p[0]), acc[fa / P]);
+        acc[fb / P] = fmaf(L2[fb % P], __uint_as_float(p[1]), acc[fb / P]);
     }
 }
 
 // Remainder tile t: rows rr = 32 t + i hold (k0, f) = (rr / B, 32 A + rr % B),
 // weight L_{k0} L_{k1} L_{k2}; rows past B P are zero and skipped.
 template <int P>
-__device__ __forceinline__ void mma5_fold_rem(int t, const f32x16 &uA, const f32x16 &vA, const f32x16 &uB,
-                                              const f32x16 &vB, const float (&L0)[P], const float (&L1)[P],
-                                              const float (&L2)[P], float &u, float &v)
+__device__ __forceinline__ void mma5_fold_rem(int t, const f32x16 &dA, const f32x16 &dB, const float (&L0)[P],
+                                              const float (&L1)[P], const float (&L2)[P], float &u)
 {
     constexpr Mma5Geom g = mma5_geom(P);
 #pragma unroll
@@ -177,19 +136,14 @@ __device__ __forceinline__ void mma5_fold_rem(int t, const f32x16 &uA, const f32
         const int ia = 8 * (r >> 2) + (r & 3), ib = ia + 4;
         const int ra = 32 * t + ia, rb = 32 * t + ib;
         if (ra >= g.B * P) continue;   // rb > ra
-        const auto pu = __builtin_amdgcn_permlane32_swap(__float_as_uint(uA[r]), __float_as_uint(uB[r]), false, false);
-        const auto pv = __builtin_amdgcn_permlane32_swap(__float_as_uint(vA[r]), __float_as_uint(vB[r]), false, false);
+        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(dA[r]), __float_as_uint(dB[r]), false, false);
         {
             const int k0 = ra / g.B, f = 32 * g.A + ra % g.B;
-            const float w = L0[k0] * (L1[f / P] * L2[f % P]);
-            u = fmaf(w, __uint_as_float(pu[0]), u);
-            v = fmaf(w, __uint_as_float(pv[0]), v);
+            u = fmaf(L0[k0] * (L1[f / P] * L2[f % P]), __uint_as_float(p[0]), u);
         }
         if (rb < g.B * P) {
             const int k0 = rb / g.B, f = 32 * g.A + rb % g.B;
-            const float w = L0[k0] * (L1[f / P] * L2[f % P]);
-            u = fmaf(w, __uint_as_float(pu[1]), u);
-            v = fmaf(w, __uint_as_float(pv[1]), v);
+            u = fmaf(L0[k0] * (L1[f / P] * L2[f % P]), __uint_as_float(p[1]), u);
         }
     }
 }
@@ -209,7 +163,7 @@ template <int P>
 __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
 {
     constexpr Mma5Geom g5 = mma5_geom(P);
-    constexpr int HK = g5.HK, A = g5.A, R = g5.R, NCH = g5.NCH;
+    constexpr int A = g5.A, R = g5.R, NCH = g5.NCH, TV = 64 * g5.NB;   // TV: 16-byte vectors of a tile's table
     constexpr int CF = (int)g5.chunk, CV = CF / 4;   // floats, 16-byte vectors per chunk
     extern __shared__ u32x4 lds[];
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wave = tid >> 6;
@@ -254,6 +208,7 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
         const uint32_t c3 = G->c3 | (uint32_t)a.tag;
         const int64_t live = a.round == 0 ? (int64_t)G->node_count * a.mcount : (int64_t)a.live_in[g];
         const float *gtab = (const float *)a.slab_table + G->slab_mma;
+        const float iu = a.inv_scale[2 * G->blk], iv = a.inv_scale[2 * G->blk + 1];
 
         // ---- this lane's path
         const int64_t p = b * bsz + (split ? lane : tid);
@@ -322,8 +277,9 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
             qe += shares;
             // ---- u and v at X_q: the step's chunks, the next one always in flight
             const bool wave_live = __ballot(alive) != 0ull;
-            float a3[P], b3[P], a4[HK], b4[HK], L1[P], L2[P];
-            mma5_operands<P>(X[3], X[4], a3, b3, a4, b4);
+            Mma5B<P> bA, bB;
+            float L1[P], L2[P];
+            mma5_operands<P>(X[3], X[4], a.bscale, bA, bB);
             legendre_row<P>(X[1], L1);
             legendre_row<P>(X[2], L2);
             const float *step_src = gtab + (int64_t)q * a.slab_stride;
@@ -332,6 +288,10 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
                 const float *src = c + 1 < NCH ? step_src + (int64_t)(c + 1) * CF
                                                : (more ? gtab + (int64_t)qe * a.slab_stride : nullptr);
                 if (src) mma_stage((const u32x4 *)src, lds + (buf ^ 1) * CV, CV, tid, nthr);
+            };
+            auto tile = [&](const u32x4 *S, const Mma5B<P> &pA, const Mma5B<P> &pB, f32x16 &dA, f32x16 &dB) {
+                if (nparts == 1) mma5_tile<P, false>(S, lane, pA, pB, 0, 1, dA, dB);
+                else mma5_tile<P, true>(S, lane, pA, pB, part, nparts, dA, dB);
             };
             float u = 0.f, v = 0.f;
             if constexpr (A > 0) {
@@ -344,10 +304,11 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
                     for (int t = 0; t < A; ++t) {
                         stage_next(k0 * A + t);
                         if (wave_live) {
-                            f32x16 uA, vA, uB, vB;
-                            mma5_tile_part<P>(part, nparts, (const float *)(lds + buf * CV), lane, a3, b3, a4, b4,
-                                              uA, vA, uB, vB);
-                            mma5_fold_main<P>(t, uA, vA, uB, vB, L2, au, av);
+                            f32x16 dA, dB;
+                            tile(lds + buf * CV, bA, bB, dA, dB);
+                            mma5_fold_main<P>(t, dA, dB, L2, au);
+                            tile(lds + buf * CV + TV, bA, bB, dA, dB);
+                            mma5_fold_main<P>(t, dA, dB, L2, av);
                         }
                         mma_stage_wait();
                         __syncthreads();
@@ -373,10 +334,11 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
                 for (int t = 0; t < R; ++t) {
                     stage_next(P * A + t);
                     if (wave_live) {
-                        f32x16 uA, vA, uB, vB;
-                        mma5_tile_part<P>(part, nparts, (const float *)(lds + buf * CV), lane, a3, b3, a4, b4, uA, vA,
-                                          uB, vB);
-                        mma5_fold_rem<P>(t, uA, vA, uB, vB, L0, L1, L2, u, v);
+                        f32x16 dA, dB;
+                        tile(lds + buf * CV, bA, bB, dA, dB);
+                        mma5_fold_rem<P>(t, dA, dB, L0, L1, L2, u);
+                        tile(lds + buf * CV + TV, bA, bB, dA, dB);
+                        mma5_fold_rem<P>(t, dA, dB, L0, L1, L2, v);
                     }
                     mma_stage_wait();
                     __syncthreads();
@@ -394,6 +356,8 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
                     v += s_red[1][k][lane];
                 }
             }
+            u *= iu;
+            v *= iv;
             if (alive) {   // residual at X_q, time tau_q = t_{n,l} - q Delta
                 const float r = f_of<float>(a.phys, u) + source_space<float, 5>(a.phys, X, s_tf[tslot]) + v;
                 const float y = delta * r;

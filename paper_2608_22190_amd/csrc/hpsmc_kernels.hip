@@ -317,9 +317,9 @@ constexpr int kSlabQ = 32;
 // 2^-23 of an entry, or 2^-39 of the largest where that is more).  Exponents
 // are kept to what the inverse scale holds in FP32; non-finite coefficients
 // pass through as such.
-__global__ void __launch_bounds__(256) coef_scale_kernel(SlabArgs a)
+__global__ void __launch_bounds__(1024) coef_scale_kernel(SlabArgs a)
 {
-    __shared__ double sm[256];
+    __shared__ double sm[1024];
     const int blk = blockIdx.x, g = a.blk_group[blk], tid = threadIdx.x;
     const int T1 = a.deg[g] + 1;
     const int64_t n = (int64_t)a.rows * a.P;
@@ -334,7 +334,7 @@ __global__ void __launch_bounds__(256) coef_scale_kernel(SlabArgs a)
         }
         sm[tid] = mx;
         __syncthreads();
-        for (int o = 128; o > 0; o >>= 1) {
+        for (int o = blockDim.x / 2; o > 0; o >>= 1) {
             if (tid < o) sm[tid] = fmax(sm[tid], sm[tid + o]);
             __syncthreads();
         }
@@ -352,7 +352,7 @@ __global__ void __launch_bounds__(256) coef_scale_kernel(SlabArgs a)
 hipError_t launch_coef_scale(const SlabArgs &a, hipStream_t s)
 {
     if (a.n_blk <= 0) return hipSuccess;
-    hipLaunchKernelGGL(coef_scale_kernel, dim3((unsigned)a.n_blk), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(coef_scale_kernel, dim3((unsigned)a.n_blk), dim3(a.rows > 1024 ? 1024 : 256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -372,10 +372,10 @@ __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
     const double *cu = a.cu + a.coef_off[g], *cv = a.cv + a.coef_off[g];
     const double *cs = a.cs ? a.cs + a.cs_off[g] : nullptr;   // polynomial source, folded into v
     const double span = a.span[g], delta = a.delta[g], h2 = a.h2[g];
-    // matrix-core image of halves (layout 1, P >= 17): an entry is one coefficient, its
-    // two parts go to two places, and a lane pair trades parts for 4-byte stores
-    const bool split = mma && mma_split(a.P);
-    const int nb = mma_blocks(a.P);
+    // matrix-core images of halves: an entry is one coefficient, its two parts go to
+    // two places, and a lane pair trades parts for 4-byte stores
+    const bool split = mma5 || (mma && mma_split(a.P));
+    const int nb = mma5 ? g5.NB : mma_blocks(a.P);
     const double sc[2] = {split ? a.scale[2 * a.blk[g]] : 1.0, split ? a.scale[2 * a.blk[g] + 1] : 1.0};
     for (int q0 = blockIdx.x * kSlabQ; q0 < nq; q0 += gridDim.x * kSlabQ) {
         const int qn = min(kSlabQ, nq - q0);
@@ -395,9 +395,10 @@ __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
         for (int64_t e = threadIdx.x; e < stride; e += blockDim.x) {
             int64_t row = 0;
             int uv = 0, kl = 0;
+            int64_t off = 0;   // halves: the float of this pair's part 0
             bool live;
             if (mma5) {  // 32-row tiles over (k0, k1, k2), columns (k3, k4)
-                live = mma5_source(g5, e, uv, row, kl);
+                live = mma5_source(g5, e, uv, row, kl, off);
             } else {
                 if (mma && !split) {   // column c = uv * PP + k1 of kMmaRows rows k0
                     const int c = (int)(e / kMmaRows);
@@ -409,6 +410,7 @@ __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
                     const int c = (int)(e >> 8);
                     uv = c / nb;
                     kl = 8 * (c - uv * nb) + (int)(e & 7);
+                    off = (int64_t)(2 * uv * nb + (c - uv * nb)) * 128 + (e >> 1 & 127);
                 } else {
                     row = e / (2 * a.PP);
                     const int rem = (int)(e - row * 2 * a.PP);
@@ -436,9 +438,8 @@ __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
             }
             if (split) {
                 // even lanes store part 0 of the pair of modes, odd lanes part 1
-                const int part = (int)(e & 1), c = (int)(e >> 8);
-                uint32_t *dst = (uint32_t *)table + base + (int64_t)q0 * stride +
-                                (((uv * 2 + part) * nb + (c - uv * nb)) * 128 + (int)(e >> 1 & 127));
+                const int part = (int)(e & 1);
+                uint32_t *dst = (uint32_t *)table + base + (int64_t)q0 * stride + off + part * nb * 128;
                 const double f = uv ? sc[1] : sc[0];
 #pragma unroll
                 for (int j = 0; j < kSlabQ; ++j) {
