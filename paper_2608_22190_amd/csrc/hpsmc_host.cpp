@@ -399,7 +399,7 @@ struct hpsmc_plan {
     int64_t g0t_off = 0, d2t_off = 0, phi_off = 0, phit_off = 0;   // transposes and the phi collocation
     std::vector<int64_t> btt_off, d1t_off;
     // adjoint buffers (allocated on the first gradient call)
-    double *hist_u = nullptr, *hist_v = nullptr, *lam = nullptr, *cbar_u = nullptr, *cbar_v = nullptr;
+    double *hist_u = nullptr, *hist_v = nullptr, *lam = nullptr, *cbar_u = nullptr, *cbar_v = nullptr, *cbar_part = nullptr;
     double *dtarget = nullptr, *dloss = nullptr, *dgrad = nullptr;
     void *slab_bar = nullptr;
     int32_t adj_use_mfma = 1;
@@ -1571,7 +1571,7 @@ void hpsmc_destroy(hpsmc_plan *plan)
         for (auto &e : *pool) { (void)hipEventDestroy(e.a); (void)hipEventDestroy(e.b); }
     void *ptrs[] = {plan->U, plan->cu, plan->cv, plan->tmp0, plan->tmp1, plan->ic, plan->mats,
                     plan->slab_table, plan->part, plan->counters, plan->maxbits, plan->hist_u, plan->hist_v,
-                    plan->lam, plan->cbar_u, plan->cbar_v, plan->dtarget, plan->dloss, plan->dgrad, plan->slab_bar,
+                    plan->lam, plan->cbar_u, plan->cbar_v, plan->cbar_part, plan->dtarget, plan->dloss, plan->dgrad, plan->slab_bar,
                     plan->frac_tab, plan->src_poly, plan->cu_ch, plan->cv_ch, plan->cs_ch, plan->share_sum, plan->lat_table};
     for (void *p : ptrs) dfree(plan, p);
     delete plan;
@@ -2862,6 +2862,7 @@ hpsmc_status hpsmc_loss_grad_c0(hpsmc_plan *plan, const double *target, double *
     const int64_t I = plan->n_inst, nsp = plan->nsp, psp = plan->psp;
     const int64_t usz = I * nsp * T1, csz = I * psp * T1;
     NodeSet &set = plan->sets[0];
+    const int shares = slab_adjoint_shares(set.slab, plan->degree[0], (int)I, set.max_nstar, plan->cus);
     hpsmc_status st;
     if (!plan->lam) {
         if ((st = dalloc(plan, (void **)&plan->hist_u, (size_t)K * csz * 8)) ||
@@ -2869,6 +2870,7 @@ hpsmc_status hpsmc_loss_grad_c0(hpsmc_plan *plan, const double *target, double *
             (st = dalloc(plan, (void **)&plan->lam, (size_t)usz * 8)) ||
             (st = dalloc(plan, (void **)&plan->cbar_u, (size_t)csz * 8)) ||
             (st = dalloc(plan, (void **)&plan->cbar_v, (size_t)csz * 8)) ||
+            (shares > 1 && (st = dalloc(plan, (void **)&plan->cbar_part, (size_t)shares * 2 * csz * 8))) ||
             (st = dalloc(plan, (void **)&plan->dtarget, (size_t)I * nsp * 8)) ||
             (st = dalloc(plan, (void **)&plan->dloss, (size_t)I * 8)) ||
             (st = dalloc(plan, (void **)&plan->dgrad, (size_t)I * nsp * 8)) ||
@@ -2901,7 +2903,8 @@ hpsmc_status hpsmc_loss_grad_c0(hpsmc_plan *plan, const double *target, double *
         if ((st = adjoint_sampling(plan, set, plan->pb.fresh_per_iter ? k : 0, s))) return st;
         SlabArgs sb = set.slab;
         sb.slab_table = plan->slab_bar;
-        HIP_TRY(launch_slab_adjoint(sb, plan->degree[0], (int)I, plan->fp32, plan->cbar_u, plan->cbar_v, psp * T1, s));
+        HIP_TRY(launch_slab_adjoint(sb, plan->degree[0], (int)I, plan->fp32, plan->cbar_u, plan->cbar_v, psp * T1,
+                                    plan->cbar_part ? shares : 1, plan->cbar_part, s));
         // cbar_u += (c^u -> c^v)^T cbar_v
         for (int i = 0; i < d; ++i)
             HIP_TRY(launch_mode_product(plan->cbar_v, plan->cbar_u, I * ipow(P, i), P, P, ipow(P, d - 1 - i) * T1,

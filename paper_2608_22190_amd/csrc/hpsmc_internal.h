@@ -298,7 +298,8 @@ size_t adjoint_mma2_lds_bytes(int P, int nthr);
 // that its registers spill; larger P keep u* on the vector units)
 constexpr int kAdjMma2MaxKH = 10;
 hipError_t launch_slab_adjoint(const SlabArgs &a, int32_t groups_per_inst, int32_t n_inst, int fp32, double *cbar_u,
-                               double *cbar_v, int64_t coef_inst_stride, hipStream_t s);
+                               double *cbar_v, int64_t coef_inst_stride, int32_t shares, double *part, hipStream_t s);
+int slab_adjoint_shares(const SlabArgs &a, int32_t groups_per_inst, int32_t n_inst, int max_nstar, int cus);
 hipError_t launch_loss_lambda(const double *U, const double *target, int n_inst, int64_t nsp, int T1, double *lambda,
                               double *loss, hipStream_t s);
 hipError_t launch_column_sum(const double *lambda, int64_t rows, int T1, double *out, hipStream_t s);

@@ -909,18 +909,23 @@ hipError_t launch_slice_reduce(const double *result, int64_t n_nodes, int64_t mc
 // instance: one coalesced 1 KiB row per step, a chunk of kSlabQ steps' loads
 // in flight per thread (a half or a quarter of it past degree 15), the Legendre values of
 // those steps in LDS (computed once per block, one row per degree with the
-// steps contiguous).  Each entry's sums run over (l, q) in order, with the
-// recurrence of the slab kernel.  The degree loop has a fixed trip count T1P
+// steps contiguous).  Few instances give few blocks, so the chunks of an instance's
+// groups are split into shares: each block sums one share of them in order into a
+// partial tensor, and adjoint_shares_kernel adds those in share order (eight
+// instances at d = 2, P = 18, 12 groups: 24 blocks took 10.5 ms, 768 take 0.47).  Each
+// entry's sums run over (l, q) in order within a share, with the recurrence of the slab
+// kernel.  The degree loop has a fixed trip count T1P
 // (T1 rounded up to a multiple of 4): the degrees past T1 sum finite values
 // that are never stored, and steps past a chunk's end meet zero Legendre rows.
 template <typename T, int T1P>
 __device__ __forceinline__ void slab_adjoint_body(const SlabArgs &a, int32_t groups_per_inst, double *cbar_u,
-                                                  double *cbar_v, int64_t coef_inst_stride,
-                                                  double (*Lt)[kSlabQ])
+                                                  double *cbar_v, int64_t coef_inst_stride, int32_t shares,
+                                                  int64_t share_stride, double (*Lt)[kSlabQ])
 {
     constexpr int QB = T1P <= 16 ? kSlabQ : T1P <= 20 ? kSlabQ / 2 : kSlabQ / 4;   // loads in flight per thread
     const int inst = blockIdx.z * kGridYZ + blockIdx.y;   // instances over y and z (y at most 65535)
-    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t share = blockIdx.x % shares;
+    const int64_t e = blockIdx.x / shares * (int64_t)blockDim.x + threadIdx.x;
     const int64_t row = e / (2 * a.PP);
     const int rem = (int)(e - row * 2 * a.PP), uv = rem / a.PP, kl = rem - uv * a.PP;
     const bool live = e < a.slab_stride && kl < a.P;
@@ -929,12 +934,18 @@ __device__ __forceinline__ void slab_adjoint_body(const SlabArgs &a, int32_t gro
     double acc[T1P];
 #pragma unroll
     for (int m = 0; m < T1P; ++m) acc[m] = 0.0;
+    int64_t total = 0, c0 = 0;   // chunks of the instance, and of the groups before gl
+    for (int gl = 0; gl < groups_per_inst; ++gl) total += (a.nstar[inst * groups_per_inst + gl] + kSlabQ - 1) / kSlabQ;
+    const int64_t lo = total * share / shares, hi = total * (share + 1) / shares;
     for (int gl = 0; gl < groups_per_inst; ++gl) {
         const int g = inst * groups_per_inst + gl;
         const int nstar = a.nstar[g];
+        const int64_t nc = (nstar + kSlabQ - 1) / kSlabQ;
+        const int first = (int)(min(max(lo - c0, (int64_t)0), nc) * kSlabQ), last = min((int)(max(min(hi - c0, nc), (int64_t)0) * kSlabQ), nstar);
+        c0 += nc;
         const double span = a.span[g], delta = a.delta[g], h2 = a.h2[g];
         const T *src = tab + a.slab_off[g] + (live ? e : 0);
-        for (int q0 = 0; q0 < nstar; q0 += kSlabQ) {
+        for (int q0 = first; q0 < last; q0 += kSlabQ) {
             const int qn = min(kSlabQ, nstar - q0);
             __syncthreads();   // the previous chunk's reads of Lt are over
             if ((int)threadIdx.x < kSlabQ) {
@@ -972,7 +983,7 @@ __device__ __forceinline__ void slab_adjoint_body(const SlabArgs &a, int32_t gro
         }
     }
     if (!live) return;
-    double *out = (uv ? cbar_v : cbar_u) + (int64_t)inst * coef_inst_stride + (row * a.P + kl) * T1;
+    double *out = (uv ? cbar_v : cbar_u) + share * share_stride + (int64_t)inst * coef_inst_stride + (row * a.P + kl) * T1;
 #pragma unroll
     for (int m = 0; m < T1P; ++m)
         if (m < T1) out[m] = acc[m];
@@ -982,32 +993,56 @@ template <typename T>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 slab_adjoint_kernel(SlabArgs a, int32_t groups_per_inst, int32_t n_inst,
                                                            double *__restrict__ cbar_u, double *__restrict__ cbar_v,
-                                                           int64_t coef_inst_stride)
+                                                           int64_t coef_inst_stride, int32_t shares, int64_t share_stride)
 {
     __shared__ __align__(16) double Lt[kMaxDeg + 1][kSlabQ];
     if ((int)(blockIdx.z * kGridYZ + blockIdx.y) >= n_inst) return;
     switch ((a.deg[(blockIdx.z * kGridYZ + blockIdx.y) * groups_per_inst] + 4) >> 2) {   // ceil(T1 / 4), T1 <= 32
-    case 1: slab_adjoint_body<T, 4>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, Lt); break;
-    case 2: slab_adjoint_body<T, 8>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, Lt); break;
-    case 3: slab_adjoint_body<T, 12>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, Lt); break;
-    case 4: slab_adjoint_body<T, 16>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, Lt); break;
-    case 5: slab_adjoint_body<T, 20>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, Lt); break;
-    case 6: slab_adjoint_body<T, 24>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, Lt); break;
-    case 7: slab_adjoint_body<T, 28>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, Lt); break;
-    default: slab_adjoint_body<T, 32>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, Lt); break;
+    case 1: slab_adjoint_body<T, 4>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, shares, share_stride, Lt); break;
+    case 2: slab_adjoint_body<T, 8>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, shares, share_stride, Lt); break;
+    case 3: slab_adjoint_body<T, 12>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, shares, share_stride, Lt); break;
+    case 4: slab_adjoint_body<T, 16>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, shares, share_stride, Lt); break;
+    case 5: slab_adjoint_body<T, 20>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, shares, share_stride, Lt); break;
+    case 6: slab_adjoint_body<T, 24>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, shares, share_stride, Lt); break;
+    case 7: slab_adjoint_body<T, 28>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, shares, share_stride, Lt); break;
+    default: slab_adjoint_body<T, 32>(a, groups_per_inst, cbar_u, cbar_v, coef_inst_stride, shares, share_stride, Lt); break;
     }
 }
 
+// out = the partial tensors added in share order
+__global__ void __launch_bounds__(256) adjoint_shares_kernel(const double *__restrict__ part, int32_t shares, int64_t n,
+                                                             double *__restrict__ cbar_u, double *__restrict__ cbar_v)
+{
+    for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < 2 * n; i += (int64_t)gridDim.x * 256) {
+        double sum = part[i];
+        for (int k = 1; k < shares; ++k) sum += part[i + k * 2 * n];
+        (i < n ? cbar_u[i] : cbar_v[i - n]) = sum;
+    }
+}
+
+// shares: enough for three resident blocks on each compute unit, of at least eight chunks
+int slab_adjoint_shares(const SlabArgs &a, int32_t groups_per_inst, int32_t n_inst, int max_nstar, int cus)
+{
+    const int64_t blocks = (a.slab_stride + 255) / 256 * n_inst;
+    const int64_t chunks = (int64_t)groups_per_inst * ((max_nstar + kSlabQ - 1) / kSlabQ);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(std::min(3 * cus / blocks, chunks / 8), 64));
+}
+
+// part: shares x 2 x n_inst x coef_inst_stride doubles (not read or written with one share)
 hipError_t launch_slab_adjoint(const SlabArgs &a, int32_t groups_per_inst, int32_t n_inst, int fp32, double *cbar_u,
-                               double *cbar_v, int64_t coef_inst_stride, hipStream_t s)
+                               double *cbar_v, int64_t coef_inst_stride, int32_t shares, double *part, hipStream_t s)
 {
     if (n_inst <= 0) return hipSuccess;
-    dim3 grid((unsigned)((a.slab_stride + 255) / 256), (unsigned)std::min<int32_t>(n_inst, kGridYZ),
+    dim3 grid((unsigned)((a.slab_stride + 255) / 256 * shares), (unsigned)std::min<int32_t>(n_inst, kGridYZ),
               (unsigned)((n_inst + kGridYZ - 1) / kGridYZ)), block(256);
+    const int64_t n = n_inst * coef_inst_stride;
+    double *u = shares > 1 ? part : cbar_u, *v = shares > 1 ? part + n : cbar_v;
     if (fp32)
-        hipLaunchKernelGGL(slab_adjoint_kernel<float>, grid, block, 0, s, a, groups_per_inst, n_inst, cbar_u, cbar_v, coef_inst_stride);
+        hipLaunchKernelGGL(slab_adjoint_kernel<float>, grid, block, 0, s, a, groups_per_inst, n_inst, u, v, coef_inst_stride, shares, 2 * n);
     else
-        hipLaunchKernelGGL(slab_adjoint_kernel<double>, grid, block, 0, s, a, groups_per_inst, n_inst, cbar_u, cbar_v, coef_inst_stride);
+        hipLaunchKernelGGL(slab_adjoint_kernel<double>, grid, block, 0, s, a, groups_per_inst, n_inst, u, v, coef_inst_stride, shares, 2 * n);
+    if (shares > 1)
+        hipLaunchKernelGGL(adjoint_shares_kernel, dim3(grid_blocks(2 * n, 256)), block, 0, s, part, shares, n, cbar_u, cbar_v);
     return hipGetLastError();
 }
 
