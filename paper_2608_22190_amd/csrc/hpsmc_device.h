@@ -869,7 +869,7 @@ __device__ __forceinline__ void mma_stage_wait() { asm volatile("s_waitcnt vmcnt
 // a1 and b = b0 + b1 (each part rounded to nearest: 23 bits together), and all
 // four partial products run on v_mfma_f32_32x32x16_f16 with FP32 accumulation.
 // The tables are scaled by a power of two so that their largest entry has
-// magnitude 2^13..2^14 (coef_scale_kernel) and the basis values by 2^10, so no
+// magnitude 2^13..2^14 (coef_pack_kernel) and the basis values by 2^10, so no
 // part that matters is subnormal.  An FP32 product (32x32x2, 64 cycles for two
 // modes) was what bounded the kernel, and it does not overlap with the vector
 // work of other waves; the four half-precision products take 32 cycles for

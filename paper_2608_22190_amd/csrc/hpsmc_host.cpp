@@ -329,6 +329,7 @@ struct NodeSet {               // the nodes one sampling launch covers
     int32_t n_groups = 0, max_nstar = 0;
     int64_t slab_elems = 0;
     int64_t slab_elems_row = 0;   // the row layout's extent (the slab adjoint's table)
+    double *pack = nullptr;    // scaled coefficients in the order of the matrix-core images, and their scales
     void *group_mem = nullptr; // coef_off, slab_off, span, delta, h2, nstar, deg
     SlabArgs slab{};
     // outputs (canonical order)
@@ -778,7 +779,7 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     if ((st = dalloc(plan, (void **)&set.dev, sizeof(NodeDesc) * set.n))) return st;
     const size_t G = set.n_groups;
     const size_t NBLK = blk_group.size();
-    const size_t gbytes = G * (4 * sizeof(int64_t) + 3 * sizeof(double) + 4 * sizeof(int32_t)) + NBLK * 32;
+    const size_t gbytes = G * (4 * sizeof(int64_t) + 3 * sizeof(double) + 4 * sizeof(int32_t)) + NBLK * 16;
     if ((st = dalloc(plan, &set.group_mem, gbytes))) return st;
     std::vector<char> gh(gbytes);
     char *p = gh.data();
@@ -790,7 +791,7 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     put(src_goff.data(), G * 8);
     put(blk.data(), G * 4);
     p += G * 4;            // keeps the scales aligned
-    p += NBLK * 24;        // scale, inv_scale: written on the device
+    p += NBLK * 8;         // inv_scale: written on the device
     put(blk_group.data(), NBLK * 4);
     if (hipMemcpy(set.group_mem, gh.data(), gbytes, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(set.dev, set.host.data(), sizeof(NodeDesc) * set.n, hipMemcpyHostToDevice) != hipSuccess)
@@ -810,9 +811,8 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     sa.cs = plan->src_poly;
     sa.cs_off = (const int64_t *)(gb + G * 56);
     sa.blk = (const int32_t *)(gb + G * 64);
-    sa.scale = (double *)(gb + G * 72);
-    sa.inv_scale = (float *)(gb + G * 72 + NBLK * 16);
-    sa.blk_group = (const int32_t *)(gb + G * 72 + NBLK * 24);
+    sa.inv_scale = (float *)(gb + G * 72);
+    sa.blk_group = (const int32_t *)(gb + G * 72 + NBLK * 8);
     sa.n_blk = (int32_t)NBLK;
     sa.bscale = d == 2 ? mma_basis_scale(plan) : 1024.0;   // 5-D: |L_k| <= 1 in the domain
     sa.mma_stride = mstride;
@@ -823,6 +823,14 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     sa.PP = plan->PP;
     sa.rows = (int32_t)rows;
     sa.slab_stride = stride;
+    if (mma_ok && (d == 5 || mma_split(plan->P))) {
+        sa.scale_parts = (int32_t)std::min<int64_t>(64, (rows * plan->P + 4095) / 4096);
+        sa.pack_t = *std::max_element(deg.begin(), deg.end()) + 1;
+        const size_t pk = NBLK * sa.pack_t * mstride;
+        if ((st = dalloc(plan, (void **)&set.pack, (pk + NBLK * 2 * sa.scale_parts) * 8))) return st;
+        sa.pack = set.pack;
+        sa.scale_max = set.pack + pk;
+    }
     if ((st = dalloc(plan, (void **)&set.eps, sizeof(double) * set.n))) return st;
     if ((st = dalloc(plan, (void **)&set.sumsq, sizeof(double) * set.n))) return st;
     if (plan->pb.accel == HPSMC_ACCEL_AITKEN) {
@@ -934,7 +942,7 @@ static hpsmc_status build_lattice(hpsmc_plan *plan, NodeSet &set)
 
 static void free_set(const hpsmc_plan *plan, NodeSet &s)
 {
-    for (void *p : {(void *)s.dev, s.group_mem, (void *)s.eps, (void *)s.sumsq, (void *)s.probe, (void *)s.gdev,
+    for (void *p : {(void *)s.dev, (void *)s.pack, s.group_mem, (void *)s.eps, (void *)s.sumsq, (void *)s.probe, (void *)s.gdev,
                     s.state[0], s.state[1], (void *)s.live, (void *)s.prefix, (void *)s.result, (void *)s.vbeg,
                     (void *)s.ait, s.lat_mem})
         dfree(plan, p);
@@ -1464,7 +1472,7 @@ static hpsmc_status slab_args_for(hpsmc_plan *plan, const NodeSet &set, int layo
     sa = set.slab;
     sa.slab_table = plan->slab_table;
     sa.layout = layout;
-    if (layout == 2) HIP_TRY(launch_coef_scale(sa, s));
+    if (layout == 2) HIP_TRY(launch_coef_pack(sa, s));
     if (layout != 1 && !(cheb && layout == 0)) return HPSMC_OK;
     if (!plan->cu_ch) return fail(HPSMC_EINVAL, "no Chebyshev coefficient buffers for this slab layout");
     for (int32_t iv : set.ivs) {
@@ -1477,7 +1485,7 @@ static hpsmc_status slab_args_for(hpsmc_plan *plan, const NodeSet &set, int layo
     sa.cu = plan->cu_ch;
     sa.cv = plan->cv_ch;
     if (sa.cs) sa.cs = plan->cs_ch;
-    if (layout == 1 && mma_split(plan->P)) HIP_TRY(launch_coef_scale(sa, s));
+    if (layout == 1 && mma_split(plan->P)) HIP_TRY(launch_coef_pack(sa, s));
     return HPSMC_OK;
 }
 

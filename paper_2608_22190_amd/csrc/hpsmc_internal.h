@@ -156,8 +156,11 @@ struct SlabArgs {
     const int32_t *blk;          // per group: its coefficient block
     const int32_t *blk_group;    // per coefficient block: its first group
     int32_t n_blk;
-    double *scale;               // [blk][u, v] power of two that the image's coefficients are multiplied by
+    double *scale_max;           // [blk][u, v][scale_parts] largest entries over the parts of the block
+    int32_t scale_parts;
     float *inv_scale;            // [blk][u, v] 1 / (scale bscale)
+    double *pack;                // images of halves: [blk][pack_t][mma_stride] scaled coefficients in image order
+    int32_t pack_t;              // most time coefficients of a block
     double bscale;
     int32_t layout;              // 0: rows [k0][u: PP][v: PP]; 1: matrix-core layout
     int32_t extra;               // slabs past N* per group (1 for the Picard form: q = N*, t_{n-1})
@@ -177,7 +180,7 @@ hipError_t launch_mode_product(const double *in, double *out, int64_t outer, int
                                int64_t inner, const double *mat, double alpha, int accumulate,
                                hipStream_t s);
 hipError_t launch_slabs(const SlabArgs &a, int fp32, int max_nstar, hipStream_t s);
-hipError_t launch_coef_scale(const SlabArgs &a, hipStream_t s);
+hipError_t launch_coef_pack(const SlabArgs &a, hipStream_t s);
 hipError_t launch_sample(const SampleArgs &a, int fp32, int samples_per_lane, int waves_per_block,
                          int blocks, hipStream_t s);
 hipError_t launch_reduce_update(const double *part, int chunks, int mode, const NodeDesc *nodes, int64_t n_nodes,
@@ -257,16 +260,14 @@ constexpr Mma5Geom mma5_geom(int P)
 }
 // Entry e of a step (one coefficient, [chunk][table][block][row][mode of the block]):
 // false for padding, else its table (0 u, 1 v), the flat index row4 = ((k0 P + k1) P +
-// k2) P + k3 of the first four modes, and k4.  off: the float of the image that holds
-// part 0 of it and its neighbour (part 1: 128 NB floats on).
-__host__ __device__ inline bool mma5_source(const Mma5Geom &g, int64_t e, int &uv, int64_t &row4, int &k4, int64_t &off)
+// k2) P + k3 of the first four modes, and k4. 
+__host__ __device__ inline bool mma5_source(const Mma5Geom &g, int64_t e, int &uv, int64_t &row4, int &k4)
 {
     const int c = (int)(e / g.chunk);
     int r = (int)(e - (int64_t)c * g.chunk);
     uv = r / (256 * g.NB);
     r -= uv * 256 * g.NB;
     const int i = (r >> 3) & 31, mode = 8 * (r >> 8) + (r & 7);
-    off = (int64_t)c * g.chunk + (int64_t)uv * 256 * g.NB + (r >> 1);
     if (mode >= g.P * g.P) return false;
     const int k3 = mode / g.P;
     k4 = mode - k3 * g.P;

@@ -309,50 +309,92 @@ hipError_t launch_mode_product(const double *in, double *out, int64_t outer, int
 // ---------------------------------------------------------------------------
 constexpr int kSlabQ = 32;
 
-// Power-of-two scale of the coefficient tables whose image holds two
-// half-precision parts: one block per coefficient block (interval, instance)
-// bounds every entry at every time by the sum of its time coefficients'
-// magnitudes (|L_q| <= 1) and scales the largest into [2^13, 2^14), so a part
-// loses no bits to the narrow exponent range (the parts' rounding is then
-// 2^-23 of an entry, or 2^-39 of the largest where that is more).  Exponents
-// are kept to what the inverse scale holds in FP32; non-finite coefficients
-// pass through as such.
-__global__ void __launch_bounds__(1024) coef_scale_kernel(SlabArgs a)
+// Coefficients of the matrix-core images of halves, before the time contraction: scaled
+// by a power of two, with the polynomial source folded in, and in the order of the image
+// (zeros where it is padded), so that the contraction reads them coalesced.  The scale
+// of a coefficient block (interval, instance) and table: coef_max_kernel bounds every
+// entry at every time by the sum of its time coefficients' magnitudes (|L_q| <= 1) and
+// coef_pack_kernel scales the largest into [2^13, 2^14), so a part loses no bits to the
+// narrow exponent range (the parts' rounding is then 2^-23 of an entry, or 2^-39 of the
+// largest where that is more).  Exponents are kept to what the inverse scale holds in
+// FP32; non-finite coefficients pass through as such.
+__global__ void __launch_bounds__(256) coef_max_kernel(SlabArgs a)
 {
-    __shared__ double sm[1024];
-    const int blk = blockIdx.x, g = a.blk_group[blk], tid = threadIdx.x;
-    const int T1 = a.deg[g] + 1;
-    const int64_t n = (int64_t)a.rows * a.P;
-    for (int uv = 0; uv < 2; ++uv) {
-        const double *c = (uv ? a.cv : a.cu) + a.coef_off[g];
-        const double *cs = uv && a.cs ? a.cs + a.cs_off[g] : nullptr;
+    __shared__ double sm[4];
+    const int blk = blockIdx.x / a.scale_parts, part = blockIdx.x - blk * a.scale_parts, uv = blockIdx.y;
+    const int g = a.blk_group[blk], T1 = a.deg[g] + 1;
+    const int64_t n = (int64_t)a.rows * a.P, e1 = n * (part + 1) / a.scale_parts;
+    const double *c = (uv ? a.cv : a.cu) + a.coef_off[g];
+    const double *cs = uv && a.cs ? a.cs + a.cs_off[g] : nullptr;
+    double mx = 0.0;
+    for (int64_t e = n * part / a.scale_parts + threadIdx.x; e < e1; e += 256) {
+        double sum = 0.0;
+        for (int k = 0; k < T1; ++k) sum += fabs(cs ? c[e * T1 + k] + cs[e * T1 + k] : c[e * T1 + k]);
+        mx = fmax(mx, sum);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        a.scale_max[(2 * blk + uv) * (int64_t)a.scale_parts + part] = fmax(fmax(sm[0], sm[1]), fmax(sm[2], sm[3]));
+}
+
+__global__ void __launch_bounds__(256) coef_pack_kernel(SlabArgs a, int blocks_per_blk)
+{
+    const int blk = blockIdx.x / blocks_per_blk, pairs = (int)(a.mma_stride / 2);
+    const int p = (blockIdx.x - blk * blocks_per_blk) * 256 + threadIdx.x;
+    if (p >= pairs) return;
+    const int g = a.blk_group[blk], T1 = a.deg[g] + 1;
+    int uv = 0;
+    int64_t at[2] = {0, 0};   // the pair's coefficients' flat indices
+    bool live[2];
+    const Mma5Geom g5 = mma5_geom(a.P);
+    const int nb = mma_blocks(a.P);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int e = 2 * p + i;
+        int64_t row = 0;
+        int kl = 0;
+        if (a.layout == 2) {   // 32-row tiles over (k0, k1, k2), columns (k3, k4)
+            live[i] = mma5_source(g5, e, uv, row, kl);
+        } else {               // [uv][block][row k0 < 32][mode of the block]
+            row = (e >> 3) & 31;
+            uv = (e >> 8) / nb;
+            kl = 8 * ((e >> 8) - uv * nb) + (e & 7);
+            live[i] = kl < a.P && row < a.rows;
+        }
+        if (live[i]) at[i] = (row * a.P + kl) * T1;
+    }
+    const auto exponent = [&](int t) {   // scale 2^(kMmaScaleExp - exponent)
+        const double *m = a.scale_max + (2 * blk + t) * (int64_t)a.scale_parts;
         double mx = 0.0;
-        for (int64_t e = tid; e < n; e += blockDim.x) {
-            double sum = 0.0;
-            for (int k = 0; k < T1; ++k) sum += fabs(cs ? c[e * T1 + k] + cs[e * T1 + k] : c[e * T1 + k]);
-            mx = fmax(mx, sum);
+        for (int i = 0; i < a.scale_parts; ++i) mx = fmax(mx, m[i]);
+        const int e = mx > 0.0 && mx < 1e300 ? ilogb(mx) + 1 : 0;
+        return max(-100, min(127, e));
+    };
+    if (p == 0)
+        for (int t = 0; t < 2; ++t) a.inv_scale[2 * blk + t] = (float)(ldexp(1.0, exponent(t) - kMmaScaleExp) / a.bscale);
+    const double sc = ldexp(1.0, kMmaScaleExp - exponent(uv));
+    const double *c = (uv ? a.cv : a.cu) + a.coef_off[g];
+    const double *cs = uv && a.cs ? a.cs + a.cs_off[g] : nullptr;
+    double2 *out = (double2 *)a.pack + (int64_t)blk * a.pack_t * pairs + p;
+    for (int k = 0; k < T1; ++k) {
+        double2 w = make_double2(c[at[0] + k], c[at[1] + k]);
+        if (cs) {
+            w.x += cs[at[0] + k];
+            w.y += cs[at[1] + k];
         }
-        sm[tid] = mx;
-        __syncthreads();
-        for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-            if (tid < o) sm[tid] = fmax(sm[tid], sm[tid + o]);
-            __syncthreads();
-        }
-        if (tid == 0) {
-            const double m = sm[0];
-            int e = m > 0.0 && m < 1e300 ? ilogb(m) + 1 : 0;
-            e = max(-100, min(127, e));
-            a.scale[2 * blk + uv] = ldexp(1.0, kMmaScaleExp - e);
-            a.inv_scale[2 * blk + uv] = (float)(ldexp(1.0, e - kMmaScaleExp) / a.bscale);
-        }
-        __syncthreads();
+        out[(int64_t)k * pairs] = make_double2(live[0] ? w.x * sc : 0.0, live[1] ? w.y * sc : 0.0);
     }
 }
 
-hipError_t launch_coef_scale(const SlabArgs &a, hipStream_t s)
+hipError_t launch_coef_pack(const SlabArgs &a, hipStream_t s)
 {
     if (a.n_blk <= 0) return hipSuccess;
-    hipLaunchKernelGGL(coef_scale_kernel, dim3((unsigned)a.n_blk), dim3(a.rows > 1024 ? 1024 : 256), 0, s, a);
+    const int64_t bpb = (a.mma_stride / 2 + 255) / 256;
+    hipLaunchKernelGGL(coef_max_kernel, dim3((unsigned)(a.n_blk * a.scale_parts), 2), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(coef_pack_kernel, dim3((unsigned)(a.n_blk * bpb)), dim3(256), 0, s, a, (int)bpb);
     return hipGetLastError();
 }
 
@@ -364,19 +406,13 @@ __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
     if (g >= a.n_groups) return;
     const int nq = a.nstar[g] + a.extra;
     const int T1 = a.deg[g] + 1;
-    const bool mma = a.layout == 1, mma5 = a.layout == 2;
-    const Mma5Geom g5 = mma5_geom(a.P);
+    const bool mma = a.layout == 1;
     const int64_t stride = a.layout ? a.mma_stride : a.slab_stride;
     const int64_t base = a.layout ? a.slab_off_mma[g] : a.slab_off[g];
     T *table = (T *)a.slab_table;
     const double *cu = a.cu + a.coef_off[g], *cv = a.cv + a.coef_off[g];
     const double *cs = a.cs ? a.cs + a.cs_off[g] : nullptr;   // polynomial source, folded into v
     const double span = a.span[g], delta = a.delta[g], h2 = a.h2[g];
-    // matrix-core images of halves: an entry is one coefficient, its two parts go to
-    // two places, and a lane pair trades parts for 4-byte stores
-    const bool split = mma5 || (mma && mma_split(a.P));
-    const int nb = mma5 ? g5.NB : mma_blocks(a.P);
-    const double sc[2] = {split ? a.scale[2 * a.blk[g]] : 1.0, split ? a.scale[2 * a.blk[g] + 1] : 1.0};
     for (int q0 = blockIdx.x * kSlabQ; q0 < nq; q0 += gridDim.x * kSlabQ) {
         const int qn = min(kSlabQ, nq - q0);
         __syncthreads();   // the previous chunk's reads of Lt are over
@@ -395,30 +431,18 @@ __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
         for (int64_t e = threadIdx.x; e < stride; e += blockDim.x) {
             int64_t row = 0;
             int uv = 0, kl = 0;
-            int64_t off = 0;   // halves: the float of this pair's part 0
-            bool live;
-            if (mma5) {  // 32-row tiles over (k0, k1, k2), columns (k3, k4)
-                live = mma5_source(g5, e, uv, row, kl, off);
+            if (mma) {   // column c = uv * PP + k1 of kMmaRows rows k0
+                const int c = (int)(e / kMmaRows);
+                row = e - (int64_t)c * kMmaRows;
+                uv = c / a.PP;
+                kl = c - uv * a.PP;
             } else {
-                if (mma && !split) {   // column c = uv * PP + k1 of kMmaRows rows k0
-                    const int c = (int)(e / kMmaRows);
-                    row = e - (int64_t)c * kMmaRows;
-                    uv = c / a.PP;
-                    kl = c - uv * a.PP;
-                } else if (mma) {   // [uv][block][row k0 < 32][mode of the block]
-                    row = (e >> 3) & 31;
-                    const int c = (int)(e >> 8);
-                    uv = c / nb;
-                    kl = 8 * (c - uv * nb) + (int)(e & 7);
-                    off = (int64_t)(2 * uv * nb + (c - uv * nb)) * 128 + (e >> 1 & 127);
-                } else {
-                    row = e / (2 * a.PP);
-                    const int rem = (int)(e - row * 2 * a.PP);
-                    uv = rem / a.PP;
-                    kl = rem - uv * a.PP;
-                }
-                live = kl < a.P && row < a.rows;
+                row = e / (2 * a.PP);
+                const int rem = (int)(e - row * 2 * a.PP);
+                uv = rem / a.PP;
+                kl = rem - uv * a.PP;
             }
+            const bool live = kl < a.P && row < a.rows;
             double acc[kSlabQ];
 #pragma unroll
             for (int j = 0; j < kSlabQ; ++j) acc[j] = 0.0;
@@ -436,26 +460,80 @@ __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
                     }
                 }
             }
-            if (split) {
-                // even lanes store part 0 of the pair of modes, odd lanes part 1
-                const int part = (int)(e & 1);
-                uint32_t *dst = (uint32_t *)table + base + (int64_t)q0 * stride + off + part * nb * 128;
-                const double f = uv ? sc[1] : sc[0];
+            T *dst = table + base + (int64_t)q0 * stride + e;
 #pragma unroll
-                for (int j = 0; j < kSlabQ; ++j) {
-                    const double v = acc[j] * f;
-                    const _Float16 h = (_Float16)(float)v;
-                    const _Float16 l = (_Float16)(float)(v - (double)(float)h);
-                    const uint32_t w = (uint32_t)__builtin_bit_cast(uint16_t, h) |
-                                       (uint32_t)__builtin_bit_cast(uint16_t, l) << 16;
-                    const uint32_t o = (uint32_t)__shfl_xor((int)w, 1, 64);
-                    if (j < qn) dst[(int64_t)j * stride] = part ? o >> 16 | (w & 0xffff0000u) : (w & 0xffffu) | o << 16;
+            for (int j = 0; j < kSlabQ; ++j)
+                if (j < qn) dst[(int64_t)j * stride] = (T)acc[j];
+        }
+    }
+}
+
+// The same for the matrix-core images of halves, from the packed coefficients: a thread
+// takes two neighbouring modes, whose two parts are one 4-byte store each, and kSplitQ
+// steps, so the Legendre values read from LDS serve two sums and the stores of a wave
+// are 256 contiguous bytes.  The work is split over entries too (kSplitPairs to a block):
+// five dimensions have few groups and 10^5 entries a step.  Bound by the table's writes:
+// 2.6 TB/s at d = 5, n = 8, eight groups, and 3.6 at d = 2, n = 16, 96 groups (1.1 and 2.1
+// where a thread took one coefficient, read from the tensors with a stride of T1, and a
+// block 32 steps of all entries).
+constexpr int kSplitQ = 16, kSplitPairs = 2048;
+
+__global__ void __launch_bounds__(256) slab_split_kernel(SlabArgs a, int parts)
+{
+    __shared__ __align__(16) double Lt[kMaxDeg + 1][kSplitQ];
+    const int g = blockIdx.z * kGridYZ + blockIdx.y;
+    if (g >= a.n_groups) return;
+    const int nq = a.nstar[g] + a.extra, chunks = gridDim.x / parts;
+    const int T1 = a.deg[g] + 1;
+    const int part = blockIdx.x / chunks, chunk = blockIdx.x - part * chunks;   // chunks sharing entries run together
+    const int pairs = (int)(a.mma_stride / 2), p0 = part * kSplitPairs, p1 = min(pairs, p0 + kSplitPairs);
+    const int table_pairs = 128 * (a.layout == 2 ? mma5_geom(a.P).NB : mma_blocks(a.P));
+    uint32_t *table = (uint32_t *)a.slab_table + a.slab_off_mma[g];
+    const double2 *pack = (const double2 *)a.pack + (int64_t)a.blk[g] * a.pack_t * pairs;
+    const double span = a.span[g], delta = a.delta[g], h2 = a.h2[g];
+    const float m1 = opaque_minus_one();
+    for (int q0 = chunk * kSplitQ; q0 < nq; q0 += chunks * kSplitQ) {
+        const int qn = min(kSplitQ, nq - q0);
+        __syncthreads();   // the previous chunk's reads of Lt are over
+        if ((int)threadIdx.x < kSplitQ) {
+            const double xi = h2 * (span - (double)(q0 + (int)threadIdx.x) * delta) - 1.0;
+            double lp = 0.0, lc = 1.0;
+            for (int k = 0; k < T1; ++k) {
+                Lt[k][threadIdx.x] = lc;   // steps past the chunk's end: never stored
+                const double nx = c_rec.ad[k] * xi * lc - c_rec.bd[k] * lp;
+                lp = lc;
+                lc = nx;
+            }
+        }
+        __syncthreads();
+        for (int p = p0 + threadIdx.x; p < p1; p += 256) {
+            double acc[2][kSplitQ];
+#pragma unroll
+            for (int j = 0; j < kSplitQ; ++j) acc[0][j] = acc[1][j] = 0.0;
+#pragma unroll 2
+            for (int k = 0; k < T1; ++k) {
+                const double2 c = pack[(int64_t)k * pairs + p];
+                const double2 *lk = (const double2 *)Lt[k];
+#pragma unroll
+                for (int j = 0; j < kSplitQ / 2; ++j) {
+                    const double2 l2 = lk[j];
+                    acc[0][2 * j] = fma(c.x, l2.x, acc[0][2 * j]);
+                    acc[0][2 * j + 1] = fma(c.x, l2.y, acc[0][2 * j + 1]);
+                    acc[1][2 * j] = fma(c.y, l2.x, acc[1][2 * j]);
+                    acc[1][2 * j + 1] = fma(c.y, l2.y, acc[1][2 * j + 1]);
                 }
-            } else {
-                T *dst = table + base + (int64_t)q0 * stride + e;
+            }
+            // part 0 of the pair in its table's image, part 1 table_pairs floats on
+            const uint32_t o0 = (uint32_t)(p + p / table_pairs * table_pairs), o1 = o0 + table_pairs;
 #pragma unroll
-                for (int j = 0; j < kSlabQ; ++j)
-                    if (j < qn) dst[(int64_t)j * stride] = (T)acc[j];
+            for (int j = 0; j < kSplitQ; ++j) {
+                if (j < qn) {
+                    uint32_t *dst = table + (int64_t)(q0 + j) * a.mma_stride;
+                    const float v0 = (float)acc[0][j], v1 = (float)acc[1][j];
+                    const uint32_t h = pack_h16(v0, v1);
+                    dst[o0] = h;
+                    dst[o1] = pack_h16_rest(v0, v1, h, m1);
+                }
             }
         }
     }
@@ -464,6 +542,14 @@ __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
 hipError_t launch_slabs(const SlabArgs &a, int fp32, int max_nstar, hipStream_t s)
 {
     if (a.n_groups <= 0) return hipSuccess;
+    if (a.layout == 2 || (a.layout == 1 && mma_split(a.P))) {
+        const int64_t parts = (a.mma_stride / 2 + kSplitPairs - 1) / kSplitPairs;
+        const int64_t chunks = std::min<int64_t>((max_nstar + a.extra + kSplitQ - 1) / kSplitQ, std::max<int64_t>(1, (1 << 22) / parts));
+        const dim3 sg((unsigned)(parts * chunks), (unsigned)std::min<int64_t>(a.n_groups, kGridYZ),
+                      (unsigned)((a.n_groups + kGridYZ - 1) / kGridYZ));
+        hipLaunchKernelGGL(slab_split_kernel, sg, dim3(256), 0, s, a, (int)parts);
+        return hipGetLastError();
+    }
     int64_t bx = (max_nstar + a.extra + kSlabQ - 1) / kSlabQ;
     if (bx > 65535) bx = 65535;
     dim3 grid((unsigned)bx, (unsigned)std::min<int64_t>(a.n_groups, kGridYZ),

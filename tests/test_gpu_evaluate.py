@@ -1,9 +1,8 @@
 """Off-node values of u* and v* against the oracle, for every rounding-up of the degree
 (8, 16, 24, 32 time values in registers), one to four dimensions and point counts around
-a block of 64.  Bound: each of the P + T terms that a
-value passes through per dimension rounds at most as the nodal values themselves do, so
-16 (P + T) times the change from nodal values perturbed by one eps, the largest over the
-points."""
+a block of 64.  Bound: each of the P + T terms that a value passes through per dimension
+rounds at most as the nodal values themselves do, so 16 (P + T) times the change from
+nodal values perturbed by one eps, the largest over the points."""
 import numpy as np
 import pytest
 
