@@ -794,8 +794,9 @@ __device__ __forceinline__ void add_stats(const RoundArgs &a, unsigned long long
         slots += __shfl_xor(slots, o, 64);
     }
     if ((threadIdx.x & 63) == 0 && (evals | slots) != 0ull) {
-        atomicAdd(a.stats + 0, evals);
-        atomicAdd(a.stats + 1, slots);
+        unsigned long long *st = a.stats + blockIdx.x % kStatStripes * kStatWords;
+        atomicAdd(st, evals);
+        atomicAdd(st + 1, slots);
     }
 }
 

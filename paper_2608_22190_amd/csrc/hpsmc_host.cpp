@@ -432,7 +432,7 @@ struct hpsmc_plan {
     double *share_sum = nullptr;
     uint32_t *share_done = nullptr;
     int64_t share_max = 0;
-    unsigned long long *counters = nullptr;  // [0] work, [1] evals, [2] lane steps, [3] unused
+    unsigned long long *counters = nullptr;  // [kCounterWords]: the work counter, then the statistics
     unsigned long long *maxbits = nullptr;   // [4096]
     int64_t m_probe = 0;
     std::vector<hpsmc::NodeSet> sets;        // sequential: one per interval; sweeps: one
@@ -1382,7 +1382,7 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
     a.inv_scale = set.slab.inv_scale;
     a.bscale = (float)set.slab.bscale;
     a.work = plan->counters;
-    a.stats = plan->counters + 1;
+    a.stats = plan->counters + kStatWords;
     a.phys = physics_of(plan);
     const int blocks = std::max(1, plan->cus * plan->launch.blocks_per_cu);
     // rounds of the 5-D matrix-core kernel whose paths fit in one pass of the
@@ -1520,7 +1520,7 @@ static hpsmc_status sample_set(hpsmc_plan *plan, NodeSet &set, int tag, int reco
     a.probe = (plan->m_probe > 0 && set.probe) ? set.probe : nullptr;
     a.m_probe = plan->m_probe;
     a.work = plan->counters;
-    a.stats = plan->counters + 1;
+    a.stats = plan->counters + kStatWords;
     a.phys.dim = plan->d;
     a.phys.f_kind = plan->pb.f_kind;
     a.phys.src_kind = plan->pb.src_kind == HPSMC_SRC_POLY ? HPSMC_SRC_NONE : plan->pb.src_kind;
@@ -1683,7 +1683,7 @@ hpsmc_status hpsmc_create(const hpsmc_problem *pb, hpsmc_plan **out)
         if ((st = dalloc(pl, (void **)&pl->share_sum, (size_t)plan->share_max * (kShareBatch * 8 + 4)))) return st;
         plan->share_done = (uint32_t *)(plan->share_sum + plan->share_max * kShareBatch);
     }
-    if ((st = dalloc(pl, (void **)&pl->counters, 4 * 8))) return st;
+    if ((st = dalloc(pl, (void **)&pl->counters, kCounterWords * 8))) return st;
     if ((st = dalloc(pl, (void **)&pl->maxbits, 4096 * 8))) return st;
     if (pl->frac && (st = frac_tables(pl))) return st;
     if (pb->src_kind == HPSMC_SRC_POLY) {
@@ -1785,7 +1785,7 @@ hpsmc_status hpsmc_create(const hpsmc_problem *pb, hpsmc_plan **out)
     initial_nodes(pl, u0);
     if (hipMemcpy(pl->mats, mats.data(), mats.size() * 8, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(pl->ic, u0.data(), u0.size() * 8, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemset(pl->counters, 0, 32) != hipSuccess || hipMemset(pl->maxbits, 0, 4096 * 8) != hipSuccess ||
+        hipMemset(pl->counters, 0, kCounterWords * 8) != hipSuccess || hipMemset(pl->maxbits, 0, 4096 * 8) != hipSuccess ||
         hipMemset(pl->U, 0, usz * 8) != hipSuccess)
         return fail(HPSMC_EDEVICE, "initial upload failed");
     if (cheb && pl->src_poly) {   // the polynomial source in the image's basis, once
@@ -2345,7 +2345,7 @@ hpsmc_status hpsmc_stats(const hpsmc_plan *plan, hpsmc_stats_t *out, void *strea
     CHECK_PLAN(plan);
     if (!out) return fail(HPSMC_EINVAL, "out is NULL");
     memset(out, 0, sizeof(*out));
-    unsigned long long c[4];
+    unsigned long long c[kCounterWords];
     std::vector<unsigned long long> mb(4096);
     hipStream_t s = (hipStream_t)stream;
     if (hipMemcpyAsync(c, plan->counters, sizeof(c), hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -2361,8 +2361,10 @@ hpsmc_status hpsmc_stats(const hpsmc_plan *plan, hpsmc_stats_t *out, void *strea
     out->adjoint_launches = (int64_t)plan->n_adj;
     out->advance_launches = plan->n_advance;
     out->recon_launches = (int32_t)plan->n_recon;
-    out->path_steps = c[1];
-    out->lane_steps = c[2];
+    for (int i = 1; i <= kStatStripes; ++i) {
+        out->path_steps += c[i * kStatWords];
+        out->lane_steps += c[i * kStatWords + 1];
+    }
     out->node_samples = (uint64_t)plan->node_samples;
     if (plan->twin) {   // the FP64 twin's share of the work
         hpsmc_stats_t t;
@@ -2399,7 +2401,7 @@ hpsmc_status hpsmc_reset_stats(hpsmc_plan *plan, void *stream)
     if (plan->twin)
         if (hpsmc_status st = hpsmc_reset_stats(plan->twin, stream)) return st;
     hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(launch_fill_u64(plan->counters, 4, 0ull, s));
+    HIP_TRY(launch_fill_u64(plan->counters, kCounterWords, 0ull, s));
     HIP_TRY(launch_fill_u64(plan->maxbits, 4096, 0ull, s));
     plan->node_samples = 0;
     plan->n_records = 0;
@@ -2812,7 +2814,7 @@ static hpsmc_status adjoint_sampling(hpsmc_plan *plan, NodeSet &set, int tag, hi
     a.inv_scale = set.slab.inv_scale;
     a.bscale = (float)set.slab.bscale;
     a.work = plan->counters;
-    a.stats = plan->counters + 1;
+    a.stats = plan->counters + kStatWords;
     a.phys = physics_of(plan);
     aa.bar_stride = set.slab.slab_stride;
     aa.lambda = plan->lam;

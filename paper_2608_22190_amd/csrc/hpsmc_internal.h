@@ -45,6 +45,13 @@ struct GroupDesc {
 // beta (da, db: kFracTab + 1 values each)
 constexpr int kFracTab = 256;
 
+// The device's counters: the round's work counter, then the statistics in stripes of a
+// cache line.  Every wave adds to its block's stripe: atomics on one line, from all the
+// chip's waves, are served one by one (8192 of them held a launch of 1024 blocks for
+// 55 us).
+constexpr int kStatStripes = 64, kStatWords = 16;
+constexpr int kCounterWords = kStatWords * (1 + kStatStripes);
+
 // Problem constants every sampling lane needs.
 struct Physics {
     int32_t dim, f_kind, src_kind;
@@ -77,7 +84,7 @@ struct SampleArgs {
     double *probe;               // [node out][m_probe] or null
     int64_t m_probe;
     unsigned long long *work;    // work-item counter (zeroed before launch)
-    unsigned long long *stats;   // [0] residual evaluations, [1] lane steps
+    unsigned long long *stats;   // [kStatStripes][kStatWords]: [0] residual evaluations, [1] lane steps
     Physics phys;
 };
 
@@ -110,7 +117,7 @@ struct RoundArgs {
     const float *inv_scale;      // matrix-core images of scaled coefficients: [blk][u, v] the inverse scale
     float bscale;                // the scale of their basis values
     unsigned long long *work;    // block work counter (zeroed by the prep kernel)
-    unsigned long long *stats;   // [0] residual evaluations, [1] slot steps
+    unsigned long long *stats;   // [kStatStripes][kStatWords]: [0] residual evaluations, [1] slot steps
     Physics phys;
 };
 

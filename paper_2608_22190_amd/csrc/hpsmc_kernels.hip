@@ -207,8 +207,9 @@ __global__ void __launch_bounds__(256) sample_kernel(SampleArgs a)
     evals = wave_sum_u64(evals);
     lsteps = wave_sum_u64(lsteps);
     if (lane == 0) {
-        atomicAdd(a.stats + 0, evals);
-        atomicAdd(a.stats + 1, lsteps);
+        unsigned long long *st = a.stats + blockIdx.x % kStatStripes * kStatWords;
+        atomicAdd(st, evals);
+        atomicAdd(st + 1, lsteps);
     }
 }
 
