@@ -411,8 +411,9 @@ struct hpsmc_plan {
     int32_t sample_1d = 1;      // d = 1 rounds on the windowed 1-D kernel where eligible
     // fractional operator (d = 1): tables of the round kernel (see Physics)
     bool frac = false;
-    double *frac_tab = nullptr;
-    int32_t frac_kmax = 0, frac_K = 0, frac_nt = 0;
+    void *frac_tab = nullptr;
+    int32_t frac_kmax = 0, frac_nt = 0;
+    double frac_xs[2] = {};
     // polynomial source: per interval [P^d][T1] tensor-Legendre coefficients
     double *src_poly = nullptr;
     std::vector<int64_t> src_off;
@@ -1101,8 +1102,11 @@ static hpsmc_status resolve_nstar(const hpsmc_problem &pb, std::vector<int32_t> 
 
 // tables of the fractional round kernel: recurrence, eigenvalues, the source
 // series sum_k a_k lambda_k P_k = (-Delta)^{alpha/2}(w g) (a_k the Jacobi
-// coefficients of g by a 160-point Gauss rule), the series ratios of the
-// inverse incomplete beta; and its branch point and constants
+// coefficients of g by a 160-point Gauss rule; trailing terms that together stay
+// below the sampling precision's rounding of the sum, 2^-28 or 2^-57 of the sum of
+// all magnitudes, are left out: of the 40 taken for sin x, 11 stay in FP32), the cubics
+// of the inverse incomplete beta and (FP64) its series ratios; and its branch point
+// and constants
 static hpsmc_status frac_tables(hpsmc_plan *plan)
 {
     const double alpha = plan->pb.alpha, a = 0.5 * alpha, b = 1.0 - a;
@@ -1113,28 +1117,33 @@ static hpsmc_status frac_tables(hpsmc_plan *plan)
     case HPSMC_SRC_FRAC_SINGULAR: K = 150; break;
     case HPSMC_SRC_FRAC_POLY: K = 3; break;
     }
-    const int kmax = std::max(P, K), nt = plan->fp32 ? 26 : 60;
-    std::vector<double> A, C;
-    jacobi_rec(kmax, a, A, C);
-    std::vector<double> tab(A);
-    tab.insert(tab.end(), C.begin(), C.end());
-    for (int k = 0; k < P; ++k) tab.push_back(std::exp(std::lgamma(k + alpha + 1.0) - std::lgamma(k + 1.0)));
+    std::vector<double> A, C, src(K, 0.0);
+    jacobi_rec(std::max(P, K) + 4, a, A, C);
+    const auto lambda = [&](int k) { return std::exp(std::lgamma(k + alpha + 1.0) - std::lgamma(k + 1.0)); };
     if (K > 0) {
-        std::vector<double> xq, wq, Pv(K);
+        std::vector<double> xq, wq, Pv(K), mag(K);
         gauss_jacobi_aa(160, a, xq, wq);
-        std::vector<double> ck(K, 0.0);
         for (size_t j = 0; j < xq.size(); ++j) {
             jacobi_values(K, A, C, xq[j], Pv.data());
             const double g = frac_g(plan->pb, xq[j]);
-            for (int k = 0; k < K; ++k) ck[k] += wq[j] * g * Pv[k];
+            for (int k = 0; k < K; ++k) src[k] += wq[j] * g * Pv[k];
         }
-        for (int k = 0; k < K; ++k)
-            tab.push_back(ck[k] / jacobi_norm2(k, a) * std::exp(std::lgamma(k + alpha + 1.0) - std::lgamma(k + 1.0)));
+        double all = 0.0, tail = 0.0;
+        for (int k = 0; k < K; ++k) {
+            src[k] = src[k] / jacobi_norm2(k, a) * lambda(k);
+            // |P_k| <= P_k(1) = Gamma(k + a + 1) / (k! Gamma(a + 1))
+            mag[k] = std::fabs(src[k]) * std::exp(std::lgamma(k + a + 1.0) - std::lgamma(k + 1.0) - std::lgamma(a + 1.0));
+            all += mag[k];
+        }
+        while (K > 0 && (tail += mag[K - 1]) <= std::ldexp(all, plan->fp32 ? -28 : -57)) --K;
     }
-    for (int k = 0; k < nt; ++k) tab.push_back((k + 1.0) / (a + 1.0 + k));
-    for (int k = 0; k < nt; ++k) tab.push_back((k + 1.0) / (b + 1.0 + k));
+    const int kmax = (std::max(P, K) + 3) / 4 * 4, nt = plan->fp32 ? 0 : kFracTerms;
+    std::vector<double> tab;
+    for (int k = 0; k < kmax; ++k) tab.push_back(A[k]);
+    for (int k = 0; k < kmax; ++k) tab.push_back(C[k]);
+    for (int k = 0; k < kmax; ++k) tab.push_back(k < P ? lambda(k) : 0.0);
+    for (int k = 0; k < kmax; ++k) tab.push_back(k < K ? src[k] : 0.0);
     plan->frac_kmax = kmax;
-    plan->frac_K = K;
     plan->frac_nt = nt;
     plan->frac_lpb1 = std::log(a) + std::lgamma(a) + std::lgamma(b);
     plan->frac_lpb2 = std::log(b) + std::lgamma(a) + std::lgamma(b);
@@ -1142,11 +1151,12 @@ static hpsmc_status frac_tables(hpsmc_plan *plan)
     double S = 1.0, t = 1.0;
     for (int k = 0; k < 200; ++k) { t *= 0.5 * (k + 1.0) / (a + 1.0 + k); S += t; }
     plan->frac_half = std::exp(-std::log(2.0) - plan->frac_lpb1) * S;
-    // start tables of the inverse per branch (p = a with log(a B), p = b with
-    // log(b B)): at X0_i = i X0max / kFracTab the converged log x minus log X0_i,
-    // by the kernel's Newton iteration run in FP64 with 200 series terms, where
-    // X0max = e^{z0} at x = 1/2 (z0 the small-x asymptote of the branch)
-    double x0max[2];
+    // cubics of the inverse per branch (p = a with log(a B), p = b with log(b B)): at
+    // X0_i = i X0max / kFracTab, c_i = the converged log x minus log X0_i by Newton's
+    // iteration in FP64 with 200 series terms, where X0max = e^{z0} at x = 1/2 (z0 the
+    // small-x asymptote of the branch), and its derivative by
+    // d log x / d log X0 = (1 - x) sum_k t_k; the Hermite cubic of an interval is within
+    // 10^-11 of the function
     for (int br = 0; br < 2; ++br) {
         const double p = br ? b : a, lpb = br ? plan->frac_lpb2 : plan->frac_lpb1;
         auto series = [&](double x) {
@@ -1156,24 +1166,36 @@ static hpsmc_status frac_tables(hpsmc_plan *plan)
         };
         const double lhalf = -std::log(2.0);
         const double l_half_cdf = lhalf - lpb + std::log(series(0.5));   // log I_{1/2}(p, 1-p)
-        x0max[br] = std::exp((l_half_cdf + lpb) / p);
-        tab.push_back(0.0);   // X0 -> 0: x / X0 -> 1
+        const double x0max = std::exp((l_half_cdf + lpb) / p);
+        plan->frac_xs[br] = kFracTab / x0max;
+        double c[kFracTab + 1], d[kFracTab + 1];   // values, derivatives in units of an interval
+        c[0] = 0.0;                                // X0 -> 0: x / X0 -> 1
+        d[0] = -p / (p + 1.0) * x0max / kFracTab;
         for (int i = 1; i <= kFracTab; ++i) {
-            const double lx0 = std::log(x0max[br] * i / kFracTab), ly = p * lx0 - lpb;
+            const double lx0 = std::log(x0max * i / kFracTab), ly = p * lx0 - lpb;
             double z = std::min(lx0, lhalf);
             for (int it = 0; it < 60; ++it) {
                 const double x = std::exp(z), Sx = series(x);
                 const double lI = p * z + (1.0 - p) * std::log1p(-x) - lpb + std::log(Sx);
                 z = std::min(z - (lI - ly) * (1.0 - x) * Sx / p, lhalf);
             }
-            tab.push_back(z - lx0);
+            c[i] = z - lx0;
+            d[i] = ((1.0 - std::exp(z)) * series(std::exp(z)) - 1.0) / i;
+        }
+        for (int i = 0; i < kFracTab; ++i) {
+            const double dc = c[i + 1] - c[i];
+            for (double v : {c[i], d[i], 3.0 * dc - 2.0 * d[i] - d[i + 1], d[i] + d[i + 1] - 2.0 * dc})
+                tab.push_back(plan->fp32 ? v / std::log(2.0) : v);   // FP32: logarithms to base 2
         }
     }
-    tab.push_back(x0max[0]);
-    tab.push_back(x0max[1]);
+    for (int k = 0; k < nt; ++k) tab.push_back((k + 1.0) / (a + 1.0 + k));
+    for (int k = 0; k < nt; ++k) tab.push_back((k + 1.0) / (b + 1.0 + k));
+    const std::vector<float> tab32(tab.begin(), tab.end());
+    const size_t bytes = tab.size() * (plan->fp32 ? 4 : 8);
     hpsmc_status st;
-    if ((st = dalloc(plan, (void **)&plan->frac_tab, tab.size() * 8))) return st;
-    if (hipMemcpy(plan->frac_tab, tab.data(), tab.size() * 8, hipMemcpyHostToDevice) != hipSuccess)
+    if ((st = dalloc(plan, &plan->frac_tab, bytes))) return st;
+    if (hipMemcpy(plan->frac_tab, plan->fp32 ? (const void *)tab32.data() : tab.data(), bytes, hipMemcpyHostToDevice) !=
+        hipSuccess)
         return fail(HPSMC_EDEVICE, "fractional table upload failed");
     return HPSMC_OK;
 }
@@ -1253,7 +1275,6 @@ static Physics physics_of(const hpsmc_plan *plan)
     ph.ball = plan->pb.quad == HPSMC_QUAD_BALL;
     ph.frac = plan->frac ? 1 : 0;
     ph.frac_kmax = plan->frac_kmax;
-    ph.frac_K = plan->frac_K;
     ph.frac_nt = plan->frac_nt;
     ph.frac_P = plan->P;
     ph.frac_a = 0.5 * plan->pb.alpha;
@@ -1261,6 +1282,8 @@ static Physics physics_of(const hpsmc_plan *plan)
     ph.frac_lpb1 = plan->frac_lpb1;
     ph.frac_lpb2 = plan->frac_lpb2;
     ph.frac_tab = plan->frac_tab;
+    ph.frac_xs[0] = plan->frac_xs[0];
+    ph.frac_xs[1] = plan->frac_xs[1];
     memcpy(ph.f_param, plan->pb.f_param, sizeof(ph.f_param));
     memcpy(ph.src_param, plan->pb.src_param, sizeof(ph.src_param));
     return ph;
@@ -1351,8 +1374,7 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
     const size_t lds = k1d ? advance_1d_lds_bytes(plan->fp32, set.slab.slab_stride)
                      : mma == 2 ? advance_mma5_lds_bytes(plan->P)
                      : mma ? advance_mma_lds_bytes(plan->P)
-                     : plan->frac ? frac_lds_bytes(plan->fp32, plan->PP, plan->frac_kmax, plan->P, plan->frac_K,
-                                                   plan->frac_nt)
+                     : plan->frac ? frac_lds_bytes(plan->fp32)
                                   : (size_t)2 * ((nvec + 1) & ~1LL) * 16;
     const bool lat = k1d && set.lat;   // over nodes instead of groups
     const int C = lat ? set.lat_steps : plan->round_steps;
@@ -1363,7 +1385,7 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
     a.nodes = set.dev;
     a.n_groups = G;
     a.steps = C;
-    a.batch = nthr * ns;
+    a.batch = plan->frac ? 64 : nthr * ns;   // the fractional kernel's waves take items by themselves
     a.batch_prefix = lat ? set.lat_prefix : set.prefix;
     uint32_t *live = lat ? set.lat_live : set.live;
     LatArgs la = set.lat_args;

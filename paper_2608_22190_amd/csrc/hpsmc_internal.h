@@ -41,9 +41,9 @@ struct GroupDesc {
     int32_t blk;           // the set's coefficient block of the group's (interval, instance)
 };
 
-// intervals of the start tables of the fractional walk's inverse incomplete
-// beta (da, db: kFracTab + 1 values each)
+// intervals of the tables of the fractional walk's inverse incomplete beta (a cubic each)
 constexpr int kFracTab = 256;
+constexpr int kFracTerms = 60;   // series terms of its Newton step in FP64
 
 // The device's counters: the round's work counter, then the statistics in stripes of a
 // cache line.  Every wave adds to its block's stripe: atomics on one line, from all the
@@ -58,12 +58,14 @@ struct Physics {
     int32_t picard;              // 1: Picard-form estimator (eq. uast)
     int32_t ball;                // 1: integrand at the step's Green's-function ball point
     int32_t frac;                // 1: fractional operator (d = 1, alpha-stable walk)
-    int32_t frac_kmax, frac_K, frac_nt;  // recurrence length, source series terms, series terms of the inverse
+    int32_t frac_kmax, frac_nt;  // recurrence length (a multiple of 4), series terms of the inverse
     int32_t frac_P;              // Jacobi modes of the slab
     double frac_a;               // alpha / 2
     double frac_half;            // I_{1/2}(a, 1 - a): the branch of the inverse
     double frac_lpb1, frac_lpb2; // log(a B(a, 1-a)), log((1-a) B(1-a, a))
-    const double *frac_tab;      // A[kmax], C[kmax], lambda[P], src[K], ra[nt], rb[nt], da, db, X0max[2]
+    double frac_xs[2];           // kFracTab / X0max per branch
+    const void *frac_tab;        // in the sampling precision: A, C, lambda, src [kmax each], cubics [2][kFracTab][4],
+                                 // ra[nt], rb[nt]
     double f_param[4];
     double src_param[8];
 };
@@ -199,7 +201,7 @@ hipError_t launch_aitken(const NodeDesc *nodes, const int64_t *vbeg, int n_vec, 
 hipError_t launch_start_columns(double *U, const double *src, int64_t src_stride, int64_t src_off,
                                 int64_t dst_stride, int T1, int64_t count, int replicate, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s);
-size_t frac_lds_bytes(int fp32, int PP, int kmax, int P, int K, int nt);
+size_t frac_lds_bytes(int fp32);
 hipError_t launch_eval(const double *cu, const double *cv, int dim, int P, int T1, double t_prev, double h,
                        const double *pts, int64_t npts, double *out, hipStream_t s);
 // batch_prefix: [n_groups + 3]; batch_split > 0 lets a round that fits in at
