@@ -350,7 +350,7 @@ def run_other(name, args, torch):
         achieved = fadj * st["path_steps"] / max(1e-9, adj_ms * 1e-3) / 1e12
         out["roofline"] = {"bound": "mfma", "achieved": achieved, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                            "frac": achieved / FP32_PEAK_TFLOPS, "traffic": None,
-                           "kernel": (f"adjoint_mma2_kernel<{(P + 1) // 2}> (u* on v_mfma_f32_32x32x2f32, the "
+                           "kernel": (f"adjoint_mma2_kernel<{(P + 1) // 2}> (u* on the matrix cores as in the forward kernel, the "
                                       f"outer products on v_mfma_f32_16x16x4f32)" if P <= 20 else
                                       "adjoint_kernel<float,2,PMAX,true> (outer products on v_mfma_f32_32x32x2f32)"),
                            "flops_per_eval": fadj,
@@ -403,15 +403,14 @@ def run_compare(args, torch):
     print(json.dumps(line), flush=True)
 
 
-def flops_per_eval_frac(P, K, fp32):
-    """Algorithmic FP operations of one step of the fractional walk: the Newton
-    inverse of the incomplete beta (a start interpolated from a table, ~10, then
-    one iteration of a 26- or 60-term series at 3 flops a term, plus ~30 for
-    the logarithms and the update), the Jacobi recurrence with three
-    contractions over P modes (9 flops a mode) and the source series over K
-    modes (4 flops a mode), ~40 for w, f and the source."""
-    nit, nt = (1, 26) if fp32 else (1, 60)
-    return 10 + nit * (3 * nt + 30) + 9 * P + 4 * K + 40
+def flops_per_eval_frac(P, fp32):
+    """Flops per walk step of the fractional kernel: the inverse incomplete beta
+    (a tabulated cubic and the functions around it, ~30; FP64 one Newton step of
+    a 60-term series at 3 flops a term, plus ~30 for the logs and exps, on top),
+    the symmetric-Jacobi recurrence and the u, v, F contractions over P modes (9
+    flops a mode), the source series (4 flops a mode; of sin x's terms 12 are
+    above FP32's rounding and 20 above FP64's), ~40 for w, f and the source."""
+    return 40 + (0 if fp32 else 3 * 60 + 30) + 9 * P + 4 * (12 if fp32 else 20) + 40
 
 
 def run_frac(args, torch):
@@ -454,7 +453,7 @@ def run_frac(args, torch):
             sk = plan.hpsmc_stats(stream=stream)
         ns = wl.nodes_per_sweep * wl.M * wl.iters
         k_ms = sk["sample_ms"] / max(1, sk["sample_launches"])
-        fpe = flops_per_eval_frac(wl.n, 40, prec == "fp32")
+        fpe = flops_per_eval_frac(wl.n, prec == "fp32")
         res[prec] = {"seconds": sec, "node_samples_per_s": ns / sec, "max_error": max(errs),
                      "error_per_interval": errs, "path_steps": st["path_steps"],
                      "mean_path_length": st["path_steps"] / max(1, st["node_samples"]),
@@ -472,7 +471,7 @@ def run_frac(args, torch):
                                    "per interval, whole solve"},
             "roofline": {"bound": "alu", "achieved": r32["achieved_tflops"], "peak": FP32_PEAK_TFLOPS,
                          "unit": "TFLOP/s", "frac": r32["achieved_tflops"] / FP32_PEAK_TFLOPS,
-                         "flops_per_eval": flops_per_eval_frac(11, 40, True)},
+                         "flops_per_eval": flops_per_eval_frac(11, True)},
             "speedup_fp32_vs_fp64": r64["seconds"] / r32["seconds"], "results": res}
     print(json.dumps(line), flush=True)
 
@@ -785,7 +784,7 @@ def main():
         "roofline": {"bound": "mfma" if r32["mma"] else "alu", "achieved": achieved, "peak": FP32_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved / FP32_PEAK_TFLOPS,
                      "traffic": measured_traffic(r32["launch"]),
-                     "kernel": (f"advance_mma_kernel<{(P + 1) // 2},0> (v_mfma_f32_32x32x2f32)"
+                     "kernel": (f"advance_mma_kernel<{(P + 1) // 2},0> (v_mfma_f32_32x32x16_f16, two parts per FP32 operand)"
                                 if r32["mma"] else "advance_kernel<float,2,28,NS,0,0> (vector units)"),
                      "flops_per_eval": fpe,
                      "evals_per_launch": evals_per_launch, "avg_launch_ms": k_ms,

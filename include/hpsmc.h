@@ -401,7 +401,9 @@ hpsmc_status hpsmc_set_initial_coeffs(hpsmc_plan *plan, const double *c0, int32_
  *   "sample_mfma"       1 (default): 2-D FP32 plans with P = n + 2 <= 32 and one
  *                       sample per lane run the path-advancing kernel with the
  *                       slab contraction of eq. ufg_ep1 on the matrix cores
- *                       (v_mfma_f32_32x32x2f32) -- the residual and Picard
+ *                       (FP32 products for P < 17, from there two
+ *                       half-precision parts per operand with FP32 sums, of
+ *                       no larger error) -- the residual and Picard
  *                       forms, the centre-point and ball-point rules (plans of
  *                       the Picard form or the ball rule count as one sample
  *                       per lane); so do 5-D FP32 plans of the residual form
@@ -420,8 +422,11 @@ hpsmc_status hpsmc_set_initial_coeffs(hpsmc_plan *plan, const double *c0, int32_
  *   "sample_1d"         1 (default): d = 1 rounds of the residual form with
  *                       the centre-point rule run the windowed 1-D kernel (the
  *                       slabs of 32 walk steps staged in LDS per barrier, the
- *                       same walk and arithmetic as the general kernel); 0: the
- *                       general vector-unit kernel.
+ *                       same walk and arithmetic as the general kernel), or,
+ *                       FP64 with P <= 20 and where it is the less work, its
+ *                       tabulated form (the residual once per lattice point a
+ *                       node's walks reach and step); 0: the general
+ *                       vector-unit kernel.
  *   "sample_1d_active"  read-only: 1 when the rounds run the windowed 1-D
  *                       kernel with the current launch shape.
  *   "graph"            1: hpsmc_solve captures the whole solve into a hipGraph
