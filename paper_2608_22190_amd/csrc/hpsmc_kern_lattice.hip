@@ -19,7 +19,7 @@ namespace hpsmc {
 // values of its point and runs over the steps, whose coefficients are scalar
 // operands), the walk by its own ten-odd instructions and one LDS gather (eight
 // steps' gathers in flight together).  16 x 16 nodes, 4096 samples, five
-// iterations: 90 ms with every path evaluated, 15.6 ms so (tables 4, walk 10.6);
+// iterations: 90 ms with every path evaluated, 14.5 ms so (tables 4, walk 9.7);
 // a coarse iteration of 64 samples, 200 steps one after another: 667 -> 195 us.
 // ===========================================================================
 
@@ -247,7 +247,6 @@ hipError_t launch_lat_table(const RoundArgs &a, const LatArgs &la, hipStream_t s
                     (unsigned)la.n_groups);
     if (a.P <= 12) hipLaunchKernelGGL(lat_table_kernel<12>, grid, dim3(256), 0, s, a, la);
     else if (a.P <= 20) hipLaunchKernelGGL(lat_table_kernel<20>, grid, dim3(256), 0, s, a, la);
-    
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
