@@ -845,10 +845,9 @@ __global__ void round_prep_kernel(const GroupDesc *__restrict__ groups, int32_t 
     // at most split_max items of batch_split paths takes that batch instead;
     // batch_prefix[n_groups + 1] holds the paths per item the round kernel is
     // to use, batch_prefix[n_groups + 2] the shares each batch is split into:
-    // the largest power of two (at most kMaxShares) that keeps batches times
-    // shares within share_max, so that a round of few batches still fills the
-    // grid (each share's block walks the whole round and evaluates every
-    // shares-th step).
+    // as many (at most kMaxShares) as keep batches times shares within share_max,
+    // so that a round of few batches still fills the grid (each share's block
+    // walks the whole round and evaluates every shares-th step).
     __shared__ int64_t part[256], part_s[256];
     __shared__ int32_t s_split;
     const int t = threadIdx.x, nt = blockDim.x;
@@ -880,8 +879,7 @@ __global__ void round_prep_kernel(const GroupDesc *__restrict__ groups, int32_t 
     if (t == 0) {
         const bool split = batch_split > 0 && part_s[nt - 1] <= split_max;
         const int64_t n = split ? part_s[nt - 1] : part[nt - 1];
-        int64_t shares = 1;
-        while (n > 0 && 2 * shares * n <= share_max && 2 * shares <= kMaxShares && 2 * shares <= steps) shares *= 2;
+        const int64_t shares = n > 0 ? max((int64_t)1, min(share_max / n, (int64_t)min(kMaxShares, steps))) : 1;
         batch_prefix[n_groups] = n * shares;
         batch_prefix[n_groups + 1] = split ? batch_split : batch;
         batch_prefix[n_groups + 2] = shares;
