@@ -1415,7 +1415,12 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
     const int split_batch = mma == 2 && plan->sample_split && (waves == 2 || waves == 4) ? 64 : 0;
     const int64_t split_max = blocks;
     // shares of steps: every round kernel but the windowed 1-D and the fractional one
-    const int64_t share_max = k1d || plan->frac ? 0 : std::min<int64_t>(blocks, plan->share_max);
+    // (within the grid's blocks; on the vector units, whose blocks are bound by issue, up to
+    // three a CU also where fewer are resident: with 257 .. 384 batches unsplit some CUs run
+    // two and most one.  FP64 at two blocks a CU 370 -> 353 ms; the matrix-core kernels, whose
+    // repeated walks weigh more, got 2% slower)
+    const int64_t share_grid = mma ? blocks : std::max<int64_t>(blocks, 3 * (int64_t)plan->cus);
+    const int64_t share_max = k1d || plan->frac ? 0 : std::min<int64_t>(share_grid, plan->share_max);
     a.share_sum = plan->share_sum;
     a.share_done = plan->share_done;
     hpsmc_plan::EvPair *ek = next_pair(plan->ev_span, plan->n_span);

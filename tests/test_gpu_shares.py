@@ -35,8 +35,12 @@ def _iterate(wl, U, launch, **opt):
     (1, 3, 1, 5, 70, (1, 1, 2, 20), dict(quad="ball")),
     (1, 4, 2, 300, 33, (1, 4, 1, 16), dict(estimator="picard")),
     (2, 3, 2, 30, 50, (2, 2, 2, 20), {}),
-    (2, 3, 2, 4000, 24, (1, 4, 1, 16), {}),          # 2 x 141 batches, grid of 256 blocks: no shares
-    (2, 2, 1, 16000, 30, (1, 4, 1, 20), {}),         # 250 batches: none; later rounds two and more
+    (2, 3, 2, 4000, 24, (1, 4, 1, 16), {}),          # 2 x 141 batches: two shares
+    (2, 2, 1, 16000, 30, (1, 4, 1, 20), {}),         # 250 batches: three; later rounds more
+    (2, 3, 2, 4260, 24, (1, 4, 1, 16), {}),          # 300 batches: two shares, more items than the grid's 256 blocks
+    (2, 3, 2, 2120, 21, (1, 4, 1, 20), {}),          # 150 batches: five shares
+    (2, 3, 2, 850, 24, (2, 4, 1, 16), {}),           # 30 batches of 512: sixteen; then fewer batches
+    (2, 3, 2, 1000, 29, (1, 4, 1, 16), dict(estimator="picard")),   # 72 batches: ten
     (2, 3, 1, 37, 45, (1, 4, 4, 16), dict(estimator="picard", quad="ball")),
     (3, 2, 2, 50, 40, (2, 4, 2, 20), {}),
     (3, 10, 1, 2, 24, (1, 4, 2, 20), {}),            # LDS-chunked slabs
