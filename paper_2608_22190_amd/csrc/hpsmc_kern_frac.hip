@@ -265,8 +265,10 @@ __global__ void __launch_bounds__(256) frac_advance_kernel(RoundArgs a)
                     // ---- residual at X_q, tau_q = t_{n,l} - q Delta
                     const T wgt = frac_weight(X, fa);
                     T pm = (T)0, pc = (T)1, uj = (T)0, vj = (T)0, F = (T)0, Gs = (T)0;
+                    // (A x) p, not A (x p): its rms error over 16 modes is 5 .. 10% smaller, and A x
+                    // is off the chain from mode to mode
                     const auto next = [&](int k) {
-                        const T pn = m_fma(tA[k], X * pc, -(tC[k] * pm));
+                        const T pn = m_fma(tA[k] * X, pc, -(tC[k] * pm));
                         pm = pc;
                         pc = pn;
                     };
@@ -326,7 +328,7 @@ __global__ void __launch_bounds__(256) frac_advance_kernel(RoundArgs a)
             T pm = (T)0, pc = (T)1, uj = (T)0;
             for (int k = 0; k < a.P; ++k) {
                 uj = m_fma(Sn[k], pc, uj);
-                const T pn = m_fma(tA[k], X * pc, -(tC[k] * pm));
+                const T pn = m_fma(tA[k] * X, pc, -(tC[k] * pm));
                 pm = pc;
                 pc = pn;
             }
