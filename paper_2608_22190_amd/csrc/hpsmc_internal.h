@@ -234,9 +234,10 @@ size_t advance_mma_lds_bytes(int P);
 // T_{k0} T_{k1}.  P >= 17: halves [table u, v][part 0, 1][block of 8 modes
 // k1][row k0 < 32][8 modes], the two parts a0 + a1 of the scaled coefficients;
 // smaller P: FP32 columns (u modes k1, then v modes k1) of 33 rows k0.  Zeros past P.
-// The line: against 64 bits (random and decaying tables) the split products'
-// rms error is 1.1-1.15 times the FP32 products' at P = 5 and 10, the same at 14,
-// and 0.93-0.99, 0.92-0.96, 0.87-0.97, 0.83-0.95 of it at P = 18, 22, 26, 32.
+// The line: against 64 bits the split products' rms error is 0.87-0.97 (random tables) and
+// 0.82-0.97 (smooth ones) of the FP32 products' at P = 17 .. 32; at P = 5 and 10, split from
+// FP32 values and summed in one chain, it was 1.1-1.15 times theirs, and the products
+// are not what bounds a step there.
 constexpr int kMmaRows = 33;
 constexpr int kMmaSplitKH = 9;   // from this ceil(P / 2) on
 constexpr bool mma_split(int P) { return (P + 1) / 2 >= kMmaSplitKH; }

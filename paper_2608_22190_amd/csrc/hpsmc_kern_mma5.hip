@@ -24,9 +24,8 @@ namespace hpsmc {
 // split pairs and swaps a step and 104 products of 32x32x16 a tile, where FP32
 // products (32x32x2) took 200 a tile, of twice the time each, and formed every entry
 // again for every tile: 8^5 x 8 nodes, two samples, 302 -> 155 ms an iteration.  Error
-// against 64 bits (rms over random and decaying tables, of the largest coefficient):
-// 0.75-0.85 of the FP32 products' at P = 5, 0.55-0.8 at 10, the same to 1.2 times it at
-// P = 3 (one spatial node per dimension), 0.83-0.91 at 4.
+// against 64 bits (rms, of the FP32 products', random and smooth tables): 0.6 and 0.5 at
+// P = 4, 0.8 and 0.5 at 5, 0.75-0.8 at 6 and 7, 1.0 and 0.9 at 8, 0.75 and 0.65 at 10.
 // ===========================================================================
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -125,12 +124,15 @@ __device__ __forceinline__ void mma5_fold_main(int t, const f32x16 &dA, const f3
 }
 
 // Remainder tile t: rows rr = 32 t + i hold (k0, f) = (rr / B, 32 A + rr % B),
-// weight L_{k0} L_{k1} L_{k2}; rows past B P are zero and skipped.
+// weight L_{k0} L_{k1} L_{k2}; rows past B P are zero and skipped.  Four sums (the two
+// halves of the swap, the first tile and the others): chains of up to 125 terms into
+// one would round each of them.
 template <int P>
 __device__ __forceinline__ void mma5_fold_rem(int t, const f32x16 &dA, const f32x16 &dB, const float (&L0)[P],
-                                              const float (&L1)[P], const float (&L2)[P], float &u)
+                                              const float (&L1)[P], const float (&L2)[P], float (&u)[4])
 {
     constexpr Mma5Geom g = mma5_geom(P);
+    const int s = t > 0 ? 2 : 0;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int ia = 8 * (r >> 2) + (r & 3), ib = ia + 4;
@@ -139,11 +141,11 @@ __device__ __forceinline__ void mma5_fold_rem(int t, const f32x16 &dA, const f32
         const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(dA[r]), __float_as_uint(dB[r]), false, false);
         {
             const int k0 = ra / g.B, f = 32 * g.A + ra % g.B;
-            u = fmaf(L0[k0] * (L1[f / P] * L2[f % P]), __uint_as_float(p[0]), u);
+            u[s] = fmaf(L0[k0] * (L1[f / P] * L2[f % P]), __uint_as_float(p[0]), u[s]);
         }
         if (rb < g.B * P) {
             const int k0 = rb / g.B, f = 32 * g.A + rb % g.B;
-            u = fmaf(L0[k0] * (L1[f / P] * L2[f % P]), __uint_as_float(p[1]), u);
+            u[s + 1] = fmaf(L0[k0] * (L1[f / P] * L2[f % P]), __uint_as_float(p[1]), u[s + 1]);
         }
     }
 }
@@ -293,7 +295,7 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
                 if (nparts == 1) mma5_tile<P, false>(S, lane, pA, pB, 0, 1, dA, dB);
                 else mma5_tile<P, true>(S, lane, pA, pB, part, nparts, dA, dB);
             };
-            float u = 0.f, v = 0.f;
+            float us[4] = {}, vs[4] = {};   // sums of rising modes, added up from the last
             if constexpr (A > 0) {
                 float l0p = 0.f, l0c = 1.f;   // L_{k0}(X0)
                 for (int k0 = 0; k0 < P; ++k0) {
@@ -320,15 +322,20 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
                         su = fmaf(L1[k], au[k], su);
                         sv = fmaf(L1[k], av[k], sv);
                     }
-                    u = fmaf(l0c, su, u);
-                    v = fmaf(l0c, sv, v);
+                    if (k0 < 2) {
+                        us[0] = fmaf(l0c, su, us[0]);
+                        vs[0] = fmaf(l0c, sv, vs[0]);
+                    } else {
+                        us[1] = fmaf(l0c, su, us[1]);
+                        vs[1] = fmaf(l0c, sv, vs[1]);
+                    }
                     const float nx = (float)((2.0 * k0 + 1.0) / (k0 + 1.0)) * X[0] * l0c - (float)(k0 / (k0 + 1.0)) * l0p;
                     l0p = l0c;
                     l0c = nx;
                 }
             }
             if constexpr (R > 0) {
-                float L0[P];
+                float L0[P], ur[4] = {}, vr[4] = {};
                 legendre_row<P>(X[0], L0);
 #pragma unroll
                 for (int t = 0; t < R; ++t) {
@@ -336,15 +343,20 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
                     if (wave_live) {
                         f32x16 dA, dB;
                         tile(lds + buf * CV, bA, bB, dA, dB);
-                        mma5_fold_rem<P>(t, dA, dB, L0, L1, L2, u);
+                        mma5_fold_rem<P>(t, dA, dB, L0, L1, L2, ur);
                         tile(lds + buf * CV + TV, bA, bB, dA, dB);
-                        mma5_fold_rem<P>(t, dA, dB, L0, L1, L2, v);
+                        mma5_fold_rem<P>(t, dA, dB, L0, L1, L2, vr);
                     }
                     mma_stage_wait();
                     __syncthreads();
                     buf ^= 1;
                 }
+                us[2] = ur[0] + ur[2];
+                us[3] = ur[1] + ur[3];
+                vs[2] = vr[0] + vr[2];
+                vs[3] = vr[1] + vr[3];
             }
+            float u = us[0] + (us[1] + (us[2] + us[3])), v = vs[0] + (vs[1] + (vs[2] + vs[3]));
             if (split) {   // the waves' shares of u and v, summed in wave order
                 s_red[0][wave][lane] = u;
                 s_red[1][wave][lane] = v;

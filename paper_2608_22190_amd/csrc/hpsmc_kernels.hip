@@ -492,7 +492,6 @@ __global__ void __launch_bounds__(256) slab_split_kernel(SlabArgs a, int parts)
     uint32_t *table = (uint32_t *)a.slab_table + a.slab_off_mma[g];
     const double2 *pack = (const double2 *)a.pack + (int64_t)a.blk[g] * a.pack_t * pairs;
     const double span = a.span[g], delta = a.delta[g], h2 = a.h2[g];
-    const float m1 = opaque_minus_one();
     for (int q0 = chunk * kSplitQ; q0 < nq; q0 += chunks * kSplitQ) {
         const int qn = min(kSplitQ, nq - q0);
         __syncthreads();   // the previous chunk's reads of Lt are over
@@ -530,10 +529,11 @@ __global__ void __launch_bounds__(256) slab_split_kernel(SlabArgs a, int parts)
             for (int j = 0; j < kSplitQ; ++j) {
                 if (j < qn) {
                     uint32_t *dst = table + (int64_t)(q0 + j) * a.mma_stride;
-                    const float v0 = (float)acc[0][j], v1 = (float)acc[1][j];
-                    const uint32_t h = pack_h16(v0, v1);
+                    // part 1 is what part 0 leaves of the FP64 sum: no rounding to FP32 in between
+                    const uint32_t h = pack_h16((float)acc[0][j], (float)acc[1][j]);
+                    const h16x2 h2 = __builtin_bit_cast(h16x2, h);
                     dst[o0] = h;
-                    dst[o1] = pack_h16_rest(v0, v1, h, m1);
+                    dst[o1] = pack_h16((float)(acc[0][j] - (double)h2.x), (float)(acc[1][j] - (double)h2.y));
                 }
             }
         }

@@ -1,0 +1,178 @@
+"""Error against 64 bits of the matrix-core kernels' split half-precision products.
+
+A path of one step (N* = 1) adds Delta (a u + v) at its own node and nothing else
+unless it leaves, so its value is the reconstruction there: against the FP64
+evaluation at the same (FP32) point, what remains is the error of the FP32
+contraction.  The bar is that of FP32 products: the same sums with every product
+and sum in FP32 (fma chains in the order of the 32x32x2 products and of the rows),
+computed here.  The split form's rms error has to be no larger, but for the scatter
+of an rms over some 10^3 to 10^4 values, 2%.
+
+That bar is about 2^-23 of the value, so it also fails if a low part is lost: 2^-12
+of every entry (checked on the model below)."""
+import numpy as np
+import pytest
+from numpy.polynomial import chebyshev, legendre
+
+from paper_2608_22190_amd import workloads as W
+
+gpu = pytest.mark.gpu
+F = np.float32
+
+
+def _fma(a, b, c):
+    return (a.astype(np.float64) * b.astype(np.float64) + c.astype(np.float64)).astype(F)
+
+
+def _cheb(x, P):
+    T = [np.ones_like(x), x]
+    for k in range(1, P - 1):
+        T.append(_fma(x + x, T[k], -T[k - 1]))
+    return T[:P]
+
+
+def _leg(x, P):
+    L = [np.ones_like(x), x]
+    for k in range(1, P - 1):
+        L.append(_fma(F((2 * k + 1) / (k + 1)) * x, L[k], -(F(k / (k + 1)) * L[k - 1])))
+    return L[:P]
+
+
+def _model_2d(C, x0, x1):
+    """FP32 products of a table C[k0][k1] in the Chebyshev basis at points (x0, x1)."""
+    P, KH = len(C), (len(C) + 1) // 2
+    A, T0, T1 = C.astype(F), _cheb(x0, P), _cheb(x1, P)
+    T = np.zeros((P, x0.size), F)
+    for kk in range(KH):
+        for k in (kk, KH + kk):
+            if k < P:
+                T = _fma(A[:, k, None], T1[k][None], T)
+    s = np.zeros_like(x0)
+    for g in range(0, P, 8):
+        for k in [g + r + h for r in range(4) for h in (0, 4)]:
+            if k < P:
+                s = _fma(T0[k], T[k], s)
+    return s
+
+
+def _model_5d(C, X):
+    """FP32 products of a table C[k0..k4] in the Legendre basis at points X[5]."""
+    P = len(C)
+    L = [_leg(x, P) for x in X]
+    A = C.reshape(P ** 3, P, P).astype(F)
+    T = np.zeros((P ** 3, X[0].size), F)
+    for k3 in range(P):
+        for k4 in range(P):
+            T = _fma(A[:, k3, k4, None], (L[3][k3] * L[4][k4])[None], T)
+    main = P * P // 32 * 32   # rows (k1, k2) of every k0 in main tiles, the rest one after another
+    u = np.zeros_like(X[0])
+    for k0 in range(P):
+        au = [np.zeros_like(u) for _ in range(P)]
+        for f in range(main):
+            au[f // P] = _fma(L[2][f % P], T[k0 * P * P + f], au[f // P])
+        su = np.zeros_like(u)
+        for k in range(P if main else 0):
+            su = _fma(L[1][k], au[k], su)
+        u = _fma(L[0][k0], su, u)
+    for k0 in range(P):
+        for f in range(main, P * P):
+            u = _fma(L[0][k0] * (L[1][f // P] * L[2][f % P]), T[k0 * P * P + f], u)
+    return u
+
+
+def _values(kind, x, t, inst, dim, rng):
+    out = np.empty((inst, len(x) ** dim, len(t)))
+    for i in range(inst):
+        if kind == "random":
+            out[i] = rng.standard_normal(out[i].shape)
+            continue
+        g = np.ones(1)
+        for _ in range(dim):
+            a = rng.uniform(-0.4, 0.4, 3)
+            g = np.multiply.outer(g, (1 - x * x) * (1 + a[0] * x + a[1] * x * x + a[2] * np.sin(2 * x)))
+        out[i] = g.reshape(-1)[:, None] * np.exp(-t / t[-1])
+    return out
+
+
+def _errors(dim, n, kind, estimator, inst, deg, points):
+    """(kernel's, FP32 products') errors relative to the tables' rms value, and the kernel that ran."""
+    from paper_2608_22190_amd import hpsmc as H
+    wl = W.small(dim=dim, n=n, M_deg=deg, M=1, T=1e-4, f="affine", f_param=[0.7, 0.0, 0, 0], src="none", ic="singular",
+                 precision="fp32", estimator=estimator, nstar=1, n_instances=inst)
+    rng = np.random.default_rng(n)
+    P, van = n + 2, chebyshev.chebvander if dim == 2 else legendre.legvander
+    xs = np.cos((np.arange(P) + 0.5) * np.pi / P)
+    inv = np.linalg.inv(van(xs, P - 1))
+    ker, mod = [], []
+    with H.Plan(wl) as plan:
+        plan.hpsmc_set_launch(1, 4, 2, 64)
+        active = plan.hpsmc_get_option("sample_mfma_active")
+        x, t = plan.hpsmc_grid(0)
+        U = _values(kind, x, t, inst, dim, rng)
+        if estimator == "picard":
+            U[:, :, 0] = 0.0   # nothing to add at the walk's end
+        plan.hpsmc_set_probe(1)
+        plan.hpsmc_set_nodes(0, U)
+        plan.hpsmc_iterate(0, 1)
+        got = plan.hpsmc_get_probe(0)[..., 0].reshape(inst, deg, -1)
+        plan.hpsmc_set_nodes(0, U)
+        sel = rng.choice(wl.nsp, min(points, wl.nsp), replace=False)
+        X = np.stack([x[i].astype(F) for i in np.unravel_index(sel, (n,) * dim)])
+        grid = np.stack(np.meshgrid(*[xs] * dim, indexing="ij"), -1).reshape(-1, dim)
+        pts = np.concatenate([X.T.astype(np.float64), grid])
+        for i in range(inst):
+            for l in range(1, deg + 1):
+                uv = plan.hpsmc_eval(0, i, np.concatenate([pts, np.full((len(pts), 1), t[l])], 1))
+                uv, tab = uv[:len(sel)], uv[len(sel):]
+                if estimator == "picard":
+                    uv[:, 1] = tab[:, 1] = 0.0
+                ref = 0.7 * uv[:, 0] + uv[:, 1]
+                m = []
+                for c in range(2):
+                    C = tab[:, c].reshape((P,) * dim)
+                    for axis in range(dim):
+                        C = np.moveaxis(np.tensordot(inv, C, (1, axis)), 0, axis)
+                    m.append(_model_2d(C, *X) if dim == 2 else _model_5d(C, X))
+                dl = F(t[l] - t[0])
+                val, mdl = got[i, l - 1, sel], dl * _fma(np.full_like(m[0], 0.7), m[0], m[1])
+                stays = val != 0.0
+                s = np.sqrt(np.mean(ref ** 2))
+                ker.append((val / np.float64(dl) - ref)[stays] / s)
+                mod.append((mdl.astype(np.float64) / np.float64(dl) - ref)[stays] / s)
+    return np.concatenate(ker), np.concatenate(mod), active
+
+
+def _rms(e):
+    return float(np.sqrt(np.mean(e ** 2)))
+
+
+CASES = ([(2, n, kind, est, 8, 4, 400) for n in (15, 16, 18, 24, 30) for kind, est in
+          (("random", "residual"), ("smooth", "residual"), ("smooth", "picard"))] +
+         [(5, n, kind, "residual", inst, 2, pts) for n, inst, pts in ((2, 40, 32), (3, 8, 243), (5, 4, 500), (6, 6, 400), (8, 2, 256))
+          for kind in ("random", "smooth")])
+
+
+@gpu
+@pytest.mark.parametrize("dim,n,kind,estimator,inst,deg,points", CASES)
+def test_no_less_exact_than_fp32_products(dim, n, kind, estimator, inst, deg, points):
+    print("[case] split error", dim, n, kind, estimator, flush=True)
+    ker, mod, active = _errors(dim, n, kind, estimator, inst, deg, points)
+    assert active == (1 if dim == 2 else 2)
+    print(f"rms error {_rms(ker):.3e}, of FP32 products {_rms(mod):.3e}, {ker.size} values")
+    assert _rms(ker) <= 1.02 * _rms(mod)
+
+
+@pytest.mark.parametrize("P", [17, 32])
+@pytest.mark.parametrize("lost", ["table", "basis"])
+def test_a_lost_low_part_breaks_the_bar(P, lost):
+    rng = np.random.default_rng(P)
+    C = rng.standard_normal((P, P))
+    x = rng.uniform(-1, 1, (2, 200)).astype(F)
+    T = [chebyshev.chebvander(v.astype(np.float64), P - 1) for v in x]
+    ref = np.einsum("sk,kl,sl->s", T[0], C, T[1])
+    part = lambda a: a.astype(np.float16).astype(np.float64)
+    A, B = (part(C), T[1]) if lost == "table" else (C, part(T[1]))
+    lossy = np.einsum("sk,kl,sl->s", T[0], A, B)
+    bar = _rms(_model_2d(C, *x) - ref)
+    assert bar <= 16 * 2.0 ** -24 * _rms(ref)
+    assert _rms(lossy - ref) > 50 * bar
