@@ -401,18 +401,19 @@ hpsmc_status hpsmc_set_initial_coeffs(hpsmc_plan *plan, const double *c0, int32_
  *   "sample_mfma"       1 (default): 2-D FP32 plans with P = n + 2 <= 32 and one
  *                       sample per lane run the path-advancing kernel with the
  *                       slab contraction of eq. ufg_ep1 on the matrix cores
- *                       (FP32 products for P < 17, from there two
- *                       half-precision parts per operand with FP32 sums, of
- *                       no larger error) -- the residual and Picard
+ *                       (FP32 products for P < 17, from there products of two
+ *                       half-precision parts per operand with FP32 sums, no
+ *                       further from 64 bits) -- the residual and Picard
  *                       forms, the centre-point and ball-point rules (plans of
  *                       the Picard form or the ball rule count as one sample
  *                       per lane); so do 5-D FP32 plans of the residual form
  *                       with the centre-point rule, P <= 12 and one sample per
  *                       lane (the innermost two modes of the contraction as
- *                       matrix-core products); 0: always on the vector units.
- *                       Same walks and exit steps either way; the FP32 sums
- *                       differ only by rounding order.  Changing it discards a
- *                       captured graph.
+ *                       matrix-core products: FP32 for P = 3, from P = 4 on
+ *                       two half-precision parts per operand likewise); 0:
+ *                       always on the vector units.  Same walks and exit steps
+ *                       either way; the values differ by rounding.  Changing
+ *                       it discards a captured graph.
  *   "sample_split"      1 (default): in a round of the 5-D matrix-core kernel
  *                       whose live paths fit in one pass of the grid at 64
  *                       paths per block, the block's two or four waves walk the

@@ -824,7 +824,7 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     sa.PP = plan->PP;
     sa.rows = (int32_t)rows;
     sa.slab_stride = stride;
-    if (mma_ok && (d == 5 || mma_split(plan->P))) {
+    if (mma_ok && (d == 5 ? mma5_split(plan->P) : mma_split(plan->P))) {
         sa.scale_parts = (int32_t)std::min<int64_t>(64, (rows * plan->P + 4095) / 4096);
         sa.pack_t = *std::max_element(deg.begin(), deg.end()) + 1;
         const size_t pk = NBLK * sa.pack_t * mstride;
@@ -1499,7 +1499,7 @@ static hpsmc_status slab_args_for(hpsmc_plan *plan, const NodeSet &set, int layo
     sa = set.slab;
     sa.slab_table = plan->slab_table;
     sa.layout = layout;
-    if (layout == 2) HIP_TRY(launch_coef_pack(sa, s));
+    if (layout == 2 && mma5_split(plan->P)) HIP_TRY(launch_coef_pack(sa, s));
     if (layout != 1 && !(cheb && layout == 0)) return HPSMC_OK;
     if (!plan->cu_ch) return fail(HPSMC_EINVAL, "no Chebyshev coefficient buffers for this slab layout");
     for (int32_t iv : set.ivs) {

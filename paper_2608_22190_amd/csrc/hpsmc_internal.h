@@ -256,9 +256,13 @@ constexpr int kMmaScaleExp = 14;
 // (k3, k4), k3 P + k4.  The rows f = k1 P + k2 < 32 A of each k0 fill A main tiles
 // per k0, k0-major; the B = P^2 - 32 A remaining rows of every k0 are gathered,
 // k0-major, into R tiles at the end, so every P in 3..12 wastes at most 3% of the
-// rows.  Entries past P^2 modes and past the last row are zero.
+// rows.  Entries past P^2 modes and past the last row are zero.  P = 3 (27 products a
+// path and table, and few modes to round) keeps FP32 entries, [table u, v][mode][row <
+// 32]: the parts were up to 2.6 times as far from 64 bits there as FP32 products.
+constexpr bool mma5_split(int P) { return P >= 4; }
 struct Mma5Geom {
     int P, NB, A, B, R, NCH;
+    int64_t table;   // floats of a chunk's u or v
     int64_t chunk;   // floats per chunk
     int64_t step;    // floats per step
 };
@@ -266,18 +270,20 @@ constexpr Mma5Geom mma5_geom(int P)
 {
     const int NB = (P * P + 7) / 8;
     const int A = P * P / 32, B = P * P - 32 * A, R = (B * P + 31) / 32;
-    return Mma5Geom{P, NB, A, B, R, P * A + R, (int64_t)512 * NB, (int64_t)(P * A + R) * 512 * NB};
+    const int64_t table = mma5_split(P) ? (int64_t)256 * NB : (int64_t)32 * ((P * P + 1) / 2 * 2);
+    return Mma5Geom{P, NB, A, B, R, P * A + R, table, 2 * table, (P * A + R) * 2 * table};
 }
-// Entry e of a step (one coefficient, [chunk][table][block][row][mode of the block]):
-// false for padding, else its table (0 u, 1 v), the flat index row4 = ((k0 P + k1) P +
-// k2) P + k3 of the first four modes, and k4. 
+// Entry e of a step (one coefficient, [chunk][table][block][row][mode of the block] or
+// [chunk][table][mode][row]): false for padding, else its table (0 u, 1 v), the flat index
+// row4 = ((k0 P + k1) P + k2) P + k3 of the first four modes, and k4.
 __host__ __device__ inline bool mma5_source(const Mma5Geom &g, int64_t e, int &uv, int64_t &row4, int &k4)
 {
     const int c = (int)(e / g.chunk);
     int r = (int)(e - (int64_t)c * g.chunk);
-    uv = r / (256 * g.NB);
-    r -= uv * 256 * g.NB;
-    const int i = (r >> 3) & 31, mode = 8 * (r >> 8) + (r & 7);
+    uv = r / (int)g.table;
+    r -= uv * (int)g.table;
+    const bool parts = mma5_split(g.P);
+    const int i = parts ? (r >> 3) & 31 : r & 31, mode = parts ? 8 * (r >> 8) + (r & 7) : r >> 5;
     if (mode >= g.P * g.P) return false;
     const int k3 = mode / g.P;
     k4 = mode - k3 * g.P;

@@ -16,8 +16,8 @@ namespace hpsmc {
 // + O(P^3) operations of a residual evaluation; it runs on the matrix cores in
 // 32-row tiles (the slab layout of mma5_geom) streamed through LDS.
 //
-// Both factors are split into two half-precision parts (as in the 2-D kernel, whose
-// operand layout it shares): a product of 32x32x16 takes eight modes, lanes 0-31
+// From P = 4 on both factors are split into two half-precision parts (as in the 2-D
+// kernel, whose operand layout it shares): a product of 32x32x16 takes eight modes, lanes 0-31
 // feeding part 0 of the B entries and lanes 32-63 part 1 against the same part of
 // the slab.  Paths 0-31 form product "A", paths 32-63 product "B".  The B entries are
 // formed and split once per step and stay in registers for all tiles: at P = 10, 50
@@ -27,8 +27,6 @@ namespace hpsmc {
 // against 64 bits (rms, of the FP32 products', random and smooth tables): 0.6 and 0.5 at
 // P = 4, 0.8 and 0.5 at 5, 0.75-0.8 at 6 and 7, 1.0 and 0.9 at 8, 0.75 and 0.65 at 10.
 // ===========================================================================
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 template <int P>
 __device__ __forceinline__ void legendre_row(float x, float (&L)[P])
 {
@@ -39,11 +37,13 @@ __device__ __forceinline__ void legendre_row(float x, float (&L)[P])
         L[k + 1] = (float)((2.0 * k + 1.0) / (k + 1.0)) * x * L[k] - (float)(k / (k + 1.0)) * L[k - 1];
 }
 
-// B operands: entries L_{k3}(x3) L_{k4}(x4) of the wave's 64 points, scaled by
-// bscale, in two parts, modes k3 P + k4 in pairs
+// B operands: entries L_{k3}(x3) L_{k4}(x4) of the wave's 64 points, modes k3 P + k4 in
+// pairs: scaled by bscale, in two parts; or in FP32, lanes 0-31 the even mode of a pair,
+// lanes 32-63 the odd one
 template <int P> struct Mma5B {
-    static constexpr int NB = mma5_geom(P).NB;
-    uint32_t r[4 * NB];
+    static constexpr bool SPLIT = mma5_split(P);
+    static constexpr int NB = mma5_geom(P).NB, NR = SPLIT ? 4 * NB : (P * P + 1) / 2;
+    uint32_t r[NR];
     __device__ __forceinline__ h16x8 block(int b) const
     {
         const u32x4 q = {r[4 * b], r[4 * b + 1], r[4 * b + 2], r[4 * b + 3]};
@@ -56,17 +56,23 @@ __device__ __forceinline__ void mma5_operands(float x3, float x4, float bscale, 
     float L3[P], L4[P];
     legendre_row<P>(x3, L3);
     legendre_row<P>(x4, L4);
+    if constexpr (Mma5B<P>::SPLIT) {
 #pragma unroll
-    for (int k = 0; k < P; ++k) L3[k] *= bscale;   // a power of two
+        for (int k = 0; k < P; ++k) L3[k] *= bscale;   // a power of two
+    }
     const float m1 = opaque_minus_one();
 #pragma unroll
-    for (int i = 0; i < 4 * Mma5B<P>::NB; ++i) {
+    for (int i = 0; i < Mma5B<P>::NR; ++i) {
         bA.r[i] = 0u;
         bB.r[i] = 0u;
         if (2 * i < P * P) {
             const int m0 = 2 * i, n0 = 2 * i + 1 < P * P ? 2 * i + 1 : 2 * i;
             const float e0 = L3[m0 / P] * L4[m0 % P], e1 = n0 > m0 ? L3[n0 / P] * L4[n0 % P] : 0.f;
-            const uint32_t h = pack_h16(e0, e1), l = pack_h16_rest(e0, e1, h, m1);
+            uint32_t h = __float_as_uint(e0), l = __float_as_uint(e1);
+            if constexpr (Mma5B<P>::SPLIT) {
+                h = pack_h16(e0, e1);
+                l = pack_h16_rest(e0, e1, h, m1);
+            }
             const auto r = __builtin_amdgcn_permlane32_swap(h, l, false, false);
             bA.r[i] = r[0];
             bB.r[i] = r[1];
@@ -84,9 +90,20 @@ __device__ __forceinline__ void mma5_tile(const u32x4 *S, int lane, const Mma5B<
                                           int nparts, f32x16 &dA, f32x16 &dB)
 {
     constexpr int NB = mma5_geom(P).NB, N = 2 * NB;
-    const u32x4 *A = S + (lane & 31);
     dA = f32x16{};
     dB = f32x16{};
+    if constexpr (!Mma5B<P>::SPLIT) {   // FP32 products of a pair of modes each
+        const float *A = (const float *)S + lane;   // mode 2 i + lane / 32, row lane % 32
+#pragma unroll
+        for (int i = 0; i < Mma5B<P>::NR; ++i) {
+            if (!PARTS || i % nparts == part) {
+                dA = __builtin_amdgcn_mfma_f32_32x32x2f32(A[64 * i], __uint_as_float(bA.r[i]), dA, 0, 0, 0);
+                dB = __builtin_amdgcn_mfma_f32_32x32x2f32(A[64 * i], __uint_as_float(bB.r[i]), dB, 0, 0, 0);
+            }
+        }
+        return;
+    }
+    const u32x4 *A = S + (lane & 31);
     // operand n: block n % NB of part 1 (n < NB), then of part 0
     auto addr = [](int n) { return ((n < NB ? NB : 0) + n % NB) * 32; };
     u32x4 x[2];
@@ -165,7 +182,7 @@ template <int P>
 __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
 {
     constexpr Mma5Geom g5 = mma5_geom(P);
-    constexpr int A = g5.A, R = g5.R, NCH = g5.NCH, TV = 64 * g5.NB;   // TV: 16-byte vectors of a tile's table
+    constexpr int A = g5.A, R = g5.R, NCH = g5.NCH, TV = (int)g5.table / 4;   // TV: 16-byte vectors of a tile's table
     constexpr int CF = (int)g5.chunk, CV = CF / 4;   // floats, 16-byte vectors per chunk
     extern __shared__ u32x4 lds[];
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wave = tid >> 6;
@@ -210,7 +227,11 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
         const uint32_t c3 = G->c3 | (uint32_t)a.tag;
         const int64_t live = a.round == 0 ? (int64_t)G->node_count * a.mcount : (int64_t)a.live_in[g];
         const float *gtab = (const float *)a.slab_table + G->slab_mma;
-        const float iu = a.inv_scale[2 * G->blk], iv = a.inv_scale[2 * G->blk + 1];
+        float iu = 1.f, iv = 1.f;
+        if constexpr (Mma5B<P>::SPLIT) {
+            iu = a.inv_scale[2 * G->blk];
+            iv = a.inv_scale[2 * G->blk + 1];
+        }
 
         // ---- this lane's path
         const int64_t p = b * bsz + (split ? lane : tid);

@@ -408,6 +408,7 @@ __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
     const int nq = a.nstar[g] + a.extra;
     const int T1 = a.deg[g] + 1;
     const bool mma = a.layout == 1;
+    const Mma5Geom g5 = mma5_geom(a.P);
     const int64_t stride = a.layout ? a.mma_stride : a.slab_stride;
     const int64_t base = a.layout ? a.slab_off_mma[g] : a.slab_off[g];
     T *table = (T *)a.slab_table;
@@ -432,18 +433,23 @@ __global__ void __launch_bounds__(256) slab_kernel(SlabArgs a)
         for (int64_t e = threadIdx.x; e < stride; e += blockDim.x) {
             int64_t row = 0;
             int uv = 0, kl = 0;
-            if (mma) {   // column c = uv * PP + k1 of kMmaRows rows k0
-                const int c = (int)(e / kMmaRows);
-                row = e - (int64_t)c * kMmaRows;
-                uv = c / a.PP;
-                kl = c - uv * a.PP;
+            bool live;
+            if (a.layout == 2) {   // 32-row tiles over (k0, k1, k2), columns (k3, k4)
+                live = mma5_source(g5, e, uv, row, kl);
             } else {
-                row = e / (2 * a.PP);
-                const int rem = (int)(e - row * 2 * a.PP);
-                uv = rem / a.PP;
-                kl = rem - uv * a.PP;
+                if (mma) {   // column c = uv * PP + k1 of kMmaRows rows k0
+                    const int c = (int)(e / kMmaRows);
+                    row = e - (int64_t)c * kMmaRows;
+                    uv = c / a.PP;
+                    kl = c - uv * a.PP;
+                } else {
+                    row = e / (2 * a.PP);
+                    const int rem = (int)(e - row * 2 * a.PP);
+                    uv = rem / a.PP;
+                    kl = rem - uv * a.PP;
+                }
+                live = kl < a.P && row < a.rows;
             }
-            const bool live = kl < a.P && row < a.rows;
             double acc[kSlabQ];
 #pragma unroll
             for (int j = 0; j < kSlabQ; ++j) acc[j] = 0.0;
@@ -543,7 +549,7 @@ __global__ void __launch_bounds__(256) slab_split_kernel(SlabArgs a, int parts)
 hipError_t launch_slabs(const SlabArgs &a, int fp32, int max_nstar, hipStream_t s)
 {
     if (a.n_groups <= 0) return hipSuccess;
-    if (a.layout == 2 || (a.layout == 1 && mma_split(a.P))) {
+    if ((a.layout == 2 && mma5_split(a.P)) || (a.layout == 1 && mma_split(a.P))) {
         const int64_t parts = (a.mma_stride / 2 + kSplitPairs - 1) / kSplitPairs;
         const int64_t chunks = std::min<int64_t>((max_nstar + a.extra + kSplitQ - 1) / kSplitQ, std::max<int64_t>(1, (1 << 22) / parts));
         const dim3 sg((unsigned)(parts * chunks), (unsigned)std::min<int64_t>(a.n_groups, kGridYZ),

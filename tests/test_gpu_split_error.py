@@ -148,6 +148,7 @@ def _rms(e):
 
 CASES = ([(2, n, kind, est, 8, 4, 400) for n in (15, 16, 18, 24, 30) for kind, est in
           (("random", "residual"), ("smooth", "residual"), ("smooth", "picard"))] +
+         [(5, 1, "smooth", "residual", 400, 3, 1), (5, 1, "random", "residual", 400, 3, 1)] +
          [(5, n, kind, "residual", inst, 2, pts) for n, inst, pts in ((2, 40, 32), (3, 8, 243), (5, 4, 500), (6, 6, 400), (8, 2, 256))
           for kind in ("random", "smooth")])
 
