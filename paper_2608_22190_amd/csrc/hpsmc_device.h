@@ -761,6 +761,22 @@ template <typename T, int D> struct PathState {
     T acc, comp;
     uint32_t node;     // node row in the set's node array
     uint32_t sample;
+    // a sum in FP64: the two FP32 fields hold its words
+    __device__ __forceinline__ void put_sum(double s)
+    {
+        if constexpr (sizeof(T) == 8) {
+            acc = s;
+            comp = (T)0;
+        } else {
+            acc = __int_as_float(__double2hiint(s));
+            comp = __int_as_float(__double2loint(s));
+        }
+    }
+    __device__ __forceinline__ double sum() const
+    {
+        if constexpr (sizeof(T) == 8) return acc;
+        else return __hiloint2double(__float_as_int(acc), __float_as_int(comp));
+    }
 };
 
 // The next work item of this block, in [0, total), or total.  The first one
@@ -800,43 +816,105 @@ __device__ __forceinline__ void add_stats(const RoundArgs &a, unsigned long long
     }
 }
 
+// Path sums (eq. interIQ) of the round kernels that split rounds: FP64, by windows of
+// W steps, each window's sum added to the path's in step order.  A window
+// belongs to one block, so the order, and with it a path's value, is the same
+// however a round is split.  (FP64 for FP32 residuals too: a conversion and an fma are
+// less than a compensated FP32 sum.)  The sums stand in LDS, touched once a window.
+template <int NS, int W> struct PathSums {
+    double w[NS];      // the open window
+    bool open[NS];     // it holds something
+    double *lds;       // the block's sums
+    double *base;      // shares: the batch's windows in share_val
+    int stride, bsz, slot;
+    __device__ __forceinline__ void start(double *lds_, const RoundArgs &a, int64_t batch, int bsz_, int slot_, int nthr)
+    {
+        lds = lds_;
+        stride = nthr;
+        bsz = bsz_;
+        slot = slot_;
+        base = a.share_val + batch * a.share_rows * bsz;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) { w[s] = 0.0; open[s] = false; acc(s) = 0.0; }
+    }
+    __device__ __forceinline__ double &acc(int s) const { return lds[s * stride + (int)threadIdx.x]; }
+    // window k of the path, or the round's last row: the end of the Picard form
+    __device__ __forceinline__ double &val(int k, int s) const { return (base + (int64_t)k * bsz)[slot + s * stride]; }
+    __device__ __forceinline__ void add(int s, double delta, double r)
+    {
+        w[s] = fma(delta, r, w[s]);
+        open[s] = true;
+    }
+    __device__ __forceinline__ static bool last(int k) { return k % W == W - 1; }   // step k of the round
+    __device__ __forceinline__ static int next(int k, int shares)   // the step that a share evaluates after it
+    {
+        return last(k) ? k + 1 + (shares - 1) * W : k + 1;
+    }
+    // the window of step k is over
+    __device__ __forceinline__ void close(int k, int shares)
+    {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (open[s]) {
+                if (shares > 1) val(k / W, s) = w[s];
+                else acc(s) += w[s];
+                w[s] = 0.0;
+                open[s] = false;
+            }
+        }
+    }
+};
 // A round of few batches is split into shares: `shares` blocks walk the same
 // batch through the whole round (positions cost little next to a residual
-// evaluation and do not depend on one), share i evaluates steps q0 + i, q0 + i +
-// shares, ..., and the block that finishes last adds the shares' parts of every
-// path sum in share order and alone writes results and survivors.  (Such rounds
-// ran at the latency of one evaluation after another in a few blocks: the last
-// two thirds of the rounds of the long-time plane problem took 0.6 ms for 256
-// steps however few paths were left.)
-// Returns whether this block is the last; sum[] (this thread's parts, of the paths at
-// slot + i stride of the batch) are then the whole.  writer: the thread's parts
-// count (where several waves hold the same paths).  Called by every thread of the block.
-template <int N>
-__device__ __forceinline__ bool share_combine(const RoundArgs &a, int64_t item, int64_t batch, int shares, int bsz,
-                                              int slot, int stride, bool writer, double (&sum)[N], long long &s_flag)
+// evaluation and do not depend on one), share i evaluates windows i, i +
+// shares, ... of it and stores their sums, and the block that finishes last adds them
+// to the paths' and alone writes results and survivors.  (Such rounds ran at the
+// latency of one evaluation after another in a few blocks: the last two thirds of
+// the rounds of the long-time plane problem took 0.6 ms for 256 steps however few
+// paths were left.)
+// Whether this block is the last of its batch, the other shares' sums then visible.
+// Called by every thread of the block.
+__device__ __forceinline__ bool share_last(const RoundArgs &a, int64_t batch, int shares, long long &s_flag)
 {
-    double *part = a.share_sum + item * bsz + slot;
-    if (writer) {
-#pragma unroll
-        for (int n = 0; n < N; ++n) __hip_atomic_store(part + n * stride, sum[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
     __threadfence();
     __syncthreads();
     if (threadIdx.x == 0) s_flag = (long long)atomicAdd(a.share_done + batch, 1u);
     __syncthreads();
     if (s_flag != (long long)shares - 1) return false;
     __threadfence();
-    if (writer) {
-        part = a.share_sum + batch * shares * bsz + slot;
+    return true;
+}
+
+// The windows of this thread's paths, len[s] steps of path s, into their sums.  Bound by the
+// latency of reads that other chiplets wrote: 32 registers of them in flight.
+template <int NS, int W>
+__device__ __forceinline__ void share_fold(PathSums<NS, W> &ps, const int (&len)[NS])
+{
+    constexpr int N = 16 / NS;
+    int n[NS], most = 0;
+    double t[NS];
 #pragma unroll
-        for (int n = 0; n < N; ++n) {
-            double t = 0.0;
-            for (int i = 0; i < shares; ++i)
-                t += __hip_atomic_load(part + (int64_t)i * bsz + n * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            sum[n] = t;
+    for (int s = 0; s < NS; ++s) {
+        n[s] = (len[s] + W - 1) / W;
+        most = max(most, n[s]);
+        t[s] = ps.acc(s);
+    }
+    for (int k = 0; k < most; k += N) {
+        double v[N][NS];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) v[j][s] = ps.val(max(min(k + j, n[s] - 1), 0), s);
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                if (k + j < n[s]) t[s] += v[j][s];
         }
     }
-    return true;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) ps.acc(s) = t[s];
 }
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));

@@ -313,8 +313,12 @@ static double phi_legendre(int p, const double *L) { return 2.0 * (p + 1) / (2.0
 // ---------------------------------------------------------------------------
 // Plan
 // ---------------------------------------------------------------------------
-// paths of the largest batch: 256 threads, four paths each
+// rounds split into shares of steps: paths of the largest batch (256 threads, four paths
+// each), and bytes for the window sums of a round at most: 384 batches of 512 paths and 256
+// steps, the most that are split at the launch shapes in use, take 102 MB; five dimensions,
+// with a sum a step, 68 MB at 512 batches of 256 paths and 64 steps
 constexpr int kShareBatch = 1024;
+constexpr int64_t kShareBytes = (int64_t)1 << 27;
 
 struct DevBuf {
     void *p = nullptr;
@@ -429,10 +433,10 @@ struct hpsmc_plan {
     double *part = nullptr;
     int64_t part_elems = 0;
     double *lat_table = nullptr;             // lattice form: residuals of one round
-    // rounds of few batches, split into shares of steps: [share_max][kShareBatch] part sums, [share_max] counters
-    double *share_sum = nullptr;
+    // rounds of few batches, split into shares of steps: share_cap window sums, [share_max] counters
+    double *share_val = nullptr;
     uint32_t *share_done = nullptr;
-    int64_t share_max = 0;
+    int64_t share_max = 0, share_cap = 0;
     unsigned long long *counters = nullptr;  // [kCounterWords]: the work counter, then the statistics
     unsigned long long *maxbits = nullptr;   // [4096]
     int64_t m_probe = 0;
@@ -1421,7 +1425,7 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
     // repeated walks weigh more, got 2% slower)
     const int64_t share_grid = mma ? blocks : std::max<int64_t>(blocks, 3 * (int64_t)plan->cus);
     const int64_t share_max = k1d || plan->frac ? 0 : std::min<int64_t>(share_grid, plan->share_max);
-    a.share_sum = plan->share_sum;
+    a.share_val = plan->share_val;
     a.share_done = plan->share_done;
     hpsmc_plan::EvPair *ek = next_pair(plan->ev_span, plan->n_span);
     if (ek) HIP_TRY(hipEventRecord(ek->a, s));
@@ -1436,8 +1440,10 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
             a.state_out = set.state[(r + 1) & 1];
             a.live_in = live + (r & 1) * G;
             a.live_out = live + ((r + 1) & 1) * G;
-            HIP_TRY(launch_round_prep(a.groups, G, r, C, mc, a.batch, split_batch, split_max, share_max, a.live_in,
-                                      a.live_out, const_cast<int64_t *>(a.batch_prefix), plan->share_done,
+            const int W = window_steps(plan->d);
+            a.share_rows = (std::min(C, set.max_nstar - r * C) + W - 1) / W + 1;
+            HIP_TRY(launch_round_prep(a.groups, G, r, C, mc, a.batch, split_batch, split_max, share_max, plan->share_cap,
+                                      a.share_rows, std::min(kMaxShares, a.share_rows - 1), a.live_in, a.live_out, const_cast<int64_t *>(a.batch_prefix), plan->share_done,
                                       plan->counters, s));
             hpsmc_plan::EvPair *ea = next_pair(plan->ev_sample, plan->n_sample);
             if (ea) HIP_TRY(hipEventRecord(ea->a, s));
@@ -1607,7 +1613,7 @@ void hpsmc_destroy(hpsmc_plan *plan)
     void *ptrs[] = {plan->U, plan->cu, plan->cv, plan->tmp0, plan->tmp1, plan->ic, plan->mats,
                     plan->slab_table, plan->part, plan->counters, plan->maxbits, plan->hist_u, plan->hist_v,
                     plan->lam, plan->cbar_u, plan->cbar_v, plan->cbar_part, plan->dtarget, plan->dloss, plan->dgrad, plan->slab_bar,
-                    plan->frac_tab, plan->src_poly, plan->cu_ch, plan->cv_ch, plan->cs_ch, plan->share_sum, plan->lat_table};
+                    plan->frac_tab, plan->src_poly, plan->cu_ch, plan->cv_ch, plan->cs_ch, plan->share_val, plan->share_done, plan->lat_table};
     for (void *p : ptrs) dfree(plan, p);
     delete plan;
 }
@@ -1707,8 +1713,7 @@ hpsmc_status hpsmc_create(const hpsmc_problem *pb, hpsmc_plan **out)
     if (!plan->frac && !advance_1d_eligible(plan->d, plan->P, pb->estimator == HPSMC_EST_PICARD,
                                             pb->quad == HPSMC_QUAD_BALL, 0, 1)) {
         plan->share_max = 4 * (int64_t)plan->cus;
-        if ((st = dalloc(pl, (void **)&pl->share_sum, (size_t)plan->share_max * (kShareBatch * 8 + 4)))) return st;
-        plan->share_done = (uint32_t *)(plan->share_sum + plan->share_max * kShareBatch);
+        if ((st = dalloc(pl, (void **)&pl->share_done, (size_t)plan->share_max * 4))) return st;
     }
     if ((st = dalloc(pl, (void **)&pl->counters, kCounterWords * 8))) return st;
     if ((st = dalloc(pl, (void **)&pl->maxbits, 4096 * 8))) return st;
@@ -1843,6 +1848,18 @@ hpsmc_status hpsmc_create(const hpsmc_problem *pb, hpsmc_plan **out)
     }
     if (lat_max > 0 && (st = dalloc(pl, (void **)&pl->lat_table, (size_t)lat_max * 8))) return st;
     for (auto &s : plan->sets) { slab_max = std::max(slab_max, s.slab_elems); nmax = std::max(nmax, s.n); }
+    if (plan->share_max > 0) {
+        // the window sums of the rounds that are split, over the sets: at most share_max / 2 batches (each group's
+        // last one not full) of at most 512 steps
+        for (auto &s : plan->sets) {
+            if (!s.rounds) continue;
+            const int64_t paths = std::min<int64_t>(plan->share_max / 2 * kShareBatch,
+                                                    s.n * s.ms + (int64_t)s.ghost.size() * kShareBatch);
+            const int64_t rows = (std::min(s.max_nstar, 512) + window_steps(plan->d) - 1) / window_steps(plan->d) + 1;
+            plan->share_cap = std::max(plan->share_cap, std::min<int64_t>(kShareBytes / 8, paths * rows));
+        }
+        if (plan->share_cap > 0 && (st = dalloc(pl, (void **)&pl->share_val, (size_t)plan->share_cap * 8))) return st;
+    }
     plan->slab_bytes = (size_t)slab_max * (plan->fp32 ? 4 : 8);
     if ((st = dalloc(pl, &pl->slab_table, plan->slab_bytes))) return st;
     plan->part_elems = nmax * ((pb->M + 63) / 64) * 2;
@@ -2863,7 +2880,7 @@ static hpsmc_status adjoint_sampling(hpsmc_plan *plan, NodeSet &set, int tag, hi
             a.live_in = set.live + (r & 1) * G;
             a.live_out = set.live + ((r + 1) & 1) * G;
             HIP_TRY(launch_round_prep(set.gdev, G, r, C, mc, a.batch, 0, 0, std::min<int64_t>(blocks, plan->share_max),
-                                      a.live_in, a.live_out, set.prefix, plan->share_done, plan->counters, s));
+                                      INT64_MAX, 0, std::min(kMaxShares, C), a.live_in, a.live_out, set.prefix, plan->share_done, plan->counters, s));
             hpsmc_plan::EvPair *ea = next_pair(plan->ev_adj, plan->n_adj);
             if (ea) HIP_TRY(hipEventRecord(ea->a, s));
             HIP_TRY(launch_adjoint(aa, plan->fp32, waves, blocks, lds, s));

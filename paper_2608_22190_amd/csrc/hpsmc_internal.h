@@ -106,7 +106,8 @@ struct RoundArgs {
     uint32_t *live_out;          // per group, survivors appended to state_out
     const int64_t *batch_prefix; // [n_groups + 3] batches per group, prefix ([n_groups]: work items, batches
                                  // times shares); [n_groups + 1] paths per batch; [n_groups + 2] shares
-    double *share_sum;           // [work item][path of the batch] each share's part of the path sums
+    double *share_val;           // [batch][window of the round, then the end][path of the batch] sums
+    int32_t share_rows;          // windows of the round and one
     uint32_t *share_done;        // [batch] shares that have written theirs
     double *result;              // [node out][mcount] path value S of each sample
     int32_t n_chunks;            // LDS chunks per slab: P^cf, the first cf dimensions fixed per chunk
@@ -208,11 +209,17 @@ hipError_t launch_eval(const double *cu, const double *cv, int dim, int P, int T
 // most split_max items of batch_split paths use that batch (the 5-D
 // matrix-core kernel then splits each item's products over the block's waves);
 // share_max > 0: a round of few batches is split into shares of steps while
-// batches times shares stay within share_max (share_done: its batch counters)
+// batches times shares stay within share_max (share_done: its batch counters) and
+// batches times rows times paths of a batch within share_cap, at most max_shares
 constexpr int kMaxShares = 16;
+// steps of a path sum's windows (divisors of 4, as rounds are multiples of 4).  Longer ones
+// are fewer sums to store and add: a step each took 0.89 of the speed of unordered sums in
+// the plane solve, four 0.97; in five dimensions, with rounds of 16 steps of 10^5 products,
+// four leave too few to share out (138 -> 183 ms)
+constexpr int window_steps(int dim) { return dim >= 4 ? 1 : 4; }
 hipError_t launch_round_prep(const GroupDesc *groups, int32_t n_groups, int32_t round, int32_t steps,
                              int64_t mcount, int32_t batch, int32_t batch_split, int64_t split_max, int64_t share_max,
-                             const uint32_t *live_in, uint32_t *live_out, int64_t *batch_prefix, uint32_t *share_done,
+                             int64_t share_cap, int32_t rows, int32_t max_shares, const uint32_t *live_in, uint32_t *live_out, int64_t *batch_prefix, uint32_t *share_done,
                              unsigned long long *work, hipStream_t s);
 // kern: 0 the vector-unit kernel, 1 the 2-D matrix-core kernel, 2 the 5-D one,
 // 3 the windowed 1-D kernel

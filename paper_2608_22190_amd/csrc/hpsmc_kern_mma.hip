@@ -26,6 +26,8 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
     __shared__ long long s_item;
     __shared__ SrcTime<float> s_tf[256];   // source time factors of a window of blockDim.x steps
+    __shared__ double s_acc[256];          // path sums
+    __shared__ uint16_t s_len[256];        // shares: the steps each path takes in the round
     constexpr int mvec = MmaB<KH>::VECS;                 // 16-byte vectors per LDS buffer (slab image)
     constexpr int svec = PIC ? mvec / 2 : mvec;         // of which staged: the Picard form reads the u table only
     cptr<GroupDesc> groups = as_const(a.groups);
@@ -69,7 +71,10 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
         const bool began = p < live;
         bool alive = began;
         uint32_t node = 0, sample = 0, c0 = 0;
-        float x0 = 0.f, x1 = 0.f, acc = 0.f, comp = 0.f;
+        float x0 = 0.f, x1 = 0.f;
+        using Sums = PathSums<1, window_steps(2)>;
+        Sums ps;
+        ps.start(s_acc, a, batch, a.batch, tid, nthr);
         if (alive) {
             if (a.round == 0) {
                 node = (uint32_t)(G->node_begin + p / a.mcount);
@@ -80,20 +85,20 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                 const State st = sin[G->path_off + p];
                 x0 = st.x[0];
                 x1 = st.x[1];
-                acc = st.acc;
-                comp = st.comp;
+                ps.acc(0) = st.sum();
                 node = st.node;
                 sample = st.sample;
-                if (share != 0) { acc = 0.f; comp = 0.f; }
             }
             c0 = nodes[node].c0;
         }
+        if (shares > 1) s_len[tid] = (uint16_t)(alive ? q1 - q0 : 0);
         auto fill_time = [&](int qs) {
             const int qq = qs + tid;
             if (qq < q1) s_tf[tid] = source_time<float>(a.phys, (float)(t_prev + (span - (double)qq * ddelta)));
         };
         fill_time(q0);
-        int qe = q0 + share;   // the next step this share evaluates
+        int qe = q0 + share * window_steps(2);   // the next step this share evaluates
+        bool drawn = share == 0;         // its operands were formed one step ahead
         if (qe < q1) mma_stage((const u32x4 *)(gtab + (int64_t)qe * a.slab_stride), lds, svec, tid, nthr);
         float ex0 = x0, ex1 = x1;   // where the current step's integrand is evaluated
         if constexpr (BALL) {
@@ -128,13 +133,14 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                     const float y0 = fmaf(J, d0, x0), y1 = fmaf(J, d1, x1);
                     alive = fabsf(y0) < 1.f && fabsf(y1) < 1.f;
                     if (alive) { x0 = y0; x1 = y1; }
+                    else s_len[tid] = (uint16_t)(q - q0);
                 }
                 continue;
             }
-            qe += shares;
+            qe = q0 + Sums::next(q - q0, shares);
             if (qe < q1)
                 mma_stage((const u32x4 *)(gtab + (int64_t)qe * a.slab_stride), lds + (buf ^ 1) * mvec, svec, tid, nthr);
-            if (shares > 1) {   // the operands of this step's point were not drawn one step ahead
+            if (!drawn) {
                 ex0 = x0;
                 ex1 = x1;
                 if constexpr (BALL) {
@@ -148,6 +154,7 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                 mma_operands<KH>(ex1, a.P, a.bscale, b0, b1);
             }
             float u = 0.f, v = 0.f, y0 = x0, y1 = x1, nx0 = x0, nx1 = x1;
+            drawn = qe == q + 1;
             bool inside = false;
             if (__ballot(alive) != 0ull) {
                 f32x16 du0, dv0, du1, dv1;
@@ -161,7 +168,7 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                 nx0 = y0;
                 nx1 = y1;
                 if constexpr (BALL) {
-                    if (alive && inside && qe == q + 1 && qe < q1) {
+                    if (alive && inside && drawn && qe < q1) {
                         float off[2];
                         ball_offset<float, 2>(c0, sample, q + 1, c3, a.key0, a.key1, off);
                         nx0 = fmaf(J, off[0], y0);
@@ -169,7 +176,7 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                     }
                 }
                 MmaB<KH> nb0 = b0, nb1 = b1;
-                if (shares == 1) mma_operands<KH>(nx1, a.P, a.bscale, nb0, nb1);
+                if (drawn) mma_operands<KH>(nx1, a.P, a.bscale, nb0, nb1);
                 mma_epilogue<KH, PIC>(du0, dv0, du1, dv1, ex0, u, v);
                 if constexpr (MmaB<KH>::SPLIT) {
                     u *= iu;
@@ -181,13 +188,8 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
             if (alive) {
                 if (inside) {   // residual at X_q (or its ball point), time tau_q = t_{n,l} - q Delta
                     const float X[2] = {ex0, ex1};
-                    const float r = f_of<float>(a.phys, u) + source_space<float, 2, !BALL>(a.phys, X, s_tf[tslot]) +
-                                    (PIC ? 0.f : v);
-                    const float y = delta * r;
-                    const float yc = y - comp;
-                    const float tt = acc + yc;
-                    comp = (tt - acc) - yc;
-                    acc = tt;
+                    const float r = f_of<float>(a.phys, u) + source_space<float, 2, !BALL>(a.phys, X, s_tf[tslot]) + (PIC ? 0.f : v);
+                    ps.add(0, (double)delta, (double)r);
                     x0 = y0;
                     x1 = y1;
                     ex0 = nx0;
@@ -195,11 +197,17 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                     ++evals;
                 } else {        // path ended: L = q
                     alive = false;
+                    if (shares > 1) s_len[tid] = (uint16_t)(q - q0);
                 }
             }
             buf ^= 1;
             mma_stage_wait();
-            if (__syncthreads_or(alive ? 1 : 0) == 0) { ++q; break; }
+            if (Sums::last(q - q0) || q + 1 == q1) ps.close(q - q0, shares);   // its store after the wait
+            if (__syncthreads_or(alive ? 1 : 0) == 0) {
+                ps.close(q - q0, shares);
+                ++q;
+                break;
+            }
         }
 
         // ---- Picard form (eq. uast): a path still inside after all N* steps adds
@@ -219,24 +227,22 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                     mma_epilogue<KH, true>(du0, dv0, du1, dv1, x0, u, v);
                     if constexpr (MmaB<KH>::SPLIT) u *= iu;
                     if (alive) {
-                        const float yc = u - comp;
-                        const float tt = acc + yc;
-                        comp = (tt - acc) - yc;
-                        acc = tt;
+                        if (shares == 1) ps.acc(0) += (double)u;
+                        else ps.val(a.share_rows - 1, 0) = (double)u;
                     }
                 }
             }
         }
 
-        // ---- paths ended in this round or at N*, and those carried to the next round
-        double sum[1] = {(double)acc - (double)comp};
         if (shares > 1) {
-            if (!share_combine<1>(a, item, batch, shares, a.batch, tid, 0, true, sum, s_item)) continue;
-            acc = (float)sum[0];
-            comp = (float)((double)acc - sum[0]);
+            if (!share_last(a, batch, shares, s_item)) continue;
+            const int len[1] = {s_len[tid]};
+            share_fold(ps, len);
+            if (PIC && q1 == nstar && alive) ps.acc(0) += ps.val(a.share_rows - 1, 0);
         }
+        // ---- paths ended in this round or at N*, and those carried to the next round
         const bool carry = alive && q1 < nstar;
-        if (began && !carry) a.result[(int64_t)nodes[node].out * a.mcount + (sample - a.m0)] = sum[0];
+        if (began && !carry) a.result[(int64_t)nodes[node].out * a.mcount + (sample - a.m0)] = ps.acc(0);
         const unsigned long long mask = __ballot(carry);
         if (mask != 0ull) {
             uint32_t base = 0;
@@ -247,8 +253,7 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                 State st;
                 st.x[0] = x0;
                 st.x[1] = x1;
-                st.acc = acc;
-                st.comp = comp;
+                st.put_sum(ps.acc(0));
                 st.node = node;
                 st.sample = sample;
                 sout[G->path_off + off] = st;

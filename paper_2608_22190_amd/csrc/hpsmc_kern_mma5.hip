@@ -188,6 +188,8 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wave = tid >> 6;
     __shared__ long long s_item;
     __shared__ SrcTime<float> s_tf[256];   // source time factors of a window of blockDim.x steps
+    __shared__ double s_acc[256];          // path sums
+    __shared__ uint16_t s_len[256];        // shares: the steps each path takes in the round
     __shared__ float s_red[2][4][64];      // sparse rounds: each wave's share of u and v
     cptr<GroupDesc> groups = as_const(a.groups);
     cptr<NodeDesc> nodes = as_const(a.nodes);
@@ -238,7 +240,10 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
         const bool began = p < live;
         bool alive = began;
         uint32_t node = 0, sample = 0, c0 = 0;
-        float X[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, acc = 0.f, comp = 0.f;
+        float X[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+        using Sums = PathSums<1, window_steps(5)>;
+        Sums ps;
+        ps.start(s_acc, a, batch, bsz, split ? lane : tid, nthr);
         if (alive) {
             if (a.round == 0) {
                 node = (uint32_t)(G->node_begin + p / a.mcount);
@@ -249,21 +254,20 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
                 const State st = sin[G->path_off + p];
 #pragma unroll
                 for (int i = 0; i < 5; ++i) X[i] = st.x[i];
-                acc = st.acc;
-                comp = st.comp;
+                ps.acc(0) = st.sum();
                 node = st.node;
                 sample = st.sample;
-                if (share != 0) { acc = 0.f; comp = 0.f; }
             }
             c0 = nodes[node].c0;
         }
+        if (shares > 1) s_len[tid] = (uint16_t)(alive ? q1 - q0 : 0);
         auto fill_time = [&](int qs) {
             const int qq = qs + tid;
             if (qq < q1) s_tf[tid] = source_time<float>(a.phys, (float)(t_prev + (span - (double)qq * ddelta)));
         };
         fill_time(q0);
         // chunk 0 of the first evaluated step into buffer 0; buf: the buffer of the current chunk
-        int qe = q0 + share;   // the next step this share evaluates
+        int qe = q0 + share * window_steps(5);   // the next step this share evaluates
         if (qe < q1) mma_stage((const u32x4 *)(gtab + (int64_t)qe * a.slab_stride), lds, CV, tid, nthr);
         mma_stage_wait();
         __syncthreads();
@@ -288,6 +292,7 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
                     inside = inside && (fabsf(Y[i]) < 1.f);
                 }
                 alive = inside;   // else the path ended: L = q
+                if (shares > 1 && !inside) s_len[tid] = (uint16_t)(q - q0);
             }
             if (writer && share == 0) ++slots;
             if (q != qe) {   // another share's step: the walk alone
@@ -297,7 +302,7 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
                 }
                 continue;
             }
-            qe += shares;
+            qe = q0 + Sums::next(q - q0, shares);
             // ---- u and v at X_q: the step's chunks, the next one always in flight
             const bool wave_live = __ballot(alive) != 0ull;
             Mma5B<P> bA, bB;
@@ -393,27 +398,27 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
             v *= iv;
             if (alive) {   // residual at X_q, time tau_q = t_{n,l} - q Delta
                 const float r = f_of<float>(a.phys, u) + source_space<float, 5>(a.phys, X, s_tf[tslot]) + v;
-                const float y = delta * r;
-                const float yc = y - comp;
-                const float tt = acc + yc;
-                comp = (tt - acc) - yc;
-                acc = tt;
+                if (writer) ps.add(0, (double)delta, (double)r);
 #pragma unroll
                 for (int i = 0; i < 5; ++i) X[i] = Y[i];
                 if (writer) ++evals;
             }
-            if (__syncthreads_or(alive ? 1 : 0) == 0) { ++q; break; }
+            if (Sums::last(q - q0) || q + 1 == q1) ps.close(q - q0, shares);
+            if (__syncthreads_or(alive ? 1 : 0) == 0) {
+                ps.close(q - q0, shares);
+                ++q;
+                break;
+            }
         }
 
         // ---- paths ended in this round or at N*, and those carried to the next round
-        double sum[1] = {(double)acc - (double)comp};
         if (shares > 1) {
-            if (!share_combine<1>(a, item, batch, shares, bsz, split ? lane : tid, 0, writer, sum, s_item)) continue;
-            acc = (float)sum[0];
-            comp = (float)((double)acc - sum[0]);
+            if (!share_last(a, batch, shares, s_item)) continue;
+            const int len[1] = {writer ? s_len[tid] : 0};
+            share_fold(ps, len);
         }
         const bool carry = writer && alive && q1 < nstar;
-        if (writer && began && !carry) a.result[(int64_t)nodes[node].out * a.mcount + (sample - a.m0)] = sum[0];
+        if (writer && began && !carry) a.result[(int64_t)nodes[node].out * a.mcount + (sample - a.m0)] = ps.acc(0);
         const unsigned long long mask = __ballot(carry);
         if (mask != 0ull) {
             uint32_t base = 0;
@@ -424,8 +429,7 @@ __device__ __forceinline__ void advance_mma5_body(const RoundArgs &a)
                 State st;
 #pragma unroll
                 for (int i = 0; i < 5; ++i) st.x[i] = X[i];
-                st.acc = acc;
-                st.comp = comp;
+                st.put_sum(ps.acc(0));
                 st.node = node;
                 st.sample = sample;
                 sout[G->path_off + off] = st;

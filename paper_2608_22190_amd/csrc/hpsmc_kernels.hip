@@ -840,7 +840,8 @@ size_t path_state_bytes(int fp32, int dim)
 
 __global__ void round_prep_kernel(const GroupDesc *__restrict__ groups, int32_t n_groups, int32_t round,
                                   int32_t steps, int64_t mcount, int32_t batch, int32_t batch_split,
-                                  int64_t split_max, int64_t share_max, const uint32_t *__restrict__ live_in,
+                                  int64_t split_max, int64_t share_max, int64_t share_cap, int32_t rows,
+                                  int32_t max_shares, const uint32_t *__restrict__ live_in,
                                   uint32_t *__restrict__ live_out, int64_t *__restrict__ batch_prefix,
                                   uint32_t *__restrict__ share_done, unsigned long long *work)
 {
@@ -851,9 +852,10 @@ __global__ void round_prep_kernel(const GroupDesc *__restrict__ groups, int32_t 
     // at most split_max items of batch_split paths takes that batch instead;
     // batch_prefix[n_groups + 1] holds the paths per item the round kernel is
     // to use, batch_prefix[n_groups + 2] the shares each batch is split into:
-    // as many (at most kMaxShares) as keep batches times shares within share_max,
+    // as many (at most max_shares) as keep batches times shares within share_max,
     // so that a round of few batches still fills the grid (each share's block
-    // walks the whole round and evaluates every shares-th step).
+    // walks the whole round and evaluates every shares-th window of steps); one where the
+    // batches' window sums would not fit in share_cap.
     __shared__ int64_t part[256], part_s[256];
     __shared__ int32_t s_split;
     const int t = threadIdx.x, nt = blockDim.x;
@@ -885,7 +887,9 @@ __global__ void round_prep_kernel(const GroupDesc *__restrict__ groups, int32_t 
     if (t == 0) {
         const bool split = batch_split > 0 && part_s[nt - 1] <= split_max;
         const int64_t n = split ? part_s[nt - 1] : part[nt - 1];
-        const int64_t shares = n > 0 ? max((int64_t)1, min(share_max / n, (int64_t)min(kMaxShares, steps))) : 1;
+        const int64_t bsz = split ? batch_split : batch;
+        const bool fits = n > 0 && n <= share_max && n * rows * bsz <= share_cap;
+        const int64_t shares = fits ? max((int64_t)1, min(share_max / n, (int64_t)max_shares)) : 1;
         batch_prefix[n_groups] = n * shares;
         batch_prefix[n_groups + 1] = split ? batch_split : batch;
         batch_prefix[n_groups + 2] = shares;
@@ -904,11 +908,11 @@ __global__ void round_prep_kernel(const GroupDesc *__restrict__ groups, int32_t 
 
 hipError_t launch_round_prep(const GroupDesc *groups, int32_t n_groups, int32_t round, int32_t steps, int64_t mcount,
                              int32_t batch, int32_t batch_split, int64_t split_max, int64_t share_max,
-                             const uint32_t *live_in, uint32_t *live_out, int64_t *batch_prefix, uint32_t *share_done,
+                             int64_t share_cap, int32_t rows, int32_t max_shares, const uint32_t *live_in, uint32_t *live_out, int64_t *batch_prefix, uint32_t *share_done,
                              unsigned long long *work, hipStream_t s)
 {
     hipLaunchKernelGGL(round_prep_kernel, dim3(1), dim3(256), 0, s, groups, n_groups, round, steps, mcount, batch,
-                       batch_split, split_max, share_max, live_in, live_out, batch_prefix, share_done, work);
+                       batch_split, split_max, share_max, share_cap, rows, max_shares, live_in, live_out, batch_prefix, share_done, work);
     return hipGetLastError();
 }
 

@@ -49,6 +49,8 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
     const int64_t cvec = (nvec + 1) & ~(int64_t)1;                   // LDS buffer stride in vectors
     __shared__ long long s_item;
     __shared__ SrcTime<T> s_tf[256];   // source time factors of a window of blockDim.x steps
+    __shared__ double s_acc[NS * 256];     // path sums
+    __shared__ uint16_t s_len[NS * 256];   // shares: the steps each path takes in the round
     cptr<GroupDesc> groups = as_const(a.groups);
     cptr<NodeDesc> nodes = as_const(a.nodes);
     const int64_t total = a.batch_prefix[a.n_groups];
@@ -85,7 +87,10 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
         const T *gtab = (const T *)a.slab_table + G->slab;
 
         // ---- the batch's paths
-        T X[NS][D], Y[NS][D], acc[NS], comp[NS];
+        T X[NS][D], Y[NS][D];
+        using Sums = PathSums<NS, window_steps(D)>;
+        Sums ps;
+        ps.start(s_acc, a, batch, a.batch, tid, nthr);
         bool alive[NS], began[NS];
         uint32_t node[NS], sample[NS], c0[NS];
 #pragma unroll
@@ -93,7 +98,6 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
             const int64_t p = b * a.batch + (int64_t)s * nthr + tid;
             began[s] = alive[s] = p < live;
             node[s] = 0; sample[s] = 0; c0[s] = 0;
-            acc[s] = (T)0; comp[s] = (T)0;
 #pragma unroll
             for (int i = 0; i < D; ++i) X[s][i] = (T)0;
             if (alive[s]) {
@@ -106,14 +110,13 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
                     const State st = sin[G->path_off + p];
 #pragma unroll
                     for (int i = 0; i < D; ++i) X[s][i] = st.x[i];
-                    acc[s] = st.acc;
-                    comp[s] = st.comp;
+                    ps.acc(s) = st.sum();
                     node[s] = st.node;
                     sample[s] = st.sample;
-                    if (share != 0) { acc[s] = (T)0; comp[s] = (T)0; }
                 }
                 c0[s] = nodes[node[s]].c0;
             }
+            if (shares > 1) s_len[s * nthr + tid] = (uint16_t)(alive[s] ? q1 - q0 : 0);
         }
 
         // ---- source time factors of steps [q0, q0 + nthr), one per thread
@@ -124,7 +127,7 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
         fill_time(q0);
 
         // ---- first chunk of the first evaluated step's slab into LDS buffer 0
-        int qe = q0 + share, buf = 0;   // the next step this share evaluates, its buffer
+        int qe = q0 + share * window_steps(D), buf = 0;   // the next step this share evaluates, its buffer
         if (qe < q1) mma_stage((const u32x4 *)(gtab + (int64_t)qe * a.slab_stride), lds, (int)nvec, tid, nthr);
         mma_stage_wait();
         __syncthreads();
@@ -177,6 +180,7 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
                         inside = inside && (fabs(Y[s][i]) < (T)1);
                     }
                     alive[s] = inside;   // else the path ended: L = q
+                    if (shares > 1 && !inside) s_len[s * nthr + tid] = (uint16_t)(q - q0);
                 }
                 any_live = any_live || alive[s];
             }
@@ -191,7 +195,7 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
                 }
                 continue;
             }
-            qe += shares;
+            qe = q0 + Sums::next(q - q0, shares);
             // ---- the point where step q's integrand is evaluated: the ball centre
             // X_q (eq. interIQ) or the step's Green's-function ball point, written
             // over X (a live path moves to Y after the evaluation)
@@ -265,22 +269,19 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
                     if (alive[s]) {
                         const T r = f_of<T>(a.phys, u[s]) + source_space<T, D>(a.phys, X[s], tf) +
                                     (picard ? (T)0 : v[s]);
-                        const T y = delta * r;
-                        if constexpr (sizeof(T) == 4) {
-                            const T yc = y - comp[s];
-                            const T tt = acc[s] + yc;
-                            comp[s] = (tt - acc[s]) - yc;
-                            acc[s] = tt;
-                        } else {
-                            acc[s] += y;
-                        }
+                        ps.add(s, (double)delta, (double)r);
 #pragma unroll
                         for (int i = 0; i < D; ++i) X[s][i] = Y[s][i];
                         ++evals;
                     }
                 }
             }
-            if (__syncthreads_or(any_live ? 1 : 0) == 0) { ++q; break; }
+            if (Sums::last(q - q0) || q + 1 == q1) ps.close(q - q0, shares);
+            if (__syncthreads_or(any_live ? 1 : 0) == 0) {
+                ps.close(q - q0, shares);
+                ++q;
+                break;
+            }
         }
 
         // ---- Picard form (eq. uast): a path still inside after all N* steps has
@@ -331,34 +332,29 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 if (alive[s]) {
-                    if constexpr (sizeof(T) == 4) {
-                        const T yc = u[s] - comp[s];
-                        const T tt = acc[s] + yc;
-                        comp[s] = (tt - acc[s]) - yc;
-                        acc[s] = tt;
-                    } else {
-                        acc[s] += u[s];
-                    }
+                    if (shares > 1) ps.val(a.share_rows - 1, s) = (double)u[s];
+                    else ps.acc(s) += (double)u[s];
                 }
             }
         }
 
-        // ---- paths ended in this round or at N*, and those carried to the next round
-        double sum[NS];
-#pragma unroll
-        for (int s = 0; s < NS; ++s) sum[s] = (double)acc[s] - (double)comp[s];
         if (shares > 1) {
-            if (!share_combine<NS>(a, item, batch, shares, a.batch, tid, nthr, true, sum, s_item)) continue;
+            if (!share_last(a, batch, shares, s_item)) continue;
+            int len[NS];
+#pragma unroll
+            for (int s = 0; s < NS; ++s) len[s] = s_len[s * nthr + tid];
+            share_fold(ps, len);
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                acc[s] = (T)sum[s];
-                comp[s] = (T)((double)acc[s] - sum[s]);
+                if (picard && q1 == nstar && alive[s])
+                    ps.acc(s) += ps.val(a.share_rows - 1, s);
             }
         }
+        // ---- paths ended in this round or at N*, and those carried to the next round
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const bool carry = alive[s] && q1 < nstar;
-            if (began[s] && !carry) a.result[(int64_t)nodes[node[s]].out * a.mcount + (sample[s] - a.m0)] = sum[s];
+            if (began[s] && !carry) a.result[(int64_t)nodes[node[s]].out * a.mcount + (sample[s] - a.m0)] = ps.acc(s);
             const unsigned long long mask = __ballot(carry);
             if (mask != 0ull) {
                 uint32_t base = 0;
@@ -369,8 +365,7 @@ __device__ __forceinline__ void advance_body(const RoundArgs &a)
                     State st;
 #pragma unroll
                     for (int i = 0; i < D; ++i) st.x[i] = X[s][i];
-                    st.acc = acc[s];
-                    st.comp = comp[s];
+                    st.put_sum(ps.acc(s));
                     st.node = node[s];
                     st.sample = sample[s];
                     sout[G->path_off + off] = st;
