@@ -428,8 +428,10 @@ hpsmc_status hpsmc_set_initial_coeffs(hpsmc_plan *plan, const double *c0, int32_
  *                       tabulated form (the residual once per lattice point a
  *                       node's walks reach and step); 0: the general
  *                       vector-unit kernel.
- *   "sample_1d_active"  read-only: 1 when the rounds run the windowed 1-D
- *                       kernel with the current launch shape.
+ *   "sample_1d_active"  read-only: 1 when the rounds run a 1-D kernel
+ *                       (either form) with the current launch shape.
+ *   "sample_1d_lattice_active"  read-only: 1 when some interval's rounds run
+ *                       the tabulated form.
  *   "graph"            1: hpsmc_solve captures the whole solve into a hipGraph
  *                       on its first call (on a stream of the plan) and replays
  *                       it on this and later calls; 0 (default): eager launches.

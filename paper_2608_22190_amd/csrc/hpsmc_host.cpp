@@ -1307,8 +1307,8 @@ static bool uses_1d(const hpsmc_plan *plan, int ns)
 
 static int set_uses_mma(const hpsmc_plan *plan, const NodeSet &set);
 
-// Whether the rounds of this set run the windowed 1-D kernel with the current
-// launch shape (its slabs then hold Chebyshev coefficients)
+// Whether the rounds of this set run a 1-D kernel, windowed or tabulated (set.lat), with
+// the current launch shape (its slabs then hold Chebyshev coefficients)
 static bool set_uses_1d(const hpsmc_plan *plan, const NodeSet &set)
 {
     return set.rounds && set_uses_mma(plan, set) == 0 &&
@@ -2807,6 +2807,11 @@ hpsmc_status hpsmc_get_option(const hpsmc_plan *plan, const char *name, int64_t 
     if (strcmp(name, "sample_split") == 0) { *value = plan->sample_split; return HPSMC_OK; }
     if (strcmp(name, "sample_1d") == 0) { *value = plan->sample_1d; return HPSMC_OK; }
     if (strcmp(name, "sample_1d_active") == 0) { *value = set_uses_1d(plan, plan->sets[0]); return HPSMC_OK; }
+    if (strcmp(name, "sample_1d_lattice_active") == 0) {
+        *value = 0;
+        for (const NodeSet &set : plan->sets) *value |= set.lat && set_uses_1d(plan, set);
+        return HPSMC_OK;
+    }
     if (strcmp(name, "sample_mfma_active") == 0) {
         *value = 0;
         for (int iv = 0; iv < (plan->pb.schedule == HPSMC_SEQUENTIAL ? plan->n_iv : 1); ++iv)

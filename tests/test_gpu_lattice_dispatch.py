@@ -1,0 +1,60 @@
+"""Which form the 1-D FP64 rounds run, on both sides of each line: the tabulated form up
+to P = 20, the windowed kernel past it and where a node's lattice is wider than
+4096 points, and neither for the Picard form, the ball rule, FP32's tabulation, or
+with the 1-D kernels switched off.  The windowed kernel at P = 12 and 20, one to
+four paths a lane, against the general kernel on the same words: the same walk,
+evaluation counts equal, 1e-12 of the largest path value as in the parity tests."""
+import numpy as np
+import pytest
+
+from paper_2608_22190_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _active(plan):
+    return plan.hpsmc_get_option("sample_1d_active"), plan.hpsmc_get_option("sample_1d_lattice_active")
+
+
+@pytest.mark.parametrize("n,T,nstar,kw,want", [
+    (6, 0.5, 200, {}, (1, 1)),
+    (18, 0.3, 700, {}, (1, 1)),
+    (19, 0.3, 700, {}, (1, 0)),
+    (5, 1e-5, 300, {}, (1, 0)),                       # J = 2.6e-4: more than 4096 points a side
+    (6, 0.5, 200, dict(precision="fp32"), (1, 0)),
+    (6, 0.5, 200, dict(estimator="picard"), (0, 0)),
+    (6, 0.5, 200, dict(quad="ball"), (0, 0))])
+def test_form_of_the_rounds(n, T, nstar, kw, want):
+    from paper_2608_22190_amd import hpsmc as H
+    print("[case] 1d form", n, T, kw, flush=True)
+    with H.Plan(W.small(dim=1, n=n, M_deg=2, M=64, T=T, f="sin", src="none", ic="singular", nstar=nstar, **kw)) as plan:
+        assert _active(plan) == want
+        plan.hpsmc_set_option("sample_1d", 0)
+        assert _active(plan) == (0, 0)
+        with pytest.raises(H.HpsmcError):
+            plan.hpsmc_set_option("sample_1d_lattice_active", 1)
+
+
+@pytest.mark.parametrize("n,launch", [(10, (1, 4, 2, 64)), (10, (2, 2, 4, 128)), (10, (4, 4, 2, 64)),
+                                      (18, (1, 2, 3, 64)), (18, (2, 4, 2, 32)), (18, (4, 4, 2, 256))])
+def test_windowed_kernel_below_the_line(n, launch):
+    from paper_2608_22190_amd import hpsmc as H
+    print("[case] windowed fp64", n, launch, flush=True)
+    # sqrt(2 T) = 0.0075: at n = 18 some paths of the outermost nodes, 0.019 from the boundary, leave
+    wl = W.small(dim=1, n=n, M_deg=2, M=300, T=2.8e-5, f="sin", src="none", ic="singular", nstar=330)
+    U = np.random.default_rng(n).standard_normal((1, n, 3)) * 0.4
+    out = []
+    for win in (0, 1):
+        with H.Plan(wl) as plan:
+            plan.hpsmc_set_option("sample_1d", win)
+            plan.hpsmc_set_launch(*launch)
+            assert _active(plan) == (win, 0)
+            plan.hpsmc_set_probe(8)
+            plan.hpsmc_set_nodes(0, U)
+            plan.hpsmc_iterate(0, 1)
+            out.append((plan.hpsmc_get_probe(0), plan.hpsmc_get_increment(0)[0], plan.hpsmc_stats()["path_steps"]))
+    (pg, eg, sg), (pw, ew, sw) = out
+    assert sw == sg
+    scale = 1.0 + np.max(np.abs(pg))
+    assert np.max(np.abs(pw - pg)) <= 1e-12 * scale
+    assert np.max(np.abs(ew - eg)) <= 1e-12 * scale
