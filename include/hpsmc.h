@@ -261,7 +261,9 @@ typedef struct {
     int32_t blocks_per_cu;     /* persistent grid = CUs * blocks_per_cu          */
     int32_t round_steps;       /* walk steps per round of the path-advancing
                                   kernel (multiple of 4 in 16..4096; 0 keeps
-                                  the current value)                             */
+                                  the current value); the tabulated form of the
+                                  1-D rounds (sample_1d) takes as many as its
+                                  table holds, whatever is set                   */
 } hpsmc_launch;
 
 /* Install the allocator that plans created afterwards use for every device

@@ -2621,7 +2621,7 @@ hpsmc_status hpsmc_tune(hpsmc_plan *plan, int32_t iv, int64_t m_tune, const char
         report(c, ms);
         if (ms < best_ms) { best_ms = ms; best = c; }
     }
-    if (!st) {
+    if (!st && !(set.lat && uses_1d(plan, best.samples_per_lane))) {   // the tabulated form takes its own
         // walk steps per round: long rounds for 1-D (cheap steps), short ones from
         // 3-D on (expensive steps: compaction pays sooner)
         const int rs_d1[5] = {128, 256, 512, 1024, 128}, rs[5] = {32, 64, 128, 256, 512},
@@ -2646,7 +2646,6 @@ hpsmc_status hpsmc_tune(hpsmc_plan *plan, int32_t iv, int64_t m_tune, const char
     (void)hipEventDestroy(e1);
     (void)hipStreamSynchronize(s);
     dfree(plan, Usave);
-    (void)set;
     if (st) return st;
     st = hpsmc_set_launch(plan, &best);
     if (!st && cache_path) cache_store(cache_path, key, best);

@@ -58,3 +58,18 @@ def test_windowed_kernel_below_the_line(n, launch):
     scale = 1.0 + np.max(np.abs(pg))
     assert np.max(np.abs(pw - pg)) <= 1e-12 * scale
     assert np.max(np.abs(ew - eg)) <= 1e-12 * scale
+
+
+@pytest.mark.parametrize("n,form", [(6, 1), (19, 0)])
+def test_tuner_times_round_lengths_only_where_they_matter(n, form, monkeypatch, capfd):
+    from paper_2608_22190_amd import hpsmc as H
+    print("[case] tune 1d", n, flush=True)
+    monkeypatch.setenv("HPSMC_TUNE_VERBOSE", "1")
+    with H.Plan(W.small(dim=1, n=n, M_deg=2, M=64, T=0.5, f="sin", src="none", ic="singular", nstar=200)) as plan:
+        steps = plan.hpsmc_get_launch()[3]
+        plan.hpsmc_tune(0, 16)
+        assert _active(plan) == (1, form)
+        tried = {int(line.split("steps=")[1].split(":")[0]) for line in capfd.readouterr().err.splitlines()
+                 if line.startswith("[tune]")}
+        assert tried == {steps} if form else tried > {steps}
+        assert not form or plan.hpsmc_get_launch()[3] == steps
