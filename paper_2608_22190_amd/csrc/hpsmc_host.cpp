@@ -334,6 +334,7 @@ struct NodeSet {               // the nodes one sampling launch covers
     int64_t slab_elems = 0;
     int64_t slab_elems_row = 0;   // the row layout's extent (the slab adjoint's table)
     double *pack = nullptr;    // scaled coefficients in the order of the matrix-core images, and their scales
+    int64_t pack_elems = 0, pack_scales = 0;
     void *group_mem = nullptr; // coef_off, slab_off, span, delta, h2, nstar, deg
     SlabArgs slab{};
     // outputs (canonical order)
@@ -831,10 +832,8 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     if (mma_ok && (d == 5 ? mma5_split(plan->P) : mma_split(plan->P))) {
         sa.scale_parts = (int32_t)std::min<int64_t>(64, (rows * plan->P + 4095) / 4096);
         sa.pack_t = *std::max_element(deg.begin(), deg.end()) + 1;
-        const size_t pk = NBLK * sa.pack_t * mstride;
-        if ((st = dalloc(plan, (void **)&set.pack, (pk + NBLK * 2 * sa.scale_parts) * 8))) return st;
-        sa.pack = set.pack;
-        sa.scale_max = set.pack + pk;
+        set.pack_elems = (int64_t)(NBLK * sa.pack_t * mstride);   // allocated with the faster paths' scratch
+        set.pack_scales = (int64_t)(NBLK * 2 * sa.scale_parts);
     }
     if ((st = dalloc(plan, (void **)&set.eps, sizeof(double) * set.n))) return st;
     if ((st = dalloc(plan, (void **)&set.sumsq, sizeof(double) * set.n))) return st;
@@ -921,9 +920,8 @@ static hpsmc_status build_lattice(hpsmc_plan *plan, NodeSet &set)
     int64_t steps = std::min<int64_t>(1024, budget / (8 * sum_w)) / 32 * 32;
     steps = std::min<int64_t>(steps, (set.max_nstar + 31) / 32 * 32);
     if (t_lattice >= t_direct || steps < 32 || 2 * lat_window(wmax) * (int64_t)wmax * 8 + 16 > 65536) return HPSMC_OK;
-    hpsmc_status st;
     const size_t n = nodes.size(), nb = sizeof(GroupDesc) * n, db = sizeof(LatDesc) * n, pb = sizeof(int64_t) * (n + 3);
-    if ((st = dalloc(plan, &set.lat_mem, nb + db + pb + sizeof(uint32_t) * 2 * n))) return st;
+    if (dalloc(plan, &set.lat_mem, nb + db + pb + sizeof(uint32_t) * 2 * n) != HPSMC_OK) return HPSMC_OK;
     std::vector<char> img(nb + db);
     memcpy(img.data(), nodes.data(), nb);
     memcpy(img.data() + nb, desc.data(), db);
@@ -942,6 +940,42 @@ static hpsmc_status build_lattice(hpsmc_plan *plan, NodeSet &set)
     set.lat_steps = (int32_t)steps;
     set.lat_elems = sum_w * steps;
     set.lat = true;
+    return HPSMC_OK;
+}
+
+// Scratch of the faster paths, after everything that a plan cannot do without: where it
+// is not to be had, the rounds run the kernel that needs none (the vector units for the
+// matrix-core images of halves, the windowed kernel for the tabulated form, whole
+// rounds for shares of steps).
+static hpsmc_status fast_scratch(hpsmc_plan *plan)
+{
+    int64_t lat_max = 0;
+    for (auto &s : plan->sets) {
+        if (s.pack_elems > 0) {
+            if (dalloc(plan, (void **)&s.pack, (size_t)(s.pack_elems + s.pack_scales) * 8) == HPSMC_OK) {
+                s.slab.pack = s.pack;
+                s.slab.scale_max = s.pack + s.pack_elems;
+            } else {
+                s.slab.slab_off_mma = nullptr;
+            }
+        }
+        if (hpsmc_status st = build_lattice(plan, s)) return st;
+        lat_max = std::max(lat_max, s.lat_elems);
+    }
+    if (lat_max > 0 && dalloc(plan, (void **)&plan->lat_table, (size_t)lat_max * 8) != HPSMC_OK)
+        for (auto &s : plan->sets) s.lat = false;
+    if (plan->share_max > 0) {
+        // the window sums of the rounds that are split, over the sets: at most share_max / 2 batches (each group's
+        // last one not full) of at most 512 steps
+        for (auto &s : plan->sets) {
+            if (!s.rounds) continue;
+            const int64_t paths = std::min<int64_t>(plan->share_max / 2 * kShareBatch,
+                                                    s.n * s.ms + (int64_t)s.ghost.size() * kShareBatch);
+            const int64_t rows = (std::min(s.max_nstar, 512) + window_steps(plan->d) - 1) / window_steps(plan->d) + 1;
+            plan->share_cap = std::max(plan->share_cap, std::min<int64_t>(kShareBytes / 8, paths * rows));
+        }
+        if (dalloc(plan, (void **)&plan->share_val, (size_t)plan->share_cap * 8) != HPSMC_OK) plan->share_cap = 0;
+    }
     return HPSMC_OK;
 }
 
@@ -1841,29 +1875,14 @@ hpsmc_status hpsmc_create(const hpsmc_problem *pb, hpsmc_plan **out)
         for (int iv = 0; iv < plan->n_iv; ++iv) all.push_back(iv);
         if ((st = build_set(pl, plan->sets[0], all))) return st;
     }
-    int64_t slab_max = 0, nmax = 0, lat_max = 0;
-    for (auto &s : plan->sets) {
-        if ((st = build_lattice(pl, s))) return st;
-        lat_max = std::max(lat_max, s.lat_elems);
-    }
-    if (lat_max > 0 && (st = dalloc(pl, (void **)&pl->lat_table, (size_t)lat_max * 8))) return st;
+    int64_t slab_max = 0, nmax = 0;
     for (auto &s : plan->sets) { slab_max = std::max(slab_max, s.slab_elems); nmax = std::max(nmax, s.n); }
-    if (plan->share_max > 0) {
-        // the window sums of the rounds that are split, over the sets: at most share_max / 2 batches (each group's
-        // last one not full) of at most 512 steps
-        for (auto &s : plan->sets) {
-            if (!s.rounds) continue;
-            const int64_t paths = std::min<int64_t>(plan->share_max / 2 * kShareBatch,
-                                                    s.n * s.ms + (int64_t)s.ghost.size() * kShareBatch);
-            const int64_t rows = (std::min(s.max_nstar, 512) + window_steps(plan->d) - 1) / window_steps(plan->d) + 1;
-            plan->share_cap = std::max(plan->share_cap, std::min<int64_t>(kShareBytes / 8, paths * rows));
-        }
-        if (plan->share_cap > 0 && (st = dalloc(pl, (void **)&pl->share_val, (size_t)plan->share_cap * 8))) return st;
-    }
     plan->slab_bytes = (size_t)slab_max * (plan->fp32 ? 4 : 8);
     if ((st = dalloc(pl, &pl->slab_table, plan->slab_bytes))) return st;
     plan->part_elems = nmax * ((pb->M + 63) / 64) * 2;
     if ((st = dalloc(pl, (void **)&pl->part, plan->part_elems * 8))) return st;
+
+    if ((st = fast_scratch(pl))) return st;
 
     // initial iterate: the initial column replicated in time
     if (pb->schedule == HPSMC_SEQUENTIAL) {
@@ -2928,12 +2947,13 @@ hpsmc_status hpsmc_loss_grad_c0(hpsmc_plan *plan, const double *target, double *
             (st = dalloc(plan, (void **)&plan->lam, (size_t)usz * 8)) ||
             (st = dalloc(plan, (void **)&plan->cbar_u, (size_t)csz * 8)) ||
             (st = dalloc(plan, (void **)&plan->cbar_v, (size_t)csz * 8)) ||
-            (shares > 1 && (st = dalloc(plan, (void **)&plan->cbar_part, (size_t)shares * 2 * csz * 8))) ||
             (st = dalloc(plan, (void **)&plan->dtarget, (size_t)I * nsp * 8)) ||
             (st = dalloc(plan, (void **)&plan->dloss, (size_t)I * 8)) ||
             (st = dalloc(plan, (void **)&plan->dgrad, (size_t)I * nsp * 8)) ||
             (st = dalloc(plan, &plan->slab_bar, bar_alloc_bytes(plan, set))))
             return st;
+        // the slab adjoint's partial tensors; without them it runs unshared
+        if (shares > 1) (void)dalloc(plan, (void **)&plan->cbar_part, (size_t)shares * 2 * csz * 8);
     }
     HIP_TRY(hipMemcpyAsync(plan->dtarget, target, (size_t)I * nsp * 8,
                            on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
