@@ -280,9 +280,10 @@ hpsmc_status hpsmc_set_allocator(hpsmc_alloc_fn alloc, hpsmc_free_fn free_, void
  * nodes of every interval, the nodal-to-modal matrices of eqs. spacelag and
  * timeLag, the path lengths of eq. time division (resolved here when a rule
  * is selected), and Algorithm 1's initial guess.
- * EINVAL on any out-of-range field; ENOTSUP for unsupported combinations.  Scratch that only a faster form of the rounds
- * needs (images of half-precision parts, the tabulated 1-D form, shares of
- * steps) is allocated last; where it is not to be had, the plan does without. */
+ * EINVAL on any out-of-range field; ENOTSUP for unsupported combinations.
+ * Scratch that only a faster form of the rounds needs (images of
+ * half-precision parts, the tabulated 1-D form, shares of steps) is allocated
+ * last; where it is not to be had, the plan does without. */
 hpsmc_status hpsmc_create(const hpsmc_problem *pb, hpsmc_plan **out);
 void hpsmc_destroy(hpsmc_plan *plan);
 

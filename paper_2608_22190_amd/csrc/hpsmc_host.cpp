@@ -2941,20 +2941,17 @@ hpsmc_status hpsmc_loss_grad_c0(hpsmc_plan *plan, const double *target, double *
     NodeSet &set = plan->sets[0];
     const int shares = slab_adjoint_shares(set.slab, plan->degree[0], (int)I, set.max_nstar, plan->cus);
     hpsmc_status st;
-    if (!plan->lam) {
-        if ((st = dalloc(plan, (void **)&plan->hist_u, (size_t)K * csz * 8)) ||
-            (st = dalloc(plan, (void **)&plan->hist_v, (size_t)K * csz * 8)) ||
-            (st = dalloc(plan, (void **)&plan->lam, (size_t)usz * 8)) ||
-            (st = dalloc(plan, (void **)&plan->cbar_u, (size_t)csz * 8)) ||
-            (st = dalloc(plan, (void **)&plan->cbar_v, (size_t)csz * 8)) ||
-            (st = dalloc(plan, (void **)&plan->dtarget, (size_t)I * nsp * 8)) ||
-            (st = dalloc(plan, (void **)&plan->dloss, (size_t)I * 8)) ||
-            (st = dalloc(plan, (void **)&plan->dgrad, (size_t)I * nsp * 8)) ||
-            (st = dalloc(plan, &plan->slab_bar, bar_alloc_bytes(plan, set))))
-            return st;
-        // the slab adjoint's partial tensors; without them it runs unshared
-        if (shares > 1) (void)dalloc(plan, (void **)&plan->cbar_part, (size_t)shares * 2 * csz * 8);
-    }
+    // the buffers of the gradient, on its first call or the first after one that ran out of memory
+    const auto need = [&](void **p, size_t bytes) { return *p ? HPSMC_OK : dalloc(plan, p, bytes); };
+    const bool first = !plan->slab_bar;
+    if ((st = need((void **)&plan->hist_u, (size_t)K * csz * 8)) || (st = need((void **)&plan->hist_v, (size_t)K * csz * 8)) ||
+        (st = need((void **)&plan->lam, (size_t)usz * 8)) || (st = need((void **)&plan->cbar_u, (size_t)csz * 8)) ||
+        (st = need((void **)&plan->cbar_v, (size_t)csz * 8)) || (st = need((void **)&plan->dtarget, (size_t)I * nsp * 8)) ||
+        (st = need((void **)&plan->dloss, (size_t)I * 8)) || (st = need((void **)&plan->dgrad, (size_t)I * nsp * 8)) ||
+        (st = need(&plan->slab_bar, bar_alloc_bytes(plan, set))))
+        return st;
+    // the slab adjoint's partial tensors; without them it runs unshared
+    if (first && shares > 1) (void)dalloc(plan, (void **)&plan->cbar_part, (size_t)shares * 2 * csz * 8);
     HIP_TRY(hipMemcpyAsync(plan->dtarget, target, (size_t)I * nsp * 8,
                            on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
     // forward, keeping every iteration's Legendre tensors

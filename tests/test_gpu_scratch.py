@@ -73,3 +73,27 @@ def test_a_refused_allocation_falls_back(dim, n, M, prec, forms, optional, tol):
         assert s == steps
         assert np.max(np.abs(val - ref)) <= tol * (1.0 + np.max(np.abs(ref)))
     assert seen == optional
+
+
+def test_a_gradient_after_one_that_ran_out_of_memory():
+    from paper_2608_22190_amd import hpsmc as H
+    print("[case] scratch gradient", flush=True)
+    wl = W.small(dim=2, n=6, M_deg=2, M=20, iters=2, T=0.4, f="sin", src="longtime", nstar=60, precision="fp32", ic="phi",
+                 ic_data=W.c5_coefficients(2, n=6).reshape(2, -1), n_instances=2)
+    target = 0.1 * np.random.default_rng(0).standard_normal((2, wl.nsp))
+    with H.Plan(wl) as plan:
+        loss, grad = plan.hpsmc_loss_grad_c0(target)
+    plan, hook = _create(H, wl, -1)
+    failed = 0
+    with plan:
+        while failed < 20:
+            hook.refuse = hook.calls + 1   # every call gets one buffer more and is refused the next
+            try:
+                again = plan.hpsmc_loss_grad_c0(target)
+                break
+            except H.HpsmcError as e:
+                assert e.status == -3   # ENOMEM
+                failed += 1
+    assert failed == 8   # nine buffers
+    assert np.array_equal(again[0], loss)
+    assert np.max(np.abs(again[1] - grad)) <= 1e-5 * np.max(np.abs(grad))   # FP32 sums by atomics
