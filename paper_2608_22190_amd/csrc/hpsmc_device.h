@@ -999,8 +999,8 @@ __device__ __forceinline__ float opaque_minus_one()
 }
 
 // registers of one lane's B operand: four per block of eight modes, or one per mode pair
-template <int KH> struct MmaB {
-    static constexpr bool SPLIT = KH >= kMmaSplitKH;
+template <int KH, bool SP = (KH >= kMmaSplitKH)> struct MmaB {
+    static constexpr bool SPLIT = SP;
     static constexpr int NB = (KH + 3) / 4, NR = SPLIT ? 4 * NB : KH;
     static constexpr int VECS = SPLIT ? 128 * NB : 2 * ((KH + 1) / 2 * 4) * kMmaRows / 4;   // 16-byte vectors per image
     uint32_t r[NR];
@@ -1013,13 +1013,13 @@ template <int KH> struct MmaB {
 
 // B operands: Chebyshev values bscale T_{k1}(x1) of the wave's 64 points in two
 // half-precision parts (b0: paths 0-31, b1: paths 32-63)
-template <int KH>
-__device__ __forceinline__ void mma_operands(float x1, int P, float bscale, MmaB<KH> &b0, MmaB<KH> &b1)
+template <int KH, bool SP>
+__device__ __forceinline__ void mma_operands(float x1, int P, float bscale, MmaB<KH, SP> &b0, MmaB<KH, SP> &b1)
 {
     static_assert(KH >= 2 && KH <= 16, "one 32-row tile, at least 4 modes");
     constexpr int K2 = 2 * KH;
     const float x2 = x1 + x1;
-    if constexpr (!MmaB<KH>::SPLIT) {
+    if constexpr (!SP) {
         float L[K2];
         const float xx = x1 + x1;
         L[0] = 1.f;
@@ -1049,17 +1049,17 @@ __device__ __forceinline__ void mma_operands(float x1, int P, float bscale, MmaB
         lc = fmaf(x2, lp, -lc);
     }
 #pragma unroll
-    for (int kk = KH; kk < MmaB<KH>::NR; ++kk) { b0.r[kk] = 0u; b1.r[kk] = 0u; }
+    for (int kk = KH; kk < MmaB<KH, SP>::NR; ++kk) { b0.r[kk] = 0u; b1.r[kk] = 0u; }
 }
 
 // the products of the u and v tables with both path halves; UO: the u table only.
 // The a1 part first: its sums are the small ones.
-template <int KH, bool UO = false>
-__device__ __forceinline__ void mma_issue(const float *Sb, int lane, const MmaB<KH> &b0, const MmaB<KH> &b1,
+template <bool UO, int KH, bool SP>
+__device__ __forceinline__ void mma_issue(const float *Sb, int lane, const MmaB<KH, SP> &b0, const MmaB<KH, SP> &b1,
                                           f32x16 &du0, f32x16 &dv0, f32x16 &du1, f32x16 &dv1)
 {
     du0 = f32x16{}; dv0 = f32x16{}; du1 = f32x16{}; dv1 = f32x16{};
-    if constexpr (!MmaB<KH>::SPLIT) {
+    if constexpr (!SP) {
         constexpr int PP = (KH + 1) / 2 * 4;
         const float *Au = Sb + (lane >> 5) * KH * kMmaRows + (lane & 31), *Av = Au + PP * kMmaRows;
 #pragma unroll
@@ -1072,7 +1072,7 @@ __device__ __forceinline__ void mma_issue(const float *Sb, int lane, const MmaB<
         }
         return;
     }
-    constexpr int NB = MmaB<KH>::NB;
+    constexpr int NB = MmaB<KH, SP>::NB;
     const u32x4 *A = (const u32x4 *)Sb + (lane & 31);
 #pragma unroll
     for (int part = 1; part >= 0; --part) {
@@ -1094,7 +1094,7 @@ __device__ __forceinline__ void mma_issue(const float *Sb, int lane, const MmaB<
 // rows back to the owning lane and the contraction with T_{k0}(x0) (rows >= P
 // of T are zero).  Registers r = 4g..4g+3 hold rows 8g..8g+3 (before the swap)
 // and 8g+4..8g+7 (after it): the Chebyshev values in x0 advance eight at a time.
-template <int KH, bool UO = false>
+template <int KH, bool SP, bool UO>
 __device__ __forceinline__ void mma_epilogue(const f32x16 &du0, const f32x16 &dv0, const f32x16 &du1,
                                              const f32x16 &dv1, float x0, float &u, float &v)
 {
@@ -1104,7 +1104,7 @@ __device__ __forceinline__ void mma_epilogue(const f32x16 &du0, const f32x16 &dv
     // the others, so that the small terms of a decaying table do not each round a large
     // sum (rms error against 64 bits of the FP32 products' with one sum 0.95 and 0.8,
     // random and smooth tables; with one sum here 1.0 and 1.05).
-    constexpr int NA = MmaB<KH>::SPLIT ? 4 : 1;
+    constexpr int NA = SP ? 4 : 1;
     float su[NA] = {}, sv[NA] = {}, lp = 0.f, lc = 1.f;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {

@@ -653,13 +653,19 @@ static double walk_radius(const hpsmc_plan *plan, double delta)
     return std::sqrt(2.0 * plan->d * delta);
 }
 
-// Power of two that the basis values of the 2-D matrix-core kernel's split
-// products are scaled by (1 where it runs FP32 products): 2^10 on [-1, 1]^2 (|T_k| <= 1), less when ball points may lie outside the
-// domain, so that T_k stays below the largest half; 0 when no power >= 1 does.
-static double mma_basis_scale(const hpsmc_plan *plan)
+// Form of the 2-D matrix-core kernel's products.  Halves from P = 17 on, the basis values
+// scaled by 2^10 on [-1, 1]^2 (|T_k| <= 1), by less when ball points may lie outside
+// the domain, so that T_k stays below the largest half (a scale of 1 is no less exact);
+// FP32 products where that takes a scale below 1, as long as T_k stays below 2^24 (past
+// it an FP32 sum holds no digit of u: the vector units run such plans, as good as any).
+struct MmaForm {
+    bool ok, split;
+    double bscale;
+};
+static MmaForm mma_form(const hpsmc_plan *plan)
 {
-    if (!mma_split(plan->P)) return 1.0;
-    if (plan->pb.quad != HPSMC_QUAD_BALL) return 1024.0;
+    if (!mma_split(plan->P)) return {true, false, 1.0};
+    if (plan->pb.quad != HPSMC_QUAD_BALL) return {true, true, 1024.0};
     double jmax = 0.0;
     size_t o = 0;
     for (int iv = 0; iv < plan->n_iv; ++iv) {
@@ -668,14 +674,14 @@ static double mma_basis_scale(const hpsmc_plan *plan)
             jmax = std::max(jmax, std::sqrt(2.0 * plan->d * 0.5 * (plan->xi[iv][l] + 1.0) * h / plan->nstar[o]));
     }
     const double lg = ((plan->P - 1) * std::acosh(1.0 + jmax)) / std::log(2.0);   // log2 of twice T_{P-1}, at most
-    const int e = std::min(10, 15 - (int)std::ceil(lg));
-    return e < 0 ? 0.0 : std::ldexp(1.0, e);
+    if (lg <= 15.0) return {true, true, std::ldexp(1.0, std::min(10, 15 - (int)std::ceil(lg)))};
+    return {lg <= 25.0, false, 1.0};
 }
 
 // whether some launch shape runs this plan's rounds on a matrix-core kernel
 static bool mma_capable(const hpsmc_plan *plan)
 {
-    if (plan->d == 2 && mma_basis_scale(plan) == 0.0) return false;
+    if (plan->d == 2 && !mma_form(plan).ok) return false;
     if (plan->d == 5)
         return advance_mma5_eligible(plan->fp32, 5, plan->P, plan->pb.estimator == HPSMC_EST_PICARD,
                                      plan->pb.quad == HPSMC_QUAD_BALL, 1, 4);
@@ -695,7 +701,8 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     // plans a matrix-core round kernel can serve also get offsets in its slab layout
     const bool mma_ok = mma_capable(plan);
     const int extra = plan->pb.estimator == HPSMC_EST_PICARD ? 1 : 0;   // the slab of q = N* (t = t_{n-1})
-    const int64_t mstride = d == 5 ? mma5_geom(plan->P).step : mma_slab_elems(plan->P);
+    const MmaForm form = d == 5 ? MmaForm{true, mma5_split(plan->P), 1024.0} : mma_form(plan);   // 5-D: |L_k| <= 1 in the domain
+    const int64_t mstride = d == 5 ? mma5_geom(plan->P).step : mma_slab_elems(plan->P, form.split);
     int64_t slab_pos = 0, slab_pos_mma = 0, out = 0;
     // canonical output order: [iv][inst][node id]
     for (int32_t iv : ivs) {
@@ -820,7 +827,8 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     sa.inv_scale = (float *)(gb + G * 72);
     sa.blk_group = (const int32_t *)(gb + G * 72 + NBLK * 8);
     sa.n_blk = (int32_t)NBLK;
-    sa.bscale = d == 2 ? mma_basis_scale(plan) : 1024.0;   // 5-D: |L_k| <= 1 in the domain
+    sa.bscale = form.bscale;
+    sa.split = mma_ok && form.split;
     sa.mma_stride = mstride;
     sa.layout = 0;
     sa.extra = extra;
@@ -829,7 +837,7 @@ static hpsmc_status build_set(hpsmc_plan *plan, NodeSet &set, const std::vector<
     sa.PP = plan->PP;
     sa.rows = (int32_t)rows;
     sa.slab_stride = stride;
-    if (mma_ok && (d == 5 ? mma5_split(plan->P) : mma_split(plan->P))) {
+    if (sa.split) {
         sa.scale_parts = (int32_t)std::min<int64_t>(64, (rows * plan->P + 4095) / 4096);
         sa.pack_t = *std::max_element(deg.begin(), deg.end()) + 1;
         set.pack_elems = (int64_t)(NBLK * sa.pack_t * mstride);   // allocated with the faster paths' scratch
@@ -1411,7 +1419,7 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
     const bool k1d = set_uses_1d(plan, set);
     const size_t lds = k1d ? advance_1d_lds_bytes(plan->fp32, set.slab.slab_stride)
                      : mma == 2 ? advance_mma5_lds_bytes(plan->P)
-                     : mma ? advance_mma_lds_bytes(plan->P)
+                     : mma ? advance_mma_lds_bytes(plan->P, set.slab.split)
                      : plan->frac ? frac_lds_bytes(plan->fp32)
                                   : (size_t)2 * ((nvec + 1) & ~1LL) * 16;
     const bool lat = k1d && set.lat;   // over nodes instead of groups
@@ -1441,6 +1449,7 @@ static hpsmc_status sample_rounds(hpsmc_plan *plan, NodeSet &set, int tag, int r
     a.slab_stride = mma ? set.slab.mma_stride : set.slab.slab_stride;
     a.inv_scale = set.slab.inv_scale;
     a.bscale = (float)set.slab.bscale;
+    a.mma_split = set.slab.split;
     a.work = plan->counters;
     a.stats = plan->counters + kStatWords;
     a.phys = physics_of(plan);
@@ -1539,7 +1548,7 @@ static hpsmc_status slab_args_for(hpsmc_plan *plan, const NodeSet &set, int layo
     sa = set.slab;
     sa.slab_table = plan->slab_table;
     sa.layout = layout;
-    if (layout == 2 && mma5_split(plan->P)) HIP_TRY(launch_coef_pack(sa, s));
+    if (layout == 2 && sa.split) HIP_TRY(launch_coef_pack(sa, s));
     if (layout != 1 && !(cheb && layout == 0)) return HPSMC_OK;
     if (!plan->cu_ch) return fail(HPSMC_EINVAL, "no Chebyshev coefficient buffers for this slab layout");
     for (int32_t iv : set.ivs) {
@@ -1552,7 +1561,7 @@ static hpsmc_status slab_args_for(hpsmc_plan *plan, const NodeSet &set, int layo
     sa.cu = plan->cu_ch;
     sa.cv = plan->cv_ch;
     if (sa.cs) sa.cs = plan->cs_ch;
-    if (layout == 1 && mma_split(plan->P)) HIP_TRY(launch_coef_pack(sa, s));
+    if (layout == 1 && sa.split) HIP_TRY(launch_coef_pack(sa, s));
     return HPSMC_OK;
 }
 

@@ -119,6 +119,7 @@ struct RoundArgs {
     int64_t slab_stride;
     const float *inv_scale;      // matrix-core images of scaled coefficients: [blk][u, v] the inverse scale
     float bscale;                // the scale of their basis values
+    int32_t mma_split;           // 2-D matrix-core kernel: products of halves
     unsigned long long *work;    // block work counter (zeroed by the prep kernel)
     unsigned long long *stats;   // [kStatStripes][kStatWords]: [0] residual evaluations, [1] slot steps
     Physics phys;
@@ -172,6 +173,7 @@ struct SlabArgs {
     double *pack;                // images of halves: [blk][pack_t][mma_stride] scaled coefficients in image order
     int32_t pack_t;              // most time coefficients of a block
     double bscale;
+    int32_t split;               // the matrix-core layout holds halves
     int32_t layout;              // 0: rows [k0][u: PP][v: PP]; 1: matrix-core layout
     int32_t extra;               // slabs past N* per group (1 for the Picard form: q = N*, t_{n-1})
     const double *span;          // per group: t_{n,l} - t_{n-1}
@@ -236,7 +238,7 @@ hipError_t launch_lat_advance(const RoundArgs &a, const LatArgs &la, int ns, int
 // matrix-core form of the round kernel: FP32, d = 2, P <= 32, whole slab per
 // LDS buffer, one path per lane
 bool advance_mma_eligible(int fp32, int dim, int P, int cf, int samples_per_lane, int waves_per_block);
-size_t advance_mma_lds_bytes(int P);
+size_t advance_mma_lds_bytes(int P, int split);
 // matrix-core slab layout (d = 2), the kernel's LDS image of one step, coefficients of
 // T_{k0} T_{k1}.  P >= 17: halves [table u, v][part 0, 1][block of 8 modes
 // k1][row k0 < 32][8 modes], the two parts a0 + a1 of the scaled coefficients;
@@ -249,9 +251,9 @@ constexpr int kMmaRows = 33;
 constexpr int kMmaSplitKH = 9;   // from this ceil(P / 2) on
 constexpr bool mma_split(int P) { return (P + 1) / 2 >= kMmaSplitKH; }
 constexpr int mma_blocks(int P) { return (P + 7) / 8; }
-constexpr int64_t mma_slab_elems(int P)   // in floats
+constexpr int64_t mma_slab_elems(int P, bool split)   // in floats
 {
-    return mma_split(P) ? (int64_t)512 * mma_blocks(P) : (int64_t)2 * ((P + 3) / 4 * 4) * kMmaRows;
+    return split ? (int64_t)512 * mma_blocks(P) : (int64_t)2 * ((P + 3) / 4 * 4) * kMmaRows;
 }
 // largest exponent e of |scaled coefficient| < 2^e
 constexpr int kMmaScaleExp = 14;

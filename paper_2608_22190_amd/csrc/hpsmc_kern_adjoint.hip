@@ -472,7 +472,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) a
             float wu = 0.f, wv = 0.f;
             if (__ballot(alive) != 0ull) {
                 MmaB<KH> b0, b1;
-                mma_operands<KH>(x1, P, a.bscale, b0, b1);
+                mma_operands(x1, P, a.bscale, b0, b1);
                 f32x16 du0 = {}, du1 = {}, dv = {};
                 if constexpr (SPLIT) {
 #pragma unroll
@@ -490,7 +490,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) a
                     }
                 }
                 float u = 0.f, v = 0.f;
-                mma_epilogue<KH, true>(du0, dv, du1, dv, x0, u, v);
+                mma_epilogue<KH, SPLIT, true>(du0, dv, du1, dv, x0, u, v);
                 if constexpr (SPLIT) u *= iu;
                 if (alive) {
                     wv = lam;

@@ -18,9 +18,11 @@ namespace hpsmc {
 // point of paths that stay inside for all N* steps); bit 1: the ball-point
 // rule (the operands and the epilogue take the step's Green's-function ball
 // point, drawn one step ahead like the walk's next point).
-template <int KH, int MODE>
+// SP: products of halves.
+template <int KH, int MODE, bool SP>
 __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
 {
+    using Operands = MmaB<KH, SP>;
     constexpr bool PIC = (MODE & 1) != 0, BALL = (MODE & 2) != 0;
     extern __shared__ u32x4 lds[];
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
@@ -28,7 +30,7 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
     __shared__ SrcTime<float> s_tf[256];   // source time factors of a window of blockDim.x steps
     __shared__ double s_acc[256];          // path sums
     __shared__ uint16_t s_len[256];        // shares: the steps each path takes in the round
-    constexpr int mvec = MmaB<KH>::VECS;                 // 16-byte vectors per LDS buffer (slab image)
+    constexpr int mvec = Operands::VECS;                 // 16-byte vectors per LDS buffer (slab image)
     constexpr int svec = PIC ? mvec / 2 : mvec;         // of which staged: the Picard form reads the u table only
     cptr<GroupDesc> groups = as_const(a.groups);
     cptr<NodeDesc> nodes = as_const(a.nodes);
@@ -61,7 +63,7 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
         const int64_t live = a.round == 0 ? (int64_t)G->node_count * a.mcount : (int64_t)a.live_in[g];
         const float *gtab = (const float *)a.slab_table + G->slab_mma;
         float iu = 1.f, iv = 1.f;
-        if constexpr (MmaB<KH>::SPLIT) {
+        if constexpr (SP) {
             iu = a.inv_scale[2 * G->blk];
             iv = a.inv_scale[2 * G->blk + 1];
         }
@@ -109,8 +111,8 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                 ex1 = fmaf(J, off[1], x1);
             }
         }
-        MmaB<KH> b0, b1;
-        mma_operands<KH>(ex1, a.P, a.bscale, b0, b1);
+        Operands b0, b1;
+        mma_operands(ex1, a.P, a.bscale, b0, b1);
         mma_stage_wait();
         __syncthreads();
 
@@ -151,14 +153,14 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                         ex1 = fmaf(J, off[1], x1);
                     }
                 }
-                mma_operands<KH>(ex1, a.P, a.bscale, b0, b1);
+                mma_operands(ex1, a.P, a.bscale, b0, b1);
             }
             float u = 0.f, v = 0.f, y0 = x0, y1 = x1, nx0 = x0, nx1 = x1;
             drawn = qe == q + 1;
             bool inside = false;
             if (__ballot(alive) != 0ull) {
                 f32x16 du0, dv0, du1, dv1;
-                mma_issue<KH, PIC>((const float *)(lds + buf * mvec), lane, b0, b1, du0, dv0, du1, dv1);
+                mma_issue<PIC>((const float *)(lds + buf * mvec), lane, b0, b1, du0, dv0, du1, dv1);
                 // under the products: direction, jump, exit test, next operands
                 float d0, d1;
                 angle_dir(u01(word, 0.f), d0, d1);
@@ -175,10 +177,10 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                         nx1 = fmaf(J, off[1], y1);
                     }
                 }
-                MmaB<KH> nb0 = b0, nb1 = b1;
-                if (drawn) mma_operands<KH>(nx1, a.P, a.bscale, nb0, nb1);
-                mma_epilogue<KH, PIC>(du0, dv0, du1, dv1, ex0, u, v);
-                if constexpr (MmaB<KH>::SPLIT) {
+                Operands nb0 = b0, nb1 = b1;
+                if (drawn) mma_operands(nx1, a.P, a.bscale, nb0, nb1);
+                mma_epilogue<KH, SP, PIC>(du0, dv0, du1, dv1, ex0, u, v);
+                if constexpr (SP) {
                     u *= iu;
                     v *= iv;
                 }
@@ -219,13 +221,13 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
                 mma_stage_wait();
                 __syncthreads();
                 if (__ballot(alive) != 0ull) {
-                    MmaB<KH> tb0, tb1;
-                    mma_operands<KH>(x1, a.P, a.bscale, tb0, tb1);
+                    Operands tb0, tb1;
+                    mma_operands(x1, a.P, a.bscale, tb0, tb1);
                     f32x16 du0, dv0, du1, dv1;
-                    mma_issue<KH, true>((const float *)lds, lane, tb0, tb1, du0, dv0, du1, dv1);
+                    mma_issue<true>((const float *)lds, lane, tb0, tb1, du0, dv0, du1, dv1);
                     float u = 0.f, v = 0.f;
-                    mma_epilogue<KH, true>(du0, dv0, du1, dv1, x0, u, v);
-                    if constexpr (MmaB<KH>::SPLIT) u *= iu;
+                    mma_epilogue<KH, SP, true>(du0, dv0, du1, dv1, x0, u, v);
+                    if constexpr (SP) u *= iu;
                     if (alive) {
                         if (shares == 1) ps.acc(0) += (double)u;
                         else ps.val(a.share_rows - 1, 0) = (double)u;
@@ -263,12 +265,14 @@ __device__ __forceinline__ void advance_mma_body(const RoundArgs &a)
     add_stats(a, evals, slots);
 }
 
-template <int KH, int MODE>
+template <int KH, int MODE, bool SP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) advance_mma_kernel(RoundArgs a)
 {
-    advance_mma_body<KH, MODE>(a);
+    advance_mma_body<KH, MODE, SP>(a);
 }
 
+// From kMmaSplitKH on products of halves; FP32 ones there where ball points lie so far
+// outside the domain that no scale keeps the basis values within the halves.
 template <int KH, int MODE>
 static hipError_t adv_mma(const RoundArgs &a, int kh, dim3 grid, dim3 block, size_t lds, hipStream_t s)
 {
@@ -276,7 +280,15 @@ static hipError_t adv_mma(const RoundArgs &a, int kh, dim3 grid, dim3 block, siz
         return hipErrorInvalidValue;
     } else {
         if (kh != KH) return adv_mma<KH + 1, MODE>(a, kh, grid, block, lds, s);
-        hipLaunchKernelGGL((advance_mma_kernel<KH, MODE>), grid, block, lds, s, a);
+        constexpr bool split = KH >= kMmaSplitKH;
+        if (a.mma_split == (int)split) {
+            hipLaunchKernelGGL((advance_mma_kernel<KH, MODE, split>), grid, block, lds, s, a);
+        } else {
+            if constexpr (split && (MODE & 2) != 0)
+                hipLaunchKernelGGL((advance_mma_kernel<KH, MODE, false>), grid, block, lds, s, a);
+            else
+                return hipErrorInvalidValue;
+        }
         return hipGetLastError();
     }
 }
@@ -287,7 +299,7 @@ bool advance_mma_eligible(int fp32, int dim, int P, int cf, int samples_per_lane
            waves_per_block <= 4;
 }
 
-size_t advance_mma_lds_bytes(int P) { return (size_t)2 * mma_slab_elems(P) * sizeof(float); }
+size_t advance_mma_lds_bytes(int P, int split) { return (size_t)2 * mma_slab_elems(P, split != 0) * sizeof(float); }
 
 hipError_t launch_adv_mma(const RoundArgs &a, dim3 grid, dim3 block, size_t lds, hipStream_t s)
 {

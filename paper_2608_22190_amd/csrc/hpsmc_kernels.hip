@@ -549,7 +549,7 @@ __global__ void __launch_bounds__(256) slab_split_kernel(SlabArgs a, int parts)
 hipError_t launch_slabs(const SlabArgs &a, int fp32, int max_nstar, hipStream_t s)
 {
     if (a.n_groups <= 0) return hipSuccess;
-    if ((a.layout == 2 && mma5_split(a.P)) || (a.layout == 1 && mma_split(a.P))) {
+    if (a.layout != 0 && a.split) {
         const int64_t parts = (a.mma_stride / 2 + kSplitPairs - 1) / kSplitPairs;
         const int64_t chunks = std::min<int64_t>((max_nstar + a.extra + kSplitQ - 1) / kSplitQ, std::max<int64_t>(1, (1 << 22) / parts));
         const dim3 sg((unsigned)(parts * chunks), (unsigned)std::min<int64_t>(a.n_groups, kGridYZ),
