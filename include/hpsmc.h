@@ -151,8 +151,8 @@ enum { HPSMC_NSTAR_ARRAY = 0,     /* the `nstar` array, one entry per node time 
                                      set-up                                       */
 
 enum { HPSMC_FP64 = 0,            /* everything in FP64                            */
-       HPSMC_FP32_SAMPLING = 1,   /* paths and basis evaluation in FP32 with
-                                     compensated accumulation; reconstruction,
+       HPSMC_FP32_SAMPLING = 1,   /* paths and basis evaluation in FP32, path
+                                     sums in FP64 or compensated; reconstruction,
                                      increments, norms and stop test in FP64      */
        HPSMC_FP32_THEN_FP64 = 2 };/* hpsmc_solve samples an interval (a sweep) in
                                      FP32 until max|eps| < switch_tol, then goes on

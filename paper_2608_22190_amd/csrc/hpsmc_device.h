@@ -949,13 +949,14 @@ __device__ __forceinline__ void mma_stage_wait() { asm volatile("s_waitcnt vmcnt
 // four partial products run on v_mfma_f32_32x32x16_f16 with FP32 accumulation.
 // The tables are scaled by a power of two so that their largest entry has
 // magnitude 2^13..2^14 (coef_pack_kernel) and the basis values by 2^10, so no
-// part that matters is subnormal.  An FP32 product (32x32x2, 64 cycles for two
-// modes) was what bounded the kernel, and it does not overlap with the vector
-// work of other waves; the four half-precision products take 32 cycles for
-// eight modes each way and partly do (P = 26: 32 products of 32x32x16 per wave
+// part that matters is subnormal.  Eight modes of a table and 32 paths take four
+// FP32 products (32x32x2, 64 cycles of the matrix core each), which bounded the
+// kernel and do not overlap with the vector work of other waves, or two products of
+// parts (32x32x16, 32 cycles each), which partly do (P = 26: 32 products per wave
 // step and 52 more vector instructions, instead of 52 products of 32x32x2:
 // 24 x 24 x 16 nodes with 256 samples 704 -> 392 ms an iteration, P = 22 sweeps
-// 185 -> 107 ms, the Picard form 258 -> 181 ms).
+// 185 -> 107 ms, the Picard form 258 -> 181 ms).  Counters there: matrix cores busy
+// 0.33 of the SIMD cycles, 13 other vector instructions a product, whose issue takes 0.52.
 //
 // Operands of v_mfma_f32_32x32x16_f16: lane l holds A[l%32][8 (l/32) + j] and
 // B[8 (l/32) + j][l%32], j < 8 (four registers of two halves); D register r of

@@ -1,4 +1,5 @@
-// Matrix-core form of the 2-D FP32 round kernel (v_mfma_f32_32x32x16_f16 on split factors).
+// Matrix-core form of the 2-D FP32 round kernel (v_mfma_f32_32x32x16_f16 on split factors
+// from P = 17 on, v_mfma_f32_32x32x2f32 below).
 #include "hpsmc_device.h"
 
 namespace hpsmc {
@@ -7,7 +8,7 @@ namespace hpsmc {
 // Round kernel, matrix-core form: d = 2, FP32, one path per lane, the whole
 // slab of a step in LDS (its image copied straight from the table).  The step
 // loop is software-pipelined so that a wave's vector work runs under its own
-// products: at step q the wave issues the 4 KH products of the residual at X_q
+// products: at step q the wave issues the products of the residual at X_q
 // and meanwhile draws the direction of step q, takes the jump and the exit
 // test (eq. indexL) and forms the operands of the next point; the epilogue
 // then completes u and v, and the residual enters the path sum (eq. interIQ)

@@ -1,4 +1,5 @@
-// Matrix-core form of the 5-D FP32 round kernel (v_mfma_f32_32x32x16_f16 on split factors).
+// Matrix-core form of the 5-D FP32 round kernel (v_mfma_f32_32x32x16_f16 on split factors;
+// v_mfma_f32_32x32x2f32 at P = 3).
 #include "hpsmc_device.h"
 
 namespace hpsmc {
@@ -171,9 +172,9 @@ __device__ __forceinline__ void mma5_fold_rem(int t, const f32x16 &dA, const f32
 // Round kernel, matrix-core form: d = 5, FP32, residual form with the
 // centre-point rule, one path per lane.  The walk (directions from two
 // Philox blocks per step, jump, exit test of eq. indexL, left-point
-// quadrature of eq. interIQ with compensated summation) is the vector-unit
-// kernel's, so both take the same exit steps and differ in u, v only by the
-// order of the FP32 sums.  A step's NCH chunks stream through two LDS buffers
+// quadrature of eq. interIQ, path sums in FP64) is the vector-unit
+// kernel's, so both take the same exit steps and differ in u, v only by
+// rounding.  A step's NCH chunks stream through two LDS buffers
 // along one sequence that runs on into the next step: while a chunk's
 // products run, the next chunk is in flight (global_load_lds), and one
 // barrier per chunk publishes it.
