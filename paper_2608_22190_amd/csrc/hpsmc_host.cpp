@@ -315,10 +315,10 @@ static double phi_legendre(int p, const double *L) { return 2.0 * (p + 1) / (2.0
 // ---------------------------------------------------------------------------
 // rounds split into shares of steps: paths of the largest batch (256 threads, four paths
 // each), and bytes for the window sums of a round at most: 384 batches of 512 paths and 256
-// steps, the most that are split at the launch shapes in use, take 102 MB; five dimensions,
-// with a sum a step, 68 MB at 512 batches of 256 paths and 64 steps
+// steps, the most that are split at the launch shapes in use (256 paths: 512 steps); five
+// dimensions, with a sum a step, take 68 MB at 512 batches of 256 paths and 64 steps
 constexpr int kShareBatch = 1024;
-constexpr int64_t kShareBytes = (int64_t)1 << 27;
+constexpr int64_t kShareBytes = (int64_t)384 * 512 * (256 / 4 + 1) * 8;
 
 struct DevBuf {
     void *p = nullptr;
